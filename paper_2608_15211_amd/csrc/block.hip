@@ -6,7 +6,7 @@
 //
 // One matrix-core GEMM kernel serves every linear layer.  Operands are
 // bf16 row-major matrices in HBM, brought into XOR-swizzled LDS tiles by
-// direct-to-LDS loads through a three-stage ring; the 32 x 16 matrix-core
+// direct-to-LDS loads through a ring of stages; the 32 x 16 matrix-core
 // operands are read either straight (when the contraction index runs along
 // memory rows) or through the LDS transpose read (when it runs down memory
 // columns), so Y = X W^T, dX = dY W and dW = dY^T X all take the same
@@ -29,7 +29,7 @@ typedef __attribute__((address_space(3))) v4s lds_v4s;
 constexpr int kGT = 512;          // threads per GEMM workgroup (8 waves: 2 rows x 4 columns of 128 x 64)
 constexpr int kBM = 256;          // workgroup tile rows
 constexpr int kBN = 256;          // workgroup tile columns (128 in the four-wave form)
-constexpr int kBK = 32;           // contraction depth per stage
+constexpr int kBK = 64;           // contraction depth per stage (32 in the four-wave form)
 constexpr int kEpiS = 68;         // row stride (floats) of a wave's epilogue staging tile
 constexpr int kMaxCusBlock = 256;  // compute units the weight-gradient slices are sized for
 
@@ -101,32 +101,34 @@ __device__ inline float gelu_grad_f(float x) {
 // (kBN x kBK), each in its memory layout, unpadded, with the 16-byte chunks
 // of each row permuted by an XOR of the row index so that the matrix-core
 // operand reads hit distinct banks:
-// * KROW tile (memory [R][kBK], 4 chunks a row): chunk c of row r sits at
-//   chunk c ^ ((r >> 2) & 3) - 16 consecutive rows read at one logical chunk
-//   cover all 64 banks;
-// * COLK tile (memory [kBK][R], R / 8 chunks a row): chunk c of row k sits
+// * KROW tile (memory [R][BK], BK / 8 chunks a row): chunk c of row r sits at
+//   chunk c ^ ((r >> 1) & 7) (BK = 32: c ^ ((r >> 2) & 3)) - 16 consecutive
+//   rows read at one logical chunk cover all 64 banks;
+// * COLK tile (memory [BK][R], R / 8 chunks a row): chunk c of row k sits
 //   at chunk c ^ (4 (k & 3)) - each half-wave of a transpose read takes 64
 //   bytes from each of four rows, and these land on four different 64-byte
 //   spans of the 256 bytes the LDS banks cover (measured: no bank conflicts;
 //   with c ^ (2 (k & 3)) 0.8-2 conflict cycles per LDS instruction, though
 //   no slower).
 // ---------------------------------------------------------------------------
-template <int R, bool KROW, int NT = kGT>
+template <int R, bool KROW, int BK, int NT = kGT>
 struct Tile {
-  static constexpr int kChunks = R * kBK / 8;   // 16-byte chunks
+  static constexpr int kChunks = R * BK / 8;    // 16-byte chunks
   static constexpr int kPer = kChunks / NT;     // per thread (NT threads)
-  static constexpr int kElems = R * kBK;
+  static constexpr int kElems = R * BK;
+  static constexpr int kCpr = BK / 8;           // chunks a row (KROW)
+  __device__ static int swz(int row) { return BK == 64 ? (row >> 1) & 7 : (row >> 2) & 3; }
   // element offset of (row, logical chunk) of the memory layout
   __device__ static int off(int row, int c) {
-    if (KROW) return row * kBK + 8 * (c ^ ((row >> 2) & 3));
+    if (KROW) return row * BK + 8 * (c ^ swz(row));
     return row * R + 8 * (c ^ (4 * (row & 3)));
   }
   // memory (row, column) of the chunk stored in slot q (slot = chunk position in LDS order)
   __device__ static void slot_src(int q, int r0, int k0, int& mrow, int& mcol) {
     if (KROW) {
-      const int row = q >> 2, p = q & 3;
+      const int row = q / kCpr, p = q % kCpr;
       mrow = r0 + row;
-      mcol = k0 + 8 * (p ^ ((row >> 2) & 3));
+      mcol = k0 + 8 * (p ^ swz(row));
     } else {
       const int row = q / (R / 8), p = q - row * (R / 8);
       mrow = k0 + row;
@@ -137,10 +139,10 @@ struct Tile {
 
 // Straight operand (KROW tile): lane l receives T[m0 + l % 32][k0 + 8h + x],
 // x = 0..7, h = l / 32, as one 16-byte read.
-template <int R>
+template <int R, int BK>
 __device__ inline bf16x8 row_operand(const bf16* T, int k0, int m0, int lane) {
   const int row = m0 + (lane & 31);
-  return *reinterpret_cast<const bf16x8*>(T + Tile<R, true>::off(row, (k0 >> 3) + (lane >> 5)));
+  return *reinterpret_cast<const bf16x8*>(T + Tile<R, true, BK>::off(row, (k0 >> 3) + (lane >> 5)));
 }
 
 // Natural-order transposed operand (COLK tile): lane l receives
@@ -148,14 +150,14 @@ __device__ inline bf16x8 row_operand(const bf16* T, int k0, int m0, int lane) {
 // transpose read, lane i gets element i % 4 of the 8 bytes that lane
 // 16G + 4x + i/4 addresses, so lane L addresses row k0 + 8h + (L % 16) / 4
 // (4 rows further for the second read), columns m0 + 16 (G % 2) + 4 (L % 4).
-template <int R>
+template <int R, int BK>
 __device__ inline bf16x8 tr_operand(const bf16* T, int k0, int m0, int lane) {
   const int G = lane >> 4;
   const int row = k0 + 8 * (G >> 1) + ((lane & 15) >> 2);
   const int m = m0 + 16 * (G & 1) + 4 * (lane & 3);
   const int c = m >> 3, e = m & 7;
-  const bf16* p0 = T + Tile<R, false>::off(row, c) + e;
-  const bf16* p1 = T + Tile<R, false>::off(row + 4, c) + e;
+  const bf16* p0 = T + Tile<R, false, BK>::off(row, c) + e;
+  const bf16* p1 = T + Tile<R, false, BK>::off(row + 4, c) + e;
   const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p0);
   const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p1);
   typedef short v8s __attribute__((ext_vector_type(8)));
@@ -165,60 +167,87 @@ __device__ inline bf16x8 tr_operand(const bf16* T, int k0, int m0, int lane) {
 
 // Direct-to-LDS staging of one operand tile: each thread moves kPer 16-byte
 // chunks with buffer loads that write LDS themselves (slot q of the tile is
-// written by thread q % kGT, load q / kGT); chunks outside the operand or
-// the contraction slice read zeros.  KROW: the contraction index runs along
-// memory rows.
-template <int R, bool KROW, int NT = kGT>
-__device__ inline void stage_direct(const i32x4& rs, const Mat& X, bf16* tile, int r0, int k0, int nouter,
-                                    int kend, int64_t base = 0) {
-  typedef Tile<R, KROW, NT> T;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: the LDS base goes to M0
+// written by thread q % NT, load q / NT); chunks outside the operand or the
+// contraction slice read zeros.  The per-thread part of each chunk's address
+// does not change along the contraction, so it is worked out once (init) and
+// a stage costs one add and one bounds select a load.  KROW: the contraction
+// index runs along memory rows.
+template <int R, bool KROW, int BK, int NT>
+struct Stager {
+  typedef Tile<R, KROW, BK, NT> T;
+  int voff[T::kPer];   // byte offset at contraction index 0 (2^31: outside the operand)
+  int kpos[T::kPer];   // the chunk's contraction index inside a stage
+  __device__ void init(const Mat& X, int r0, int nouter, int64_t base) {
 #pragma unroll
-  for (int u = 0; u < T::kPer; ++u) {
-    const int q = u * NT + threadIdx.x;
-    int mr, mc;
-    T::slot_src(q, r0, k0, mr, mc);
-    const bool ok = KROW ? (mr < nouter && mc < kend) : (mr < kend && mc < nouter);
-    const int voff = ok ? (int)((base + (int64_t)mr * X.ld + mc) * 2) : (int)0x80000000;
-    bf16* dst = tile + 8 * (u * NT + wave * 64);       // wave-uniform base of 64 slots
-    raw_buffer_load_lds(rs, (__attribute__((address_space(3))) uint32_t*)(uintptr_t)(uint32_t)(uintptr_t)dst, 16,
-                        voff, 0, 0, 0);
+    for (int u = 0; u < T::kPer; ++u) {
+      int mr, mc;
+      T::slot_src(u * NT + threadIdx.x, r0, 0, mr, mc);
+      kpos[u] = KROW ? mc : mr;
+      const bool ok = (KROW ? mr : mc) < nouter;
+      voff[u] = ok ? (int)((base + (int64_t)mr * X.ld + mc) * 2) : (int)0x80000000;
+    }
   }
-}
+  // koff: byte offset of the stage's first contraction index; krem:
+  // contraction indices left from there
+  __device__ void load(const i32x4& rs, bf16* tile, int koff, int krem) const {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: the LDS base goes to M0
+#pragma unroll
+    for (int u = 0; u < T::kPer; ++u) {
+      const int v = kpos[u] < krem ? voff[u] + koff : (int)0x80000000;
+      bf16* dst = tile + 8 * (u * NT + wave * 64);       // wave-uniform base of 64 slots
+      raw_buffer_load_lds(rs, (__attribute__((address_space(3))) uint32_t*)(uintptr_t)(uint32_t)(uintptr_t)dst, 16,
+                          v, 0, 0, 0);
+    }
+  }
+};
 
 
 // C[M][N] = A[M][K] B[K][N] (+ epilogue).  AKROW: A is memory [M][K]
-// (else [K][M]); BKROW: B is memory [N][K] (else [K][N]).  blockIdx.z:
-// contraction slice [z * kslice, (z+1) * kslice).  Three LDS stages: the
-// loads of stage kt + 2 are in flight while stage kt is on the matrix
-// cores.  Eight waves, each a 128 x 64 block of the 256 x 256 tile.
-// SEG: A is a three-part operand split along K (AKROW; A.segw a multiple of
-// kBK) or along M (else; A.segw a multiple of kBM), so that every stage
-// (AKROW) or every workgroup tile (else) reads one part.
-// NW = 4: four waves and a 256 x 128 tile (72 KB of stages), so that two
-// workgroups share a CU and one's prologue and epilogue (its operand
-// latency, output traffic and, for some epilogues, input traffic) overlap
-// the other's matrix work; for short contractions, where that per-tile time
-// is a large part of the whole.
+// (else [K][M]); BKROW: B is memory [N][K] (else [K][N]).  The grid holds
+// (contraction slice, tile) pairs, slice z over [z * kslice, (z+1) * kslice).
+// Eight waves, each a 128 x 64 block of the 256 x 256 tile.  SEG: A is a
+// three-part operand split along K (AKROW; A.segw a multiple of kBK) or
+// along M (else; A.segw a multiple of kBM), so that every stage (AKROW) or
+// every workgroup tile (else) reads one part.
+//
+// What bounds it: the matrix cores and the L2 -> LDS stream about equally.
+// On 131072 x 768 x 3072 the matrix instructions alone take 367 us (the
+// clock drops to 1.9 GHz under them), the loads alone 361 us (4.8 GB through
+// the L2s), the LDS reads hide under either; together 500 us, 1240 TFLOP/s.
+// * The two waves of a SIMD (w and w + 4) take turns: while one half of the
+//   workgroup issues its 32-deep matrix cluster, the other reads its next
+//   operands from LDS and issues its loads, with a barrier after each turn.
+//   Against all eight waves reading and then multiplying together: the same
+//   product 620 -> 569 us, the weight gradients (transpose reads) 918 -> 603.
+// * Stages are 64 deep, so that a K-major row piece is a whole 128-byte
+//   line: the L2 serves half as many requests (569 -> 500 us).  Three stages
+//   of A (activations, further away) and two of B fill the 160 KB of LDS.
+// * Each XCD takes one contiguous run of (slice, tile) pairs whatever their
+//   number, so that the tiles of one token slice share an L2 (weight
+//   gradient of 3072 x 768: L2 misses 2.8e7 -> 1.1e7).
+// NW = 4: four waves and a 256 x 128 tile with 32-deep stages (72 KB, two
+// workgroups a CU), for the rows past whole rounds of 256 x 256 tiles.
 template <bool AKROW, bool BKROW, int EPI, bool SEG = false, int NW = 8>
 __global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, EpiArgs ep, int M, int N, int K,
                                                                 int kslice) {
-  constexpr int NT = NW * 64, BN = NW * 32;
-  typedef Tile<kBM, AKROW, NT> TA;
-  typedef Tile<BN, BKROW, NT> TB;
-  constexpr int kStage = TA::kElems + TB::kElems;
-  constexpr int kLoads = TA::kPer + TB::kPer;
+  constexpr int NT = NW * 64, BN = NW * 32, BK = NW == 8 ? kBK : 32;
+  typedef Tile<kBM, AKROW, BK, NT> TA;
+  typedef Tile<BN, BKROW, BK, NT> TB;
   extern __shared__ __align__(16) char smem[];
   bf16* lds = reinterpret_cast<bf16*>(smem);
 
   const int nN = (N + BN - 1) / BN;
   const int nM = (M + kBM - 1) / kBM;
   const int tiles = nM * nN;
-  int w = blockIdx.x;
-  if (tiles % 8 == 0) w = (blockIdx.x % 8) * (tiles / 8) + blockIdx.x / 8;   // same-XCD neighbours
+  // Workgroups go to the 8 XCDs in turn; each XCD takes one contiguous run
+  // of (slice, tile) pairs, so that the tiles sharing operand rows sit
+  // behind one L2.
+  const int total = gridDim.x, xcd = blockIdx.x & 7;
+  const int w0 = xcd * (total >> 3) + min(xcd, total & 7) + (blockIdx.x >> 3);
+  const int z = w0 / tiles, w = w0 - z * tiles;
   const int tm = w / nN, tn = w - (w / nN) * nN;
   const int m0 = tm * kBM, n0 = tn * BN;
-  const int kbeg = blockIdx.z * kslice;
+  const int kbeg = z * kslice;
   const int kend = min(K, kbeg + kslice);
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -232,47 +261,131 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, Epi
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
 
-  auto a_tile = [&](int st) { return lds + st * kStage; };
-  auto b_tile = [&](int st) { return lds + st * kStage + TA::kElems; };
-  auto issue = [&](int s) {
-    const int k0 = kbeg + s * kBK;
+  Stager<kBM, AKROW, BK, NT> sa;
+  Stager<BN, BKROW, BK, NT> sb;
+  int seg = 0;
+  if constexpr (SEG && !AKROW) {
+    seg = m0 / A.segw;
+    sa.init(A, m0 - seg * A.segw, min(M - seg * A.segw, A.segw), seg * A.segstride);
+  } else {
+    sa.init(A, m0, M, 0);
+  }
+  sb.init(B, n0, N, 0);
+  const int kba = AKROW ? 2 : 2 * A.ld, kbb = BKROW ? 2 : 2 * B.ld;   // bytes per contraction index
+  // LDS rings: kRA stages of A, then kRB stages of B
+  constexpr int kRA = 3, kRB = NW == 8 ? 2 : 3;
+  auto a_tile = [&](int st) { return lds + st * TA::kElems; };
+  auto b_tile = [&](int st) { return lds + kRA * TA::kElems + st * TB::kElems; };
+  auto issue_a = [&](int s, int st) {
+    const int k0 = kbeg + s * BK;
     if constexpr (SEG && AKROW) {
-      const int seg = k0 / A.segw;
-      stage_direct<kBM, true, NT>(rsa, A, a_tile(s % 3), m0, k0 - seg * A.segw, M,
-                                  min(kend - seg * A.segw, A.segw), seg * A.segstride);
-    } else if constexpr (SEG) {
-      const int seg = m0 / A.segw;
-      stage_direct<kBM, false, NT>(rsa, A, a_tile(s % 3), m0 - seg * A.segw, k0, min(M - seg * A.segw, A.segw),
-                                   kend, seg * A.segstride);
+      // the stage's part of the operand: its offset replaces the column's
+      const int sg = k0 / A.segw;
+      const int ks = k0 - sg * A.segw;
+      sa.load(rsa, a_tile(st), (int)((sg * A.segstride + ks) * 2), min(kend - k0, A.segw - ks));
     } else {
-      stage_direct<kBM, AKROW, NT>(rsa, A, a_tile(s % 3), m0, k0, M, kend);
+      sa.load(rsa, a_tile(st), k0 * kba, kend - k0);
     }
-    stage_direct<BN, BKROW, NT>(rsb, B, b_tile(s % 3), n0, k0, N, kend);
+  };
+  auto issue_b = [&](int s, int st) {
+    const int k0 = kbeg + s * BK;
+    sb.load(rsb, b_tile(st), k0 * kbb, kend - k0);
   };
 
-  const int nk = (kend - kbeg + kBK - 1) / kBK;
-  if (nk > 0) issue(0);
-  if (nk > 1) issue(1);
-  for (int kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < nk) wait_vm<kLoads>();
-    else wait_vm<0>();
-    lds_barrier();     // stage kt is in LDS; stage kt + 1 may still be loading
-    if (kt + 2 < nk) issue(kt + 2);
-    const bf16* ta = a_tile(kt % 3);
-    const bf16* tb = b_tile(kt % 3);
+  const int nk = (kend - kbeg + BK - 1) / BK;
+  bf16x8 ao[2][4], bo[2][2];
+  // operands of the 32 contraction indices from 32 * hf of a stage
+  auto read_ops = [&](const bf16* ta, const bf16* tb, int hf) {
 #pragma unroll
-    for (int c = 0; c < kBK / 16; ++c) {
-      bf16x8 bo[2];
+    for (int c = 0; c < 2; ++c) {
+      const int k0 = 32 * hf + 16 * c;
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        bo[j] = BKROW ? row_operand<BN>(tb, 16 * c, wn + 32 * j, lane) : tr_operand<BN>(tb, 16 * c, wn + 32 * j, lane);
+        bo[c][j] = BKROW ? row_operand<BN, BK>(tb, k0, wn + 32 * j, lane) : tr_operand<BN, BK>(tb, k0, wn + 32 * j, lane);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bf16x8 ao =
-            AKROW ? row_operand<kBM>(ta, 16 * c, wm + 32 * i, lane) : tr_operand<kBM>(ta, 16 * c, wm + 32 * i, lane);
+      for (int i = 0; i < 4; ++i)
+        ao[c][i] =
+            AKROW ? row_operand<kBM, BK>(ta, k0, wm + 32 * i, lane) : tr_operand<kBM, BK>(ta, k0, wm + 32 * i, lane);
+    }
+  };
+  auto mfmas = [&]() {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) mma16(acc[i][j], ao, bo[j]);
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) mma16(acc[i][j], ao[c][i], bo[c][j]);
+  };
+  if constexpr (NW == 8) {
+    // Turn 4 kt + 2 hf: the first half of the workgroup reads half hf of
+    // stage kt, the second half multiplies what it read in its last turn;
+    // in the next turn they swap.  A stage's buffer is free after turn
+    // 4 kt + 3, so the loads of B's stage kt + 1 (two buffers) go out while
+    // half 0 of stage kt is read, those of A's stage kt + 2 (three) while
+    // half 1 is.
+    const bool second = __builtin_amdgcn_readfirstlane(wave) >= NW / 2;
+    if (nk > 0) {
+      issue_a(0, 0);
+      issue_b(0, 0);
+    }
+    if (nk > 1) {
+      issue_a(1, 1);
+      wait_vm<TA::kPer>();
+    } else {
+      wait_vm<0>();
+    }
+    lds_barrier();
+    if (second) lds_barrier();
+    int sa3 = 0;               // kt % 3
+    for (int kt = 0; kt < nk; ++kt) {
+      const bf16* ta = a_tile(sa3);
+      const bf16* tb = b_tile(kt & 1);
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        read_ops(ta, tb, hf);
+        if (hf == 0) {
+          if (kt + 1 < nk) issue_b(kt + 1, (kt + 1) & 1);
+        } else {
+          if (kt + 2 < nk) issue_a(kt + 2, sa3 == 0 ? 2 : sa3 - 1);
+        }
+        auto wait_next = [&]() {     // stage kt + 1 is in LDS (A of stage kt + 2 may be in flight)
+          if (hf == 1) {
+            if (kt + 2 < nk) wait_vm<TA::kPer>();
+            else wait_vm<0>();
+          }
+        };
+        if (second) wait_next();
+        __builtin_amdgcn_sched_barrier(0);
+        lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
+        mfmas();
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (!second) wait_next();
+        lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
       }
+      sa3 = sa3 == 2 ? 0 : sa3 + 1;
+    }
+    if (!second) lds_barrier();
+  } else {
+    constexpr int kLoads = TA::kPer + TB::kPer;
+    for (int s = 0; s < 2; ++s)
+      if (s < nk) { issue_a(s, s); issue_b(s, s); }
+    int st = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+      if (kt + 1 < nk) wait_vm<kLoads>();
+      else wait_vm<0>();
+      lds_barrier();     // stage kt is in LDS; stage kt + 1 may still be loading
+      if (kt + 2 < nk) {
+        const int nx = st == 0 ? 2 : st - 1;
+        issue_a(kt + 2, nx);
+        issue_b(kt + 2, nx);
+      }
+      read_ops(a_tile(st), b_tile(st), 0);
+      mfmas();
+      st = st == 2 ? 0 : st + 1;
     }
   }
   __syncthreads();   // every wave is done with the stages: their LDS now stages the epilogue
@@ -355,7 +468,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, Epi
           for (int x = 0; x < 8; ++x) cs[q][x] += (float)t[x];
         }
       } else if (EPI == EPI_F32 || EPI == EPI_F32_ACC) {
-        float* dst = ep.outf + (EPI == EPI_F32 ? (int64_t)blockIdx.z * M * N : 0) + o;
+        float* dst = ep.outf + (EPI == EPI_F32 ? (int64_t)z * M * N : 0) + o;
         if (EPI == EPI_F32_ACC) {
           const float4 a0 = *reinterpret_cast<const float4*>(dst);
           const float4 a1 = *reinterpret_cast<const float4*>(dst + 4);
@@ -703,12 +816,12 @@ __global__ __launch_bounds__(256) void transpose_kernel(const bf16* __restrict__
 template <bool AKROW, bool BKROW, int EPI, bool SEG = false, int NW = 8>
 static hipError_t gemm(const Mat& A, const Mat& B, const EpiArgs& ep, int M, int N, int K, int nsplit,
                        hipStream_t st) {
-  constexpr int BN = NW * 32;
-  // three stages: 96 KB (eight waves), 72 KB (four)
-  constexpr size_t lds = 3 * (size_t)(kBM + BN) * kBK * sizeof(bf16);
+  constexpr int BN = NW * 32, BK = NW == 8 ? kBK : 32;
+  // three stages of A, two (four waves: three) of B: 160 KB (72 KB)
+  constexpr size_t lds = (3 * (size_t)kBM + (NW == 8 ? 2 : 3) * (size_t)BN) * BK * sizeof(bf16);
   const int tiles = ((M + kBM - 1) / kBM) * ((N + BN - 1) / BN);
-  const int kslice = ((K + nsplit - 1) / nsplit + kBK - 1) / kBK * kBK;
-  hipLaunchKernelGGL((gemm_kernel<AKROW, BKROW, EPI, SEG, NW>), dim3(tiles, 1, nsplit), dim3(NW * 64), lds, st, A, B,
+  const int kslice = ((K + nsplit - 1) / nsplit + BK - 1) / BK * BK;
+  hipLaunchKernelGGL((gemm_kernel<AKROW, BKROW, EPI, SEG, NW>), dim3(tiles * nsplit), dim3(NW * 64), lds, st, A, B,
                      ep, M, N, K, kslice);
   return hipGetLastError();
 }
@@ -736,7 +849,6 @@ static hipError_t gemm_rounds(const Mat& A, const Mat& B, const EpiArgs& ep, int
   static_assert(EPI == EPI_BF16 || EPI == EPI_BIAS_RES, "row offsets are set for these epilogues");
   const int ntn = (N + kBN - 1) / kBN, nM = (M + kBM - 1) / kBM;
   int r1 = ((nM * ntn) / kMaxCusBlock) * kMaxCusBlock / ntn;   // row tiles in whole rounds
-  while (r1 > 0 && (r1 * ntn) % 8 != 0) --r1;   // a tile count the XCD-grouped order takes
   if (r1 == 0 || r1 >= nM) return gemm<true, BKROW, EPI, SEG>(A, B, ep, M, N, K, 1, st);
   const int m1 = r1 * kBM;
   hipError_t e = gemm<true, BKROW, EPI, SEG>(A, B, ep, m1, N, K, 1, st);
@@ -818,14 +930,14 @@ hipError_t launch_block_fwd(const Geo& g, const void* x, const BlockParams& p, c
   TERRA_TRY(ln_fold(p.w_qkv, p.ln1_g, p.ln1_b, p.b_qkv, wq, sq, cq, 3 * C, C, st));
   ep.out[0] = (bf16*)s.q; ep.out[1] = (bf16*)s.k; ep.out[2] = (bf16*)s.v; ep.split = C;
   ep.mean = s.mu1; ep.rstd = s.rstd1; ep.lns = sq; ep.lnc = cq;
-  TERRA_TRY((gemm<true, true, EPI_LN_QKV, false, 4>(mat(x, C, T), mat(wq, C, 3 * C), ep,
+  TERRA_TRY((gemm<true, true, EPI_LN_QKV, false, 8>(mat(x, C, T), mat(wq, C, 3 * C), ep,
                                                                     T, 3 * C, C, 1, st)));
   // windowed attention with the route fused in
   TERRA_TRY(launch_attn_fwd(g, 1, true, s.q, s.k, s.v, table, s.o, nullptr, s.lse, st));
   // x1 = x + o W_p^T + b_p
   ep = EpiArgs{};
   ep.out[0] = (bf16*)s.x1; ep.split = C; ep.aux = (const bf16*)x; ep.bias = p.b_proj;
-  TERRA_TRY((gemm<true, true, EPI_BIAS_RES, false, 4>(mat(s.o, C, T), mat(p.w_proj, C, C), ep, T, C, C, 1, st)));
+  TERRA_TRY((gemm<true, true, EPI_BIAS_RES, false, 8>(mat(s.o, C, T), mat(p.w_proj, C, C), ep, T, C, C, 1, st)));
   // h = LN2(x1) W_1^T + b_1 (LN2 folded), a = GELU(h)
   TERRA_TRY(ln_stats(s.x1, s.mu2, s.rstd2, T, C, st));
   TERRA_TRY(ln_fold(p.w_fc1, p.ln2_g, p.ln2_b, p.b_fc1, wf, sf, cf, 4 * C, C, st));
@@ -1040,7 +1152,7 @@ hipError_t launch_block_bwd(const Geo& g, const void* dx2, const void* x, const 
   // db1 = colsum(dh) from the same epilogue: per-wave partial rows, then a
   // fixed-order sum of the 2 ceil(T / 256) partials
   ep.out[0] = dh; ep.split = 4 * C; ep.aux = (const bf16*)s.h; ep.colpart = cpart;
-  TERRA_TRY((gemm<true, true, EPI_GELU_GRAD, false, 4>(mat(dx2, C, T), mat(wt_fc2, C, 4 * C), ep, T, 4 * C, C, 1, st)));
+  TERRA_TRY((gemm<true, true, EPI_GELU_GRAD, false, 8>(mat(dx2, C, T), mat(wt_fc2, C, 4 * C), ep, T, 4 * C, C, 1, st)));
   TERRA_TRY(slice_sum(cpart, gr.b_fc1, 4 * C, 2 * ((T + kBM - 1) / kBM), st));
   // h = LN2(x1) W1^T + b1:  dW1 = dh^T LN2(x1), db1 = colsum(dh), dln2 = dh W1
   TERRA_TRY(ln_apply(s.x1, s.mu2, s.rstd2, p.ln2_g, p.ln2_b, lnb, T, C, st));
@@ -1057,7 +1169,7 @@ hipError_t launch_block_bwd(const Geo& g, const void* dx2, const void* x, const 
   TERRA_TRY(colsum(mat(dx1, C, T), C, cpart, gr.b_proj, w, st));
   ep = EpiArgs{};
   ep.out[0] = dO; ep.split = C;
-  TERRA_TRY((gemm<true, true, EPI_BF16, false, 4>(mat(dx1, C, T), mat(wt_proj, C, C), ep, T, C, C, 1, st)));
+  TERRA_TRY((gemm<true, true, EPI_BF16, false, 8>(mat(dx1, C, T), mat(wt_proj, C, C), ep, T, C, C, 1, st)));
   // attention backward (route fused in)
   TERRA_TRY(launch_attn_bwd(g, 1, true, s.q, s.k, s.v, s.o, nullptr, dO, s.lse, table, dqkv[0], dqkv[1],
                             dqkv[2], dtable, ws + w.attn, st));
