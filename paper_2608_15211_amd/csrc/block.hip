@@ -16,6 +16,7 @@
 // backward recomputes them once per weight gradient.  Bias, residual,
 // GELU and its derivative are applied in the epilogue.
 #include <algorithm>
+#include <type_traits>
 
 #include "terra_common.h"
 #include "terra_block.h"
@@ -393,113 +394,127 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, Epi
   // Epilogue, 32 rows of the wave's block at a time: acc[i][j] holds rows
   // 32i + 8g + 4h + x (register 4g + x), column 32j + lane % 32; they go
   // through the wave's own LDS tile so that each lane then handles 8
-  // consecutive columns of one row with 16-byte loads and stores.
+  // consecutive columns of rows 8t + lane / 8, t = 0..3: eight lanes cover
+  // the 64 columns of a row, so every 16-byte load or store instruction
+  // moves whole 128-byte row pieces (bf16), and a lane keeps one set of 8
+  // columns, whose constants it loads once.
   float* et = reinterpret_cast<float*>(smem) + wave * 32 * kEpiS;
   const int h = lane >> 5, col = lane & 31;
-  const int er = lane >> 1, ec = (lane & 1) * 32;     // this lane's row and first column when reading back
+  const int er = lane >> 3, ec = (lane & 7) * 8;
+  const int n = n0 + wn + ec;                          // N is a multiple of 8
   constexpr bool kCol = EPI == EPI_GELU_GRAD;
-  float cs[kCol ? 4 : 1][8] = {};                      // this lane's column sums over its four rows
-  // per-column epilogue constants of this lane's 32 columns, loaded once
-  // for the four row blocks (LayerNorm fold: s and c; bias)
+  float cs[8] = {};                                    // this lane's column sums over its rows
+  // per-column epilogue constants (LayerNorm fold: s and c; bias)
   constexpr bool kLn = EPI == EPI_LN_QKV || EPI == EPI_LN_GELU;
   constexpr int kPc = kLn ? 2 : (EPI == EPI_BIAS_RES ? 1 : 0);
-  float pc[kPc > 0 ? kPc : 1][4][8];
+  float pc[kPc > 0 ? kPc : 1][8];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int n = n0 + wn + ec + 8 * q;     // N is a multiple of 8
-#pragma unroll
-    for (int a = 0; a < kPc; ++a) {
-      const float* src = kLn ? (a == 0 ? ep.lns : ep.lnc) : ep.bias;
-      float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo;
-      if (n < N) {
-        lo = *reinterpret_cast<const float4*>(src + n);
-        hi = *reinterpret_cast<const float4*>(src + n + 4);
-      }
-      pc[a][q][0] = lo.x; pc[a][q][1] = lo.y; pc[a][q][2] = lo.z; pc[a][q][3] = lo.w;
-      pc[a][q][4] = hi.x; pc[a][q][5] = hi.y; pc[a][q][6] = hi.z; pc[a][q][7] = hi.w;
+  for (int a = 0; a < kPc; ++a) {
+    const float* src = kLn ? (a == 0 ? ep.lns : ep.lnc) : ep.bias;
+    float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo;
+    if (n < N) {
+      lo = *reinterpret_cast<const float4*>(src + n);
+      hi = *reinterpret_cast<const float4*>(src + n + 4);
     }
+    pc[a][0] = lo.x; pc[a][1] = lo.y; pc[a][2] = lo.z; pc[a][3] = lo.w;
+    pc[a][4] = hi.x; pc[a][5] = hi.y; pc[a][6] = hi.z; pc[a][7] = hi.w;
   }
+  // Row inputs of one 32-row block (residual or pre-activation pieces, or
+  // the rows' mean and 1/std), fetched one block ahead.  Tiles inside the
+  // matrix take a form without bounds checks: no branch then separates the
+  // loads, which all go out together.
+  constexpr bool kAux = EPI == EPI_BIAS_RES || EPI == EPI_GELU_GRAD;
+  struct RowIn {
+    bf16x8 aux[kAux ? 4 : 1];
+    float mu[kLn ? 4 : 1], rs[kLn ? 4 : 1];
+  };
+  auto epilogue = [&](auto full_c) {
+    constexpr bool kFull = decltype(full_c)::value;
+    auto inside = [&](int m) { return kFull || (m < M && n < N); };
+    auto fetch = [&](int i, RowIn& in) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+      for (int t4 = 0; t4 < 4; ++t4) {
+        const int m = m0 + wm + 32 * i + 8 * t4 + er;
+        if (kAux) {
+          in.aux[t4] = bf16x8{};
+          if (inside(m)) in.aux[t4] = *reinterpret_cast<const bf16x8*>(ep.aux + (int64_t)m * N + n);
+        }
+        if (kLn) {
+          in.mu[t4] = inside(m) ? ep.mean[m] : 0.0f;
+          in.rs[t4] = inside(m) ? ep.rstd[m] : 0.0f;
+        }
+      }
+    };
+    RowIn in[2];
+    if (kAux || kLn) fetch(0, in[0]);
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < 4; ++i) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) et[(8 * (r / 4) + 4 * h + (r % 4)) * kEpiS + 32 * j + col] = acc[i][j][r];
-    __builtin_amdgcn_wave_barrier();
-    const int m = m0 + wm + 32 * i + er;
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int n = n0 + wn + ec + 8 * q;
-      const float4 lo = *reinterpret_cast<const float4*>(et + er * kEpiS + ec + 8 * q);
-      const float4 hi = *reinterpret_cast<const float4*>(et + er * kEpiS + ec + 8 * q + 4);
-      float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-      if (m >= M || n >= N) continue;
-      const int64_t o = (int64_t)m * N + n;
-      if (EPI == EPI_LN_QKV || EPI == EPI_LN_GELU) {
-        const float mu = ep.mean[m], rs = ep.rstd[m];
-        bf16x8 t, g;
+        for (int r = 0; r < 16; ++r) et[(8 * (r / 4) + 4 * h + (r % 4)) * kEpiS + 32 * j + col] = acc[i][j][r];
+      if ((kAux || kLn) && i < 3) fetch(i + 1, in[(i + 1) & 1]);
+      __builtin_amdgcn_wave_barrier();
+      const RowIn& ri = in[i & 1];
+#pragma unroll
+      for (int t4 = 0; t4 < 4; ++t4) {
+        const int m = m0 + wm + 32 * i + 8 * t4 + er;
+        const float4 lo = *reinterpret_cast<const float4*>(et + (8 * t4 + er) * kEpiS + ec);
+        const float4 hi = *reinterpret_cast<const float4*>(et + (8 * t4 + er) * kEpiS + ec + 4);
+        float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        const int64_t o = (int64_t)m * N + n;
+        if (EPI == EPI_F32 || EPI == EPI_F32_ACC) {
+          if (!inside(m)) continue;
+          float* dst = ep.outf + (EPI == EPI_F32 ? (int64_t)z * M * N : 0) + o;
+          if (EPI == EPI_F32_ACC) {
+            const float4 a0 = *reinterpret_cast<const float4*>(dst);
+            const float4 a1 = *reinterpret_cast<const float4*>(dst + 4);
+            v[0] += a0.x; v[1] += a0.y; v[2] += a0.z; v[3] += a0.w;
+            v[4] += a1.x; v[5] += a1.y; v[6] += a1.z; v[7] += a1.w;
+          }
+          *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+          *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
+          continue;
+        }
+        bf16x8 t, u;
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
-          const float y = rs * (v[x] - mu * pc[0][q][x]) + pc[1][q][x];
+          float y = v[x];
+          if (kLn) y = ri.rs[t4] * (y - ri.mu[t4] * pc[0][x]) + pc[1][x];
+          if (EPI == EPI_BIAS_RES) y = y + pc[0][x] + (float)ri.aux[t4][x];
+          if (EPI == EPI_GELU_GRAD) y *= gelu_grad_f((float)ri.aux[t4][x]);
           t[x] = (bf16)y;
-          if (EPI == EPI_LN_GELU) g[x] = (bf16)gelu_f(y);
+          if (EPI == EPI_LN_GELU) u[x] = (bf16)gelu_f(y);
         }
+        if (!inside(m)) continue;
         if (EPI == EPI_LN_QKV) {
           const int blk = n / ep.split;
           *reinterpret_cast<bf16x8*>(ep.out[blk] + (int64_t)m * ep.split + (n - blk * ep.split)) = t;
         } else {
           *reinterpret_cast<bf16x8*>(ep.out[0] + o) = t;
-          *reinterpret_cast<bf16x8*>(ep.out2 + o) = g;
         }
-      } else if (EPI == EPI_BIAS_RES) {
-        const bf16x8 res = *reinterpret_cast<const bf16x8*>(ep.aux + o);
-        bf16x8 t;
+        if (EPI == EPI_LN_GELU) *reinterpret_cast<bf16x8*>(ep.out2 + o) = u;
+        if (kCol) {
 #pragma unroll
-        for (int x = 0; x < 8; ++x) t[x] = (bf16)(v[x] + pc[0][q][x] + (float)res[x]);
-        *reinterpret_cast<bf16x8*>(ep.out[0] + o) = t;
-      } else if (EPI == EPI_GELU_GRAD) {
-        const bf16x8 hv = *reinterpret_cast<const bf16x8*>(ep.aux + o);
-        bf16x8 t;
-#pragma unroll
-        for (int x = 0; x < 8; ++x) t[x] = (bf16)(v[x] * gelu_grad_f((float)hv[x]));
-        *reinterpret_cast<bf16x8*>(ep.out[0] + o) = t;
-        if constexpr (kCol) {
-#pragma unroll
-          for (int x = 0; x < 8; ++x) cs[q][x] += (float)t[x];
+          for (int x = 0; x < 8; ++x) cs[x] += (float)t[x];
         }
-      } else if (EPI == EPI_F32 || EPI == EPI_F32_ACC) {
-        float* dst = ep.outf + (EPI == EPI_F32 ? (int64_t)z * M * N : 0) + o;
-        if (EPI == EPI_F32_ACC) {
-          const float4 a0 = *reinterpret_cast<const float4*>(dst);
-          const float4 a1 = *reinterpret_cast<const float4*>(dst + 4);
-          v[0] += a0.x; v[1] += a0.y; v[2] += a0.z; v[3] += a0.w;
-          v[4] += a1.x; v[5] += a1.y; v[6] += a1.z; v[7] += a1.w;
-        }
-        *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-        *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
-      } else {
-        bf16x8 t;
-#pragma unroll
-        for (int x = 0; x < 8; ++x) t[x] = (bf16)v[x];
-        *reinterpret_cast<bf16x8*>(ep.out[0] + o) = t;
       }
+      __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_wave_barrier();
-  }
+  };
+  if (m0 + kBM <= M && n0 + BN <= N) epilogue(std::true_type{});
+  else epilogue(std::false_type{});
   if constexpr (kCol) {
-    // the wave's 32 lanes of each parity hold four-row sums of the same 32
-    // columns: through the wave's staging tile, lane c then adds column c
-    // over the 32 lanes' rows in order
+    // lanes 8t + c (t = 0..7) hold 16-row sums of columns 8c..8c+7: through
+    // the wave's staging tile, lane l then adds column l over them in order
     if (ep.colpart != nullptr) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int x = 0; x < 8; ++x) et[er * kEpiS + ec + 8 * q + x] = cs[q][x];
+      for (int x = 0; x < 8; ++x) et[er * kEpiS + ec + x] = cs[x];
       __builtin_amdgcn_wave_barrier();
       float sum = 0.0f;
-      for (int r = 0; r < 32; ++r) sum += et[r * kEpiS + lane];
-      const int n = n0 + wn + lane;
-      if (n < N) ep.colpart[(int64_t)(2 * tm + wm / 128) * N + n] = sum;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) sum += et[r * kEpiS + lane];
+      if (n0 + wn + lane < N) ep.colpart[(int64_t)(2 * tm + wm / 128) * N + n0 + wn + lane] = sum;
     }
   }
 }
