@@ -73,28 +73,33 @@ struct EpiArgs {
   float* colpart;
 };
 
-// Phi(x), the standard normal distribution function, and exp(-x^2 / 2), with
-// erf from Abramowitz and Stegun's rational approximation 7.1.26
-// (|error| <= 1.5e-7, far below bf16 resolution); the Gaussian factor is
-// shared between erf and the GELU derivative.
-__device__ inline void phi_gauss(float x, float& Phi, float& gauss) {
-  const float z = fabsf(x) * 0.70710678118654752f;
-  const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * z);
-  gauss = __expf(-0.5f * x * x);
-  const float poly =
-      t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-  const float erfz = 1.0f - poly * gauss;
-  Phi = 0.5f * (1.0f + copysignf(erfz, x));
+// Phi(x), the standard normal distribution function: with a = |x|,
+// Phi(-a) = 2^P(a), P a degree-8 polynomial fitted to log2 Phi(-a) on
+// [0, 5.6] (weighted minimax, error of Phi at most 4.5e-8 in float32
+// arithmetic; P falls without bound beyond, where Phi(-a) < 1.1e-8).  One
+// exponential and no division: the MLP epilogues are bound by vector
+// instructions.  Against Abramowitz and Stegun's 7.1.26 (a reciprocal and an
+// exponential, error 7.5e-8) the fc1 epilogue goes from 21.6 to 17.6
+// instructions an element and the 128 x 1080 fc1 product from 1026 to 959 us,
+// dh from 890 to 851.
+__device__ inline float phi_f(float x) {
+  const float a = fabsf(x);
+  float p = -2.772049e-06f;
+  p = fmaf(p, a, 3.8620746e-05f);
+  p = fmaf(p, a, -1.8254759e-04f);
+  p = fmaf(p, a, -1.4587014e-04f);
+  p = fmaf(p, a, 7.0754718e-03f);
+  p = fmaf(p, a, -5.2505028e-02f);
+  p = fmaf(p, a, -0.45920491f);
+  p = fmaf(p, a, -1.1511058f);
+  p = fmaf(p, a, -1.0f);
+  const float w = __builtin_amdgcn_exp2f(p);
+  return x > 0.0f ? 1.0f - w : w;
 }
-__device__ inline float gelu_f(float x) {
-  float Phi, g;
-  phi_gauss(x, Phi, g);
-  return x * Phi;
-}
+__device__ inline float gelu_f(float x) { return x * phi_f(x); }
+// Phi(x) + x phi(x), phi(x) = 2^(-x^2 log2(e) / 2 - log2(sqrt(2 pi)))
 __device__ inline float gelu_grad_f(float x) {
-  float Phi, g;
-  phi_gauss(x, Phi, g);
-  return Phi + x * 0.39894228040143268f * g;   // Phi(x) + x phi(x)
+  return fmaf(x, __builtin_amdgcn_exp2f(fmaf(x * x, -0.72134752f, -1.3257481f)), phi_f(x));
 }
 
 // ---------------------------------------------------------------------------
