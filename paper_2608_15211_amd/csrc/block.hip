@@ -201,8 +201,7 @@ struct Stager {
     for (int u = 0; u < T::kPer; ++u) {
       const int v = kpos[u] < krem ? voff[u] + koff : (int)0x80000000;
       bf16* dst = tile + 8 * (u * NT + wave * 64);       // wave-uniform base of 64 slots
-      raw_buffer_load_lds(rs, (__attribute__((address_space(3))) uint32_t*)(uintptr_t)(uint32_t)(uintptr_t)dst, 16,
-                          v, 0, 0, 0);
+      buffer_load_lds16(rs, dst, v);
     }
   }
 };
