@@ -26,7 +26,10 @@
 // * The bias-table gradient is summed per workgroup in LDS (one head per
 //   workgroup, many windows per workgroup), written as per-workgroup
 //   partials, and reduced in a fixed order by a second kernel.
+#include <type_traits>
+
 #include "terra_common.h"
+#include "terra_tile.h"
 
 namespace terra {
 
@@ -932,17 +935,10 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_kernel(
 // ---------------------------------------------------------------------------
 // Backward, step 2: dK and dV.  Grid: B * nwin * heads * nkc (key chunks of
 // 128; a wave owns 32 keys and walks the window's queries in LDS tiles).
-// 16-bit types ask for two resident workgroups per CU: at head_dim 128 the
-// compiler otherwise takes 280 registers (one wave per SIMD).  Capped at 256
-// (two waves per SIMD) it keeps the matrix loop free of spills and spills 5
-// (window-major) or 8 (NHWC) words of staging addresses, reloaded once per
-// 64-query tile; the loop's lean form below took that down from 17 and 21
-// words (backward -2 % at 1024-token windows, -6 % at 64-token ones).
-// Three workgroups per CU (168 registers) spill inside the loop at
-// head_dim 64 and run 25 % slower.
+// float32 only: the 16-bit types have a kernel of their own below.
 // ---------------------------------------------------------------------------
 template <typename T, int HD, bool NHWC, bool QUAD>
-__global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 2 : 1) void bwd_dkdv_kernel(
+__global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const T* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ D,
     const float* __restrict__ table, T* __restrict__ dk, T* __restrict__ dv,
@@ -1038,8 +1034,8 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 2 : 1) void bwd_dkdv_ker
       tile_load_tt(rd, dout, g, wt, tt, t0, n, hoff);
     }
     lds_barrier();
-    tile_store<T, HD, true, sizeof(T) == 4>(rq, qr, qtt);
-    tile_store<T, HD, true, sizeof(T) == 4>(rd, dr, dtt);
+    tile_store<T, HD, true, true>(rq, qr, qtt);
+    tile_store<T, HD, true, true>(rd, dr, dtt);
     if (threadIdx.x < kTile) {
       if constexpr (kTab) {
         qinfo[threadIdx.x] = winf;
@@ -1133,16 +1129,11 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 2 : 1) void bwd_dkdv_ker
       for (int eb = 0; eb < HD / 32; ++eb) {
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-          if constexpr (sizeof(T) == 2) {
-            mma16(dvacc[eb], lds_tr_op<T, HD + kPad>(dr, qb, c, eb, lane), pack8<T>(s, 8 * c));
-            mma16(dkacc[eb], lds_tr_op<T, HD + kPad>(qr, qb, c, eb, lane), pack8<T>(ds, 8 * c));
-          } else {
-            const int cofs = qb * 32 + 16 * c;
-            mma16(dvacc[eb], load_op_lds_perm<T>(dtt + tr_row<T, HD>(eb * 32 + col) + cofs, half),
-                  pack8<T>(s, 8 * c));
-            mma16(dkacc[eb], load_op_lds_perm<T>(qtt + tr_row<T, HD>(eb * 32 + col) + cofs, half),
-                  pack8<T>(ds, 8 * c));
-          }
+          const int cofs = qb * 32 + 16 * c;
+          mma16(dvacc[eb], load_op_lds_perm<T>(dtt + tr_row<T, HD>(eb * 32 + col) + cofs, half),
+                pack8<T>(s, 8 * c));
+          mma16(dkacc[eb], load_op_lds_perm<T>(qtt + tr_row<T, HD>(eb * 32 + col) + cofs, half),
+                pack8<T>(ds, 8 * c));
         }
       }
     }
@@ -1161,6 +1152,280 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 2 : 1) void bwd_dkdv_ker
         vrow[e + x] = from_float<T>(dvacc[eb][4 * grp + x]);
       }
     }
+}
+
+// ---------------------------------------------------------------------------
+// dK and dV for the 16-bit types.  A workgroup of NW waves owns NW x 32 keys
+// of one (window, head) and walks the window's queries in tiles of 64.
+// What bounds it: latency, at two waves per SIMD (registers).  So
+// * everything per query that does not depend on the tile (row address, bias
+//   offset, label, log-sum-exp, D) is worked out once per workgroup into
+//   LDS, and direct-to-LDS loads fill two tile buffers: one barrier a tile,
+//   no wait for a load just issued;
+// * up to head dim 64 the compiler is held to four phases that each issue
+//   the LDS reads of the next;
+// * masked and unmasked windows have their own copy of the walk (merged in
+//   one loop, the accumulators are copied and spill);
+// * all chunks and heads of a window go to one XCD, whose L2 then serves
+//   their common tiles, and dK, dV leave in whole row pieces.
+// Measured (us, before -> now): 64-token windows of 32 channels on 128 x 256
+// x 6 heads 28 -> 19, 144 tokens 65 -> 47, 576 tokens of 64 channels 1820 ->
+// 1603, 1024 tokens of 128 channels 1650 -> 1381, 64 tokens 458 -> 434.
+// ---------------------------------------------------------------------------
+template <typename T, int HD, bool NHWC, bool QUAD, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
+    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+    const T* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ D,
+    const float* __restrict__ table, T* __restrict__ dk, T* __restrict__ dv,
+    Geo g, int nkc, float scale_log2, float scale) {
+  constexpr int NT = NW * 64;
+  constexpr int kTB = 64 * HD * 2;                    // bytes of one tile
+  const int nP = (g.wh * g.ww + 63) & ~63;
+  extern __shared__ __align__(16) char smem[];
+  char* tiles = smem;                                 // {Q, dO} x 2 buffers
+  uint32_t* tokb = reinterpret_cast<uint32_t*>(smem + 4 * kTB);   // [nP] byte offsets
+  int* qnb = reinterpret_cast<int*>(tokb + nP);       // [nP] 4 x bias offset
+  int* qlab = qnb + nP;                               // [nP] label
+  float* ql = reinterpret_cast<float*>(qlab + nP);     // [nP] log-sum-exp, log2 units
+  float* qd = ql + nP;                                // [nP] -D
+  float* tab = qd + nP;                               // [nbins+4], forward order
+
+  int bid = xcd_item(blockIdx.x, gridDim.x);
+  if (bid >= g.B * g.nwin * g.heads * nkc) return;
+  const int kc = bid % nkc; bid /= nkc;
+  const int h = bid % g.heads; bid /= g.heads;
+  const int w = bid % g.nwin;
+  const int b = bid / g.nwin;
+  const int i = w / g.Mw, j = w - (w / g.Mw) * g.Mw;
+  const int cols = win_cols(g, j);
+  const int n = win_rows(g, i) * cols;
+  const int kbase = kc * NW * 32;
+  if (kbase >= n) return;
+  const WinTokens<NHWC> wt(g, b, i, j);
+  // bias and log-sum-exp in score units (head dim 128) or log2 units
+  const float lscale = HD == 128 ? sqrtf((float)HD) : kLog2e;
+  const int nr = (n + 63) & ~63;
+  for (int t = threadIdx.x; t < nr; t += NT) {
+    const uint32_t tok = wt.tok(g, min(t, n - 1));
+    const int inf = token_info(g, i, j, cols, t, n);
+    const uint32_t li = wt.img0 * (uint32_t)g.heads + (uint32_t)(h * g.HW) + (tok - wt.img0);
+    tokb[t] = (tok - wt.img0) * (uint32_t)(g.C * 2) + (uint32_t)(h * HD * 2);
+    qnb[t] = 4 * (inf & 0xFFFFFF);
+    qlab[t] = inf >> 24;
+    ql[t] = t < n ? lse[li] * lscale : INFINITY;      // padding queries: P = 0
+    qd[t] = t < n ? -D[li] : 0.0f;
+  }
+  for (int x = threadIdx.x; x < g.nbins + 4; x += NT)
+    tab[x] = x < g.nbins ? table[x * g.heads + h] * lscale : -INFINITY;
+  const bool mask = window_has_labels(g, i, j) || (n % 64) != 0;
+
+  const int64_t img = (int64_t)wt.img0 * g.C;
+  const uint32_t ibytes = (uint32_t)g.HW * (uint32_t)(g.C * 2);
+  const i32x4 rq = buffer_rsrc(q + img, ibytes), rd = buffer_rsrc(dout + img, ibytes);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int half = lane >> 5, col = lane & 31;
+  const int ki = kbase + wave * 32 + col;
+  const bool kvalid = ki < n;
+  const bool wactive = kbase + wave * 32 < n;         // else staging and barriers only
+  const int kinf = token_info(g, i, j, cols, kvalid ? ki : 0, n);
+  const int klab = kvalid ? (kinf >> 24) : 0xFE;
+  const int kfwd = (g.wh - 1) * g.bstride + (g.ww - 1) - (kinf & 0xFFFFFF);
+  const char* tabk = reinterpret_cast<const char*>(tab + kfwd);
+
+  lds_barrier();                                      // the row table
+  tile_load_direct<HD, NT>(rq, tiles, tokb, 0);
+  tile_load_direct<HD, NT>(rd, tiles + kTB, tokb, 0);
+  typename Operand<T>::type kop[HD / 16], vop[HD / 16];
+  const uint32_t ktok = wt.tok(g, min(ki, n - 1)) * g.C + h * HD;
+#pragma unroll
+  for (int c = 0; c < HD / 16; ++c) {
+    kop[c] = kvalid ? load_op_global<T>(k + ktok + 16 * c + 8 * half) : zero_op<T>();
+    vop[c] = kvalid ? load_op_global<T>(v + ktok + 16 * c + 8 * half) : zero_op<T>();
+  }
+  f32x16 dkacc[HD / 32], dvacc[HD / 32];
+#pragma unroll
+  for (int eb = 0; eb < HD / 32; ++eb) { dkacc[eb] = f32x16{}; dvacc[eb] = f32x16{}; }
+
+  // bias of the block's queries: quads of consecutive queries of one window
+  // row where QUAD
+  auto bias = [&](int q0, auto masked) {
+    f32x16 c;
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+      const int qq = q0 + 8 * g4 + 4 * half;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int qx = QUAD ? qq : qq + x;
+        c[4 * g4 + x] = reinterpret_cast<const float*>(tabk + qnb[qx])[QUAD ? x : 0];
+        if (decltype(masked)::value && qlab[qx] != klab) c[4 * g4 + x] = -INFINITY;
+      }
+    }
+    return c;
+  };
+  TileAddr<HD> ta(lane);
+  typename Operand<T>::type qop[HD == 128 ? 1 : HD / 16];
+  // One block of 32 queries, rows 32 rb of the tile at t0.
+  auto body = [&](const char* qr, const char* dr, int t0, int rb, auto masked) {
+    const int q0 = t0 + 32 * rb;
+    if constexpr (HD == 128) {
+      // the score accumulator starts at bias - LSE (score units), the dP one
+      // at -D: nothing per query stays in registers across the products
+      ta.opaque();
+      f32x16 s = bias(q0, masked), dp;
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(qd + q0 + 8 * g4 + 4 * half);
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(ql + q0 + 8 * g4 + 4 * half);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          dp[4 * g4 + x] = d4[x];
+          s[4 * g4 + x] -= l4[x];
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < HD / 16; ++c) {
+        mma16(s, tile_row_op<T, HD>(qr, ta, 32 * rb, c), kop[c]);
+        mma16(dp, tile_row_op<T, HD>(dr, ta, 32 * rb, c), vop[c]);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        s[r] = __builtin_amdgcn_exp2f(s[r] * scale_log2);
+        dp[r] *= s[r];
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const auto pop = pack8<T>(s, 8 * c);
+        const auto sop = pack8<T>(dp, 8 * c);
+#pragma unroll
+        for (int eb = 0; eb < HD / 32; ++eb) {
+          mma16(dvacc[eb], tile_tr_op<T, HD>(dr, ta, rb, c, eb), pop);
+          mma16(dkacc[eb], tile_tr_op<T, HD>(qr, ta, rb, c, eb), sop);
+        }
+      }
+    } else {
+      // Four phases the compiler may not move work across; each issues the
+      // LDS reads of the next, so that no product waits for its operands.
+      // bias - LSE (log2 units) is added to the scores after the product.
+      typename Operand<T>::type dop[HD / 16], dtr[HD / 16], qtr[HD / 16];
+      f32x16 s = f32x16{}, dp;
+      if (rb == 0) {
+#pragma unroll
+        for (int c = 0; c < HD / 16; ++c) qop[c] = tile_row_op<T, HD>(qr, ta, 32 * rb, c);
+      }
+#pragma unroll
+      for (int c = 0; c < HD / 16; ++c) dop[c] = tile_row_op<T, HD>(dr, ta, 32 * rb, c);
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(qd + q0 + 8 * g4 + 4 * half);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) dp[4 * g4 + x] = d4[x];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < HD / 16; ++c) mma16(s, qop[c], kop[c]);
+      f32x16 bl = bias(q0, masked);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < HD / 16; ++c) mma16(dp, dop[c], vop[c]);
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int eb = 0; eb < HD / 32; ++eb) dtr[c * HD / 32 + eb] = tile_tr_op<T, HD>(dr, ta, rb, c, eb);
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(ql + q0 + 8 * g4 + 4 * half);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const int r = 4 * g4 + x;
+          s[r] = __builtin_amdgcn_exp2f(s[r] * scale_log2 + (bl[r] - l4[x]));
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const auto pop = pack8<T>(s, 8 * c);
+#pragma unroll
+        for (int eb = 0; eb < HD / 32; ++eb) mma16(dvacc[eb], dtr[c * HD / 32 + eb], pop);
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int eb = 0; eb < HD / 32; ++eb) qtr[c * HD / 32 + eb] = tile_tr_op<T, HD>(qr, ta, rb, c, eb);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dp[r] *= s[r];
+      __builtin_amdgcn_sched_barrier(0);
+      if (rb == 0) {
+#pragma unroll
+        for (int c = 0; c < HD / 16; ++c) qop[c] = tile_row_op<T, HD>(qr, ta, 32, c);
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const auto sop = pack8<T>(dp, 8 * c);
+#pragma unroll
+        for (int eb = 0; eb < HD / 32; ++eb) mma16(dkacc[eb], qtr[c * HD / 32 + eb], sop);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto tile = [&](const char* qr, const char* dr, int t0, auto masked) {
+    if constexpr (HD == 128) {
+#pragma unroll 1
+      for (int rb = 0; rb < 2; ++rb) body(qr, dr, t0, rb, masked);
+    } else {
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) body(qr, dr, t0, rb, masked);
+    }
+  };
+  // one copy of the walk for each kind of window: merging the two in the
+  // loop costs the accumulators copies and spills
+  auto walk = [&](auto masked) {
+    int buf = 0;
+    for (int t0 = 0; t0 < n; t0 += 64, buf ^= 1) {
+      wait_vm<0>();
+      lds_barrier();        // tile t0 is in LDS; every wave is done with the other buffer
+      if (t0 + 64 < n) {
+        tile_load_direct<HD, NT>(rq, tiles + (buf ^ 1) * 2 * kTB, tokb, t0 + 64);
+        tile_load_direct<HD, NT>(rd, tiles + (buf ^ 1) * 2 * kTB + kTB, tokb, t0 + 64);
+      }
+      if (!wactive) continue;
+      const char* qr = tiles + buf * 2 * kTB;
+      const char* dr = qr + kTB;
+      tile(qr, dr, t0, masked);
+    }
+    // dK, dV rows leave through the wave's own LDS rows (the tile buffers), so
+    // that each store instruction moves whole row pieces
+    lds_barrier();
+    if (!wactive) return;
+    T* et = reinterpret_cast<T*>(tiles) + wave * 32 * HD;
+  #pragma unroll
+    for (int o = 0; o < 2; ++o) {
+  #pragma unroll
+      for (int eb = 0; eb < HD / 32; ++eb)
+  #pragma unroll
+        for (int grp = 0; grp < 4; ++grp) {
+          typedef T v4 __attribute__((ext_vector_type(4)));
+          v4 p;
+  #pragma unroll
+          for (int x = 0; x < 4; ++x)
+            p[x] = from_float<T>(o == 0 ? dkacc[eb][4 * grp + x] * scale : dvacc[eb][4 * grp + x]);
+          *reinterpret_cast<v4*>(et + tile_off<HD>(col, eb * 32 + 8 * grp + 4 * half)) = p;
+        }
+      __builtin_amdgcn_wave_barrier();
+      T* dst = o == 0 ? dk : dv;
+      constexpr int kCpr = HD / 8;
+  #pragma unroll
+      for (int u = 0; u < kCpr / 2; ++u) {
+        const int r = (u * 64 + lane) / kCpr, c = (u * 64 + lane) % kCpr;
+        const uint4 x = *reinterpret_cast<const uint4*>(et + tile_off<HD>(r, 8 * c));
+        const int t = kbase + wave * 32 + r;
+        if (t < n)
+          *reinterpret_cast<uint4*>(reinterpret_cast<char*>(dst + img) + tokb[t] + 16 * c) = x;
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  };
+  if (mask) walk(std::true_type{});
+  else walk(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------
@@ -1197,6 +1462,16 @@ static size_t dkdv_lds(const Geo& g) {
   constexpr int kTile = tile_of<T, HD>();
   return sizeof(T) * (2 * kTile * (HD + kPad) + 2 * ttile_size<T, HD>()) + 16 * kTile + 4 * (g.nbins + 4) +
          (HD > 64 ? 4 * g.wh * g.ww : 0);    // token table (head dim 128 only)
+}
+
+// The 16-bit dK/dV kernel: two {Q, dO} tile pairs, five words per window
+// token, the bias table.  Never more than a workgroup has where the dQ
+// kernel's plan (whose five bias copies decide which windows are accepted)
+// fits.
+template <int HD>
+static size_t dkdv16_lds(const Geo& g) {
+  const size_t nP = (g.wh * g.ww + 63) & ~63;
+  return 4 * 64 * HD * 2 + 20 * nP + 4 * (g.nbins + 4);
 }
 
 // Per-head slices of the dQ / bias-gradient kernel.  The grid is one round
@@ -1306,16 +1581,47 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
 #undef TERRA_LAUNCH_DQ
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int grid = g.B * g.nwin * g.heads * nqc;
-  const size_t lds_kv = dkdv_lds<T, HD>(g);
-  if (quad)
-    hipLaunchKernelGGL((bwd_dkdv_kernel<T, HD, NHWC, true>), dim3(grid), dim3(kThreads), lds_kv, st,
-                       (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse, D, table,
-                       (T*)dk, (T*)dv, g, nqc, sl2, scale);
-  else
-    hipLaunchKernelGGL((bwd_dkdv_kernel<T, HD, NHWC, false>), dim3(grid), dim3(kThreads), lds_kv, st,
-                       (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse, D, table,
-                       (T*)dk, (T*)dv, g, nqc, sl2, scale);
+  if constexpr (sizeof(T) == 2) {
+    // Four waves where two workgroups fit a CU's LDS, else eight (1024-token
+    // windows of 128 channels: 2267 us with four, 1381 with eight).  Windows
+    // of up to 256 tokens take fewer waves where that leaves fewer of them
+    // idle; longer ones keep four (576 tokens of 64 channels: 1603 us with
+    // four and a half-empty last chunk, 1890 with three, 1864 with eight).
+    const int nb = (g.wh * g.ww + 31) / 32;
+    const size_t lds_kv = dkdv16_lds<HD>(g);
+    int nw = 2 * lds_kv <= 160 * 1024 ? 4 : 8;
+    if (nb <= 8)
+      for (int c : {4, 3, 2})
+        if (c < nw && (HD == 32 || c != 3) && (nb + c - 1) / c * c < (nb + nw - 1) / nw * nw) nw = c;
+    const int nkc = (nb + nw - 1) / nw;
+    const int grid = grid8(g.B * g.nwin * g.heads * nkc);
+#define TERRA_LAUNCH_KV(QD, NW_)                                                                    \
+  hipLaunchKernelGGL((bwd_dkdv16_kernel<T, HD, NHWC, QD, NW_>), dim3(grid), dim3(NW_ * 64), lds_kv, st, \
+                     (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse, D, table,            \
+                     (T*)dk, (T*)dv, g, nkc, sl2, scale)
+#define TERRA_LAUNCH_KVN(NW_)             \
+  do {                                    \
+    if (quad) TERRA_LAUNCH_KV(true, NW_); \
+    else TERRA_LAUNCH_KV(false, NW_);     \
+  } while (0)
+    if (nw == 4) TERRA_LAUNCH_KVN(4);
+    else if (nw == 2) TERRA_LAUNCH_KVN(2);
+    else if (nw == 8) TERRA_LAUNCH_KVN(8);
+    else if constexpr (HD == 32) TERRA_LAUNCH_KVN(3);
+#undef TERRA_LAUNCH_KVN
+#undef TERRA_LAUNCH_KV
+  } else {
+    const int grid = g.B * g.nwin * g.heads * nqc;
+    const size_t lds_kv = dkdv_lds<T, HD>(g);
+    if (quad)
+      hipLaunchKernelGGL((bwd_dkdv_kernel<T, HD, NHWC, true>), dim3(grid), dim3(kThreads), lds_kv, st,
+                         (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse, D, table,
+                         (T*)dk, (T*)dv, g, nqc, sl2, scale);
+    else
+      hipLaunchKernelGGL((bwd_dkdv_kernel<T, HD, NHWC, false>), dim3(grid), dim3(kThreads), lds_kv, st,
+                         (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse, D, table,
+                         (T*)dk, (T*)dv, g, nqc, sl2, scale);
+  }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_dtab_reduce(g, partial, dtab, nslice, st);
