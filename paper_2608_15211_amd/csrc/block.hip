@@ -27,11 +27,11 @@ typedef __bf16 bf16;
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4s lds_v4s;
 
-constexpr int kGT = 512;          // threads per GEMM workgroup (8 waves: 2 rows x 4 columns of 128 x 64)
-constexpr int kBM = 256;          // workgroup tile rows
-constexpr int kBN = 256;          // workgroup tile columns (128 in the four-wave form)
-constexpr int kBK = 64;           // contraction depth per stage (32 in the four-wave form)
+constexpr int kBM = 256;          // rows and columns of a workgroup tile, eight-wave form
+constexpr int kBS = 128;          // four-wave form
+constexpr int kBK = 64;           // contraction depth per stage
 constexpr int kEpiS = 68;         // row stride (floats) of a wave's epilogue staging tile
+constexpr int kMaxWgradSlices = 64;   // most token slices of a weight gradient
 constexpr int kMaxCusBlock = 256;  // compute units the weight-gradient slices are sized for
 
 // A bf16 operand in memory: row-major, `ld` elements a row, `rows` valid rows.
@@ -108,8 +108,8 @@ __device__ inline float gelu_grad_f(float x) {
 // of each row permuted by an XOR of the row index so that the matrix-core
 // operand reads hit distinct banks:
 // * KROW tile (memory [R][BK], BK / 8 chunks a row): chunk c of row r sits at
-//   chunk c ^ ((r >> 1) & 7) (BK = 32: c ^ ((r >> 2) & 3)) - 16 consecutive
-//   rows read at one logical chunk cover all 64 banks;
+//   chunk c ^ ((r >> 1) & 7) - 16 consecutive rows read at one logical chunk
+//   cover all 64 banks;
 // * COLK tile (memory [BK][R], R / 8 chunks a row): chunk c of row k sits
 //   at chunk c ^ (4 (k & 3)) - each half-wave of a transpose read takes 64
 //   bytes from each of four rows, and these land on four different 64-byte
@@ -117,13 +117,13 @@ __device__ inline float gelu_grad_f(float x) {
 //   with c ^ (2 (k & 3)) 0.8-2 conflict cycles per LDS instruction, though
 //   no slower).
 // ---------------------------------------------------------------------------
-template <int R, bool KROW, int BK, int NT = kGT>
+template <int R, bool KROW, int BK, int NT = 512>
 struct Tile {
   static constexpr int kChunks = R * BK / 8;    // 16-byte chunks
   static constexpr int kPer = kChunks / NT;     // per thread (NT threads)
   static constexpr int kElems = R * BK;
   static constexpr int kCpr = BK / 8;           // chunks a row (KROW)
-  __device__ static int swz(int row) { return BK == 64 ? (row >> 1) & 7 : (row >> 2) & 3; }
+  __device__ static int swz(int row) { return (row >> 1) & 7; }
   // element offset of (row, logical chunk) of the memory layout
   __device__ static int off(int row, int c) {
     if (KROW) return row * BK + 8 * (c ^ swz(row));
@@ -230,19 +230,22 @@ struct Stager {
 // * Each XCD takes one contiguous run of (slice, tile) pairs whatever their
 //   number, so that the tiles of one token slice share an L2 (weight
 //   gradient of 3072 x 768: L2 misses 2.8e7 -> 1.1e7).
-// NW = 4: four waves and a 256 x 128 tile with 32-deep stages (72 KB, two
-// workgroups a CU), for the rows past whole rounds of 256 x 256 tiles.
+// NW = 4: four waves, each a 64 x 64 block of a 128 x 128 tile, for products
+// whose 256 x 256 tiles would leave most CUs idle.  There the time is a
+// workgroup's own chain of stages, so four stages of both operands keep
+// three in flight (0.65 us a stage against 1.35 in the eight-wave form).
 template <bool AKROW, bool BKROW, int EPI, bool SEG = false, int NW = 8>
-__global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, EpiArgs ep, int M, int N, int K,
-                                                                int kslice) {
-  constexpr int NT = NW * 64, BN = NW * 32, BK = NW == 8 ? kBK : 32;
-  typedef Tile<kBM, AKROW, BK, NT> TA;
+__global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(Mat A, Mat B, EpiArgs ep, int M, int N, int K,
+                                                          int kslice) {
+  constexpr int NT = NW * 64, BM = NW == 8 ? kBM : kBS, BN = BM, BK = kBK;
+  constexpr int MI = BM / 64, kWM = 32 * MI;         // 32-row blocks and rows of a wave
+  typedef Tile<BM, AKROW, BK, NT> TA;
   typedef Tile<BN, BKROW, BK, NT> TB;
   extern __shared__ __align__(16) char smem[];
   bf16* lds = reinterpret_cast<bf16*>(smem);
 
   const int nN = (N + BN - 1) / BN;
-  const int nM = (M + kBM - 1) / kBM;
+  const int nM = (M + BM - 1) / BM;
   const int tiles = nM * nN;
   // Workgroups go to the 8 XCDs in turn; each XCD takes one contiguous run
   // of (slice, tile) pairs, so that the tiles sharing operand rows sit
@@ -251,22 +254,22 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, Epi
   const int w0 = xcd * (total >> 3) + min(xcd, total & 7) + (blockIdx.x >> 3);
   const int z = w0 / tiles, w = w0 - z * tiles;
   const int tm = w / nN, tn = w - (w / nN) * nN;
-  const int m0 = tm * kBM, n0 = tn * BN;
+  const int m0 = tm * BM, n0 = tn * BN;
   const int kbeg = z * kslice;
   const int kend = min(K, kbeg + kslice);
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const int wm = (wave / (NW / 2)) * 128, wn = (wave % (NW / 2)) * 64;
+  const int wm = (wave / (NW / 2)) * kWM, wn = (wave % (NW / 2)) * 64;
   const i32x4 rsa = buffer_rsrc(A.p, (uint32_t)(((int64_t)A.rows * A.ld + (SEG ? 2 * A.segstride : 0)) * 2));
   const i32x4 rsb = buffer_rsrc(B.p, (uint32_t)((int64_t)B.rows * B.ld * 2));
 
-  f32x16 acc[4][2];
+  f32x16 acc[MI][2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
 
-  Stager<kBM, AKROW, BK, NT> sa;
+  Stager<BM, AKROW, BK, NT> sa;
   Stager<BN, BKROW, BK, NT> sb;
   int seg = 0;
   if constexpr (SEG && !AKROW) {
@@ -277,8 +280,8 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, Epi
   }
   sb.init(B, n0, N, 0);
   const int kba = AKROW ? 2 : 2 * A.ld, kbb = BKROW ? 2 : 2 * B.ld;   // bytes per contraction index
-  // LDS rings: kRA stages of A, then kRB stages of B
-  constexpr int kRA = 3, kRB = NW == 8 ? 2 : 3;
+  // LDS rings: kRA stages of A, then two (four waves: four) of B
+  constexpr int kRA = NW == 8 ? 3 : 4;
   auto a_tile = [&](int st) { return lds + st * TA::kElems; };
   auto b_tile = [&](int st) { return lds + kRA * TA::kElems + st * TB::kElems; };
   auto issue_a = [&](int s, int st) {
@@ -298,7 +301,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, Epi
   };
 
   const int nk = (kend - kbeg + BK - 1) / BK;
-  bf16x8 ao[2][4], bo[2][2];
+  bf16x8 ao[2][MI], bo[2][2];
   // operands of the 32 contraction indices from 32 * hf of a stage
   auto read_ops = [&](const bf16* ta, const bf16* tb, int hf) {
 #pragma unroll
@@ -308,16 +311,16 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, Epi
       for (int j = 0; j < 2; ++j)
         bo[c][j] = BKROW ? row_operand<BN, BK>(tb, k0, wn + 32 * j, lane) : tr_operand<BN, BK>(tb, k0, wn + 32 * j, lane);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < MI; ++i)
         ao[c][i] =
-            AKROW ? row_operand<kBM, BK>(ta, k0, wm + 32 * i, lane) : tr_operand<kBM, BK>(ta, k0, wm + 32 * i, lane);
+            AKROW ? row_operand<BM, BK>(ta, k0, wm + 32 * i, lane) : tr_operand<BM, BK>(ta, k0, wm + 32 * i, lane);
     }
   };
   auto mfmas = [&]() {
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) mma16(acc[i][j], ao[c][i], bo[c][j]);
   };
@@ -376,21 +379,23 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, Epi
     if (!second) lds_barrier();
   } else {
     constexpr int kLoads = TA::kPer + TB::kPer;
-    for (int s = 0; s < 2; ++s)
+    for (int s = 0; s < 3; ++s)
       if (s < nk) { issue_a(s, s); issue_b(s, s); }
-    int st = 0;
     for (int kt = 0; kt < nk; ++kt) {
-      if (kt + 1 < nk) wait_vm<kLoads>();
+      const int left = nk - 1 - kt;      // stages after this one
+      if (left >= 2) wait_vm<2 * kLoads>();
+      else if (left == 1) wait_vm<kLoads>();
       else wait_vm<0>();
-      lds_barrier();     // stage kt is in LDS; stage kt + 1 may still be loading
-      if (kt + 2 < nk) {
-        const int nx = st == 0 ? 2 : st - 1;
-        issue_a(kt + 2, nx);
-        issue_b(kt + 2, nx);
+      lds_barrier();     // stage kt is in LDS, and every wave is done with the one before
+      if (left >= 3) {
+        issue_a(kt + 3, (kt + 3) & 3);
+        issue_b(kt + 3, (kt + 3) & 3);
       }
-      read_ops(a_tile(st), b_tile(st), 0);
-      mfmas();
-      st = st == 2 ? 0 : st + 1;
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        read_ops(a_tile(kt & 3), b_tile(kt & 3), hf);
+        mfmas();
+      }
     }
   }
   __syncthreads();   // every wave is done with the stages: their LDS now stages the epilogue
@@ -452,12 +457,12 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, Epi
     RowIn in[2];
     if (kAux || kLn) fetch(0, in[0]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < MI; ++i) {
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) et[(8 * (r / 4) + 4 * h + (r % 4)) * kEpiS + 32 * j + col] = acc[i][j][r];
-      if ((kAux || kLn) && i < 3) fetch(i + 1, in[(i + 1) & 1]);
+      if ((kAux || kLn) && i < MI - 1) fetch(i + 1, in[(i + 1) & 1]);
       __builtin_amdgcn_wave_barrier();
       const RowIn& ri = in[i & 1];
 #pragma unroll
@@ -506,7 +511,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, Epi
       __builtin_amdgcn_wave_barrier();
     }
   };
-  if (m0 + kBM <= M && n0 + BN <= N) epilogue(std::true_type{});
+  if (m0 + BM <= M && n0 + BN <= N) epilogue(std::true_type{});
   else epilogue(std::false_type{});
   if constexpr (kCol) {
     // lanes 8t + c (t = 0..7) hold 16-row sums of columns 8c..8c+7: through
@@ -518,7 +523,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void gemm_kernel(Mat A, Mat B, Epi
       float sum = 0.0f;
 #pragma unroll
       for (int r = 0; r < 8; ++r) sum += et[r * kEpiS + lane];
-      if (n0 + wn + lane < N) ep.colpart[(int64_t)(2 * tm + wm / 128) * N + n0 + wn + lane] = sum;
+      if (n0 + wn + lane < N) ep.colpart[(int64_t)(2 * tm + wm / kWM) * N + n0 + wn + lane] = sum;
     }
   }
 }
@@ -635,7 +640,6 @@ __global__ __launch_bounds__(kRowThreads) void ln_stats_kernel(const bf16* __res
 // (dbeta) over the wave's tokens go to `part` ([wave][2][C]) for a
 // fixed-order reduction.  Each lane owns channel chunks 8 (lane + 64 c).
 // ---------------------------------------------------------------------------
-constexpr int kLnMaxChunks = 4;   // C <= 4 * 512 = 2048
 
 // NCH = ceil(C / 512) chunk slots a lane (registers for C, not for 2048)
 template <typename DY, int NCH>
@@ -832,19 +836,85 @@ __global__ __launch_bounds__(256) void transpose_kernel(const bf16* __restrict__
 // ---------------------------------------------------------------------------
 // Host side.
 // ---------------------------------------------------------------------------
-template <bool AKROW, bool BKROW, int EPI, bool SEG = false, int NW = 8>
-static hipError_t gemm(const Mat& A, const Mat& B, const EpiArgs& ep, int M, int N, int K, int nsplit,
-                       hipStream_t st) {
-  constexpr int BN = NW * 32, BK = NW == 8 ? kBK : 32;
-  // three stages of A, two (four waves: three) of B: 160 KB (72 KB)
-  constexpr size_t lds = (3 * (size_t)kBM + (NW == 8 ? 2 : 3) * (size_t)BN) * BK * sizeof(bf16);
-  const int tiles = ((M + kBM - 1) / kBM) * ((N + BN - 1) / BN);
-  const int kslice = ((K + nsplit - 1) / nsplit + BK - 1) / BK * BK;
+template <bool AKROW, bool BKROW, int EPI, bool SEG, int NW>
+static hipError_t gemm_form(const Mat& A, const Mat& B, const EpiArgs& ep, int M, int N, int K, int nsplit,
+                            hipStream_t st) {
+  constexpr int BM = NW == 8 ? kBM : kBS;
+  // stages of A and B: 3 + 2 of 32 KB (160 KB), or 4 + 4 of 16 KB (128 KB)
+  constexpr size_t lds = (NW == 8 ? 5 : 8) * (size_t)BM * kBK * sizeof(bf16);
+  const int tiles = ((M + BM - 1) / BM) * ((N + BM - 1) / BM);
+  const int kslice = ((K + nsplit - 1) / nsplit + kBK - 1) / kBK * kBK;
   hipLaunchKernelGGL((gemm_kernel<AKROW, BKROW, EPI, SEG, NW>), dim3(tiles * nsplit), dim3(NW * 64), lds, st, A, B,
                      ep, M, N, K, kslice);
   return hipGetLastError();
 }
 
+// Which form a product takes, and in how many contraction slices (float32
+// partials, summed in slice order).  Times in us from the kernels' own: a
+// stage takes 1.35 in the eight-wave form and 0.65 in the four-wave one, a
+// workgroup 8 and 3 besides (prologue, epilogue), a sum of slices 5 and its
+// traffic; workgroups run in rounds of one per CU.
+struct Plan {
+  int nw, ns;
+};
+static double plan_cost(int M, int N, int K, Plan p) {
+  const int bm = p.nw == 8 ? kBM : kBS;
+  const int tiles = ((M + bm - 1) / bm) * ((N + bm - 1) / bm);
+  const int rounds = (tiles * p.ns + kMaxCusBlock - 1) / kMaxCusBlock;
+  const int stages = ((K + p.ns - 1) / p.ns + kBK - 1) / kBK;
+  const double sum = p.ns > 1 ? 5.0 + 2e-6 * p.ns * M * N : 0.0;
+  return rounds * (p.nw == 8 ? 1.35 * stages + 8.0 : 0.65 * stages + 3.0) + sum;
+}
+static Plan plan_product(int M, int N, int K, int max_split) {
+  Plan best = {8, 1};
+  double c = plan_cost(M, N, K, best);
+  for (int ns = 1; ns <= max_split && (ns == 1 || K >= 4 * kBK * ns); ++ns) {
+    const double d = plan_cost(M, N, K, {4, ns});
+    if (d < c) { c = d; best = {4, ns}; }
+  }
+  return best;
+}
+
+template <bool AKROW, bool BKROW, int EPI, bool SEG = false>
+static hipError_t gemm(const Mat& A, const Mat& B, const EpiArgs& ep, int M, int N, int K, hipStream_t st) {
+  if (plan_product(M, N, K, 1).nw == 8) return gemm_form<AKROW, BKROW, EPI, SEG, 8>(A, B, ep, M, N, K, 1, st);
+  return gemm_form<AKROW, BKROW, EPI, SEG, 4>(A, B, ep, M, N, K, 1, st);
+}
+
+// out = bf16(sum over slices of part [+ bias + res]), the end of a product
+// in contraction slices; a thread takes 8 columns of one row.
+template <int EPI>
+__global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict__ part, EpiArgs ep, int64_t mn, int N,
+                                                       int ns) {
+  const int64_t o = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+  if (o >= mn) return;
+  float v[8] = {};
+  for (int s = 0; s < ns; ++s) {
+    const float4 lo = *reinterpret_cast<const float4*>(part + s * mn + o);
+    const float4 hi = *reinterpret_cast<const float4*>(part + s * mn + o + 4);
+    v[0] += lo.x; v[1] += lo.y; v[2] += lo.z; v[3] += lo.w;
+    v[4] += hi.x; v[5] += hi.y; v[6] += hi.z; v[7] += hi.w;
+  }
+  bf16x8 t;
+  if (EPI == EPI_BIAS_RES) {
+    const float* b = ep.bias + o % N;
+    const bf16x8 res = *reinterpret_cast<const bf16x8*>(ep.aux + o);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) t[x] = (bf16)(v[x] + b[x] + (float)res[x]);
+  } else {
+#pragma unroll
+    for (int x = 0; x < 8; ++x) t[x] = (bf16)v[x];
+  }
+  *reinterpret_cast<bf16x8*>(ep.out[0] + o) = t;
+}
+
+// Most slices of a product over K = 3C or 4C with few tiles, and the
+// float32 partials they need.
+constexpr int kMaxSplit = 8;
+static size_t split_floats(int T, int C, int K) {
+  const Plan p = plan_product(T, C, K, kMaxSplit);
+  return p.ns > 1 ? (size_t)p.ns * T * C : 0;
+}
 
 static Mat mat(const void* p, int ld, int rows) {
   Mat m;
@@ -856,21 +926,31 @@ static Mat mat(const void* p, int ld, int rows) {
   return m;
 }
 
-// A product whose 256 x 256 tiles do not fill whole rounds of one
-// workgroup per CU (N = C: 3 column tiles by ceil(T / 256) row tiles, 6.3
-// rounds on the 128x1080 grid): the rows of the whole rounds go to the
-// eight-wave form, the rest to the four-wave form, whose 256 x 128 tiles
-// spread the last partial round over twice as many workgroups.  A is
-// K-major and the epilogue writes (and, for the residual, reads) rows of
-// N, offset by the first part's rows.
+// A long product with N = C (K-major A; bf16 or bias + residual epilogue):
+// * few tiles: in contraction slices, finished by split_sum_kernel;
+// * many: the rows of whole rounds of one 256 x 256 tile per CU, then the
+//   rest (3 column tiles by ceil(T / 256) row tiles are 6.3 rounds on the
+//   128x1080 grid at C = 768) as a product of its own.
 template <bool BKROW, int EPI, bool SEG = false>
-static hipError_t gemm_rounds(const Mat& A, const Mat& B, const EpiArgs& ep, int M, int N, int K, hipStream_t st) {
+static hipError_t gemm_rounds(const Mat& A, const Mat& B, const EpiArgs& ep, int M, int N, int K, float* part,
+                              hipStream_t st) {
   static_assert(EPI == EPI_BF16 || EPI == EPI_BIAS_RES, "row offsets are set for these epilogues");
-  const int ntn = (N + kBN - 1) / kBN, nM = (M + kBM - 1) / kBM;
-  int r1 = ((nM * ntn) / kMaxCusBlock) * kMaxCusBlock / ntn;   // row tiles in whole rounds
-  if (r1 == 0 || r1 >= nM) return gemm<true, BKROW, EPI, SEG>(A, B, ep, M, N, K, 1, st);
+  const Plan p = plan_product(M, N, K, kMaxSplit);
+  if (p.ns > 1) {
+    EpiArgs pe = {};
+    pe.outf = part;
+    const hipError_t e = gemm_form<true, BKROW, EPI_F32, SEG, 4>(A, B, pe, M, N, K, p.ns, st);
+    if (e != hipSuccess) return e;
+    const int64_t mn = (int64_t)M * N;
+    hipLaunchKernelGGL((split_sum_kernel<EPI>), dim3((unsigned)((mn / 8 + 255) / 256)), dim3(256), 0, st, part, ep, mn,
+                       N, p.ns);
+    return hipGetLastError();
+  }
+  const int ntn = (N + kBM - 1) / kBM, nM = (M + kBM - 1) / kBM;
+  const int r1 = ((nM * ntn) / kMaxCusBlock) * kMaxCusBlock / ntn;   // row tiles in whole rounds
+  if (r1 == 0 || r1 >= nM) return gemm<true, BKROW, EPI, SEG>(A, B, ep, M, N, K, st);
   const int m1 = r1 * kBM;
-  hipError_t e = gemm<true, BKROW, EPI, SEG>(A, B, ep, m1, N, K, 1, st);
+  const hipError_t e = gemm_form<true, BKROW, EPI, SEG, 8>(A, B, ep, m1, N, K, 1, st);
   if (e != hipSuccess) return e;
   Mat a2 = A;
   a2.p = A.p + (int64_t)m1 * A.ld;
@@ -878,7 +958,7 @@ static hipError_t gemm_rounds(const Mat& A, const Mat& B, const EpiArgs& ep, int
   EpiArgs e2 = ep;
   e2.out[0] = ep.out[0] + (int64_t)m1 * N;
   if (EPI == EPI_BIAS_RES) e2.aux = ep.aux + (int64_t)m1 * N;
-  return gemm<true, BKROW, EPI, SEG, 4>(a2, B, e2, M - m1, N, K, 1, st);
+  return gemm<true, BKROW, EPI, SEG>(a2, B, e2, M - m1, N, K, st);
 }
 
 
@@ -904,7 +984,7 @@ static size_t al(size_t x) { return (x + 255) / 256 * 256; }
 // Forward workspace: the folded QKV and fc1 weights and their per-output
 // sums and constants.
 struct FwdWs {
-  size_t wq, wf, sq, cq, sf, cf, total;
+  size_t wq, wf, sq, cq, sf, cf, part, total;
 };
 static FwdWs fwd_ws(const Geo& g) {
   const size_t C = g.C;
@@ -916,6 +996,7 @@ static FwdWs fwd_ws(const Geo& g) {
   w.cq = off; off += al(3 * C * 4);
   w.sf = off; off += al(4 * C * 4);
   w.cf = off; off += al(4 * C * 4);
+  w.part = off; off += al(split_floats(g.B * g.H * g.W, g.C, 4 * g.C) * 4);
   w.total = off;
   return w;
 }
@@ -949,44 +1030,51 @@ hipError_t launch_block_fwd(const Geo& g, const void* x, const BlockParams& p, c
   TERRA_TRY(ln_fold(p.w_qkv, p.ln1_g, p.ln1_b, p.b_qkv, wq, sq, cq, 3 * C, C, st));
   ep.out[0] = (bf16*)s.q; ep.out[1] = (bf16*)s.k; ep.out[2] = (bf16*)s.v; ep.split = C;
   ep.mean = s.mu1; ep.rstd = s.rstd1; ep.lns = sq; ep.lnc = cq;
-  TERRA_TRY((gemm<true, true, EPI_LN_QKV, false, 8>(mat(x, C, T), mat(wq, C, 3 * C), ep,
-                                                                    T, 3 * C, C, 1, st)));
+  TERRA_TRY((gemm<true, true, EPI_LN_QKV>(mat(x, C, T), mat(wq, C, 3 * C), ep, T, 3 * C, C, st)));
   // windowed attention with the route fused in
   TERRA_TRY(launch_attn_fwd(g, 1, true, s.q, s.k, s.v, table, s.o, nullptr, s.lse, st));
   // x1 = x + o W_p^T + b_p
   ep = EpiArgs{};
   ep.out[0] = (bf16*)s.x1; ep.split = C; ep.aux = (const bf16*)x; ep.bias = p.b_proj;
-  TERRA_TRY((gemm<true, true, EPI_BIAS_RES, false, 8>(mat(s.o, C, T), mat(p.w_proj, C, C), ep, T, C, C, 1, st)));
+  TERRA_TRY((gemm<true, true, EPI_BIAS_RES>(mat(s.o, C, T), mat(p.w_proj, C, C), ep, T, C, C, st)));
   // h = LN2(x1) W_1^T + b_1 (LN2 folded), a = GELU(h)
   TERRA_TRY(ln_stats(s.x1, s.mu2, s.rstd2, T, C, st));
   TERRA_TRY(ln_fold(p.w_fc1, p.ln2_g, p.ln2_b, p.b_fc1, wf, sf, cf, 4 * C, C, st));
   ep = EpiArgs{};
   ep.out[0] = (bf16*)s.h; ep.split = 4 * C; ep.out2 = (bf16*)s.a;
   ep.mean = s.mu2; ep.rstd = s.rstd2; ep.lns = sf; ep.lnc = cf;
-  TERRA_TRY((gemm<true, true, EPI_LN_GELU>(mat(s.x1, C, T), mat(wf, C, 4 * C), ep, T, 4 * C, C, 1, st)));
+  TERRA_TRY((gemm<true, true, EPI_LN_GELU>(mat(s.x1, C, T), mat(wf, C, 4 * C), ep, T, 4 * C, C, st)));
   // x2 = x1 + a W_2^T + b_2
   ep = EpiArgs{};
   ep.out[0] = (bf16*)x2; ep.split = C; ep.aux = (const bf16*)s.x1; ep.bias = p.b_fc2;
-  TERRA_TRY((gemm_rounds<true, EPI_BIAS_RES>(mat(s.a, 4 * C, T), mat(p.w_fc2, 4 * C, C), ep, T, C, 4 * C, st)));
+  TERRA_TRY((gemm_rounds<true, EPI_BIAS_RES>(mat(s.a, 4 * C, T), mat(p.w_fc2, 4 * C, C), ep, T, C, 4 * C,
+                                              reinterpret_cast<float*>(ws + w.part), st)));
 #undef TERRA_TRY
   return hipSuccess;
 }
 
-// Token slices of a weight gradient dW[Nl][Kl] over T tokens.
-static int wgrad_slices(int T, int Nl, int Kl, int cap) {
-  const int tiles = ((Nl + kBM - 1) / kBM) * ((Kl + kBN - 1) / kBN);
-  // two whole rounds of one workgroup per CU (a third, nearly empty round
-  // would leave most CUs idle for a whole slice)
+// Form and token slices of a weight gradient dW[Nl][Kl] over T tokens.  The
+// eight-wave form takes as many slices as fill two whole rounds of one
+// workgroup per CU (a third, nearly empty round would leave most CUs idle
+// for a whole slice), each of at least four stages.
+static Plan wgrad_plan(int T, int Nl, int Kl) {
+  const int tiles = ((Nl + kBM - 1) / kBM) * ((Kl + kBM - 1) / kBM);
   int n = (2 * kMaxCusBlock) / tiles;
-  const int per = (T + n - 1) / n;
-  if (per < 4 * kBK) n = (T + 4 * kBK - 1) / (4 * kBK);  // at least four stages a slice
-  return n < 1 ? 1 : (n > cap ? cap : n);
+  if ((T + n - 1) / n < 4 * kBK) n = (T + 4 * kBK - 1) / (4 * kBK);
+  n = std::max(1, std::min(n, kMaxWgradSlices));
+  Plan best = {8, n};
+  double c = plan_cost(Nl, Kl, T, best);
+  for (int ns = 1; ns <= kMaxSplit && (ns == 1 || T >= 4 * kBK * ns); ++ns) {
+    const double d = plan_cost(Nl, Kl, T, {4, ns});
+    if (d < c) { c = d; best = {4, ns}; }
+  }
+  return best;
 }
 
 // Backward workspace layout (bytes, 256-aligned pieces).
 struct BwdWs {
   size_t dh, dln, dx1, dO, dq, dk, dv, ln, wt, attn, wpart, cpart, lpart, total;
-  int wsplit, cslices, lnwaves, rows_per_wave, cpart_rows, lgroups;
+  int cslices, lnwaves, rows_per_wave, cpart_rows, lgroups;
 };
 
 // A pure function of the geometry: the attention part is sized for kMaxCus
@@ -996,7 +1084,6 @@ static BwdWs block_ws(const Geo& geo) {
   g.cus = kMaxCus;
   BwdWs w;
   const size_t T = (size_t)g.B * g.H * g.W, C = g.C;
-  w.wsplit = 64;                         // most contraction (token) slices of a weight gradient
   w.cslices = 512;                       // row slices of the bias-gradient column sums
   w.cpart_rows = (int)((T + w.cslices - 1) / w.cslices);
   w.lnwaves = 4096;                      // waves of the LayerNorm backward
@@ -1017,11 +1104,12 @@ static BwdWs block_ws(const Geo& geo) {
   for (int i = 0; i < 4; ++i) {
     const int nl = i == 0 ? (int)C : (i == 1 ? 4 * (int)C : (i == 2 ? 3 * (int)C : (int)C));
     const int kl = i == 0 ? 4 * (int)C : (int)C;
-    wmax = std::max(wmax, (size_t)wgrad_slices((int)T, nl, kl, w.wsplit) * nl * kl);
+    wmax = std::max(wmax, (size_t)wgrad_plan((int)T, nl, kl).ns * nl * kl);
   }
+  wmax = std::max({wmax, split_floats((int)T, (int)C, 4 * (int)C), split_floats((int)T, (int)C, 3 * (int)C)});
   w.wpart = off; off += al(wmax * 4);
-  // column-sum partials: the colsum slices, or the dh product's 2 ceil(T/256) rows
-  w.cpart = off; off += al((size_t)std::max((size_t)w.cslices, 2 * ((T + kBM - 1) / kBM)) * 4 * C * 4);
+  // column-sum partials: the colsum slices, or the dh product's 2 rows a row tile
+  w.cpart = off; off += al((size_t)std::max((size_t)w.cslices, 2 * ((T + kBS - 1) / kBS)) * 4 * C * 4);
   w.lpart = off; off += al((size_t)w.lnwaves * 2 * C * 4 + (size_t)w.lgroups * 2 * C * 4);
   w.total = off;
   return w;
@@ -1068,34 +1156,23 @@ static hipError_t colsum(const Mat& X, int ncols, float* part, float* out, const
 // in token slices, reduced in slice order.  LNB: Z = LN(z) applied while
 // staging.
 
+template <bool SEG>
 static hipError_t wgrad(const Mat& dY, const Mat& Z, int T, int Nl, int Kl, float* dW, char* ws, const BwdWs& w,
                         hipStream_t st) {
   EpiArgs ep = {};
   float* part = reinterpret_cast<float*>(ws + w.wpart);
-  ep.outf = part;
-  const int ns = wgrad_slices(T, Nl, Kl, w.wsplit);
-  hipError_t e = gemm<false, false, EPI_F32>(dY, Z, ep, Nl, Kl, T, ns, st);
-  if (e != hipSuccess) return e;
-  return slice_sum(part, dW, (int64_t)Nl * Kl, ns, st);
+  const Plan p = wgrad_plan(T, Nl, Kl);
+  ep.outf = p.ns > 1 ? part : dW;
+  const hipError_t e = p.nw == 8 ? gemm_form<false, false, EPI_F32, SEG, 8>(dY, Z, ep, Nl, Kl, T, p.ns, st)
+                                 : gemm_form<false, false, EPI_F32, SEG, 4>(dY, Z, ep, Nl, Kl, T, p.ns, st);
+  if (e != hipSuccess || p.ns == 1) return e;
+  return slice_sum(part, dW, (int64_t)Nl * Kl, p.ns, st);
 }
 
 // The three-part operand's buffer resource covers 2 segstride + T C
 // elements; its byte offsets must stay below 2^31.
 static bool seg_fits(int T, int C, int64_t segstride) {
   return (2 * segstride + (int64_t)T * C) * 2 < ((int64_t)1 << 31);
-}
-
-// dWqkv[3C][C] = [dQ dK dV]^T Z over all tokens in one product (dy3: the
-// three-part T x 3C operand), in token slices reduced in slice order.
-static hipError_t wgrad3(const Mat& dy3, const Mat& Z, int T, int C, float* dW, char* ws, const BwdWs& w,
-                         hipStream_t st) {
-  EpiArgs ep = {};
-  float* part = reinterpret_cast<float*>(ws + w.wpart);
-  ep.outf = part;
-  const int ns = wgrad_slices(T, 3 * C, C, w.wsplit);
-  hipError_t e = gemm<false, false, EPI_F32, true>(dy3, Z, ep, 3 * C, C, T, ns, st);
-  if (e != hipSuccess) return e;
-  return slice_sum(part, dW, (int64_t)3 * C * C, ns, st);
 }
 
 // dz = LayerNorm backward of dy (float32 or bf16) + dres, and the per-wave
@@ -1166,29 +1243,33 @@ hipError_t launch_block_bwd(const Geo& g, const void* dx2, const void* x, const 
   TERRA_TRY(transpose(p.w_proj, wt_proj, C, C, st));
   TERRA_TRY(transpose(p.w_qkv, wt_qkv, 3 * C, C, st));
   // x2 = x1 + a W2^T + b2:  dW2 = dx2^T a, db2 = colsum(dx2), dh = (dx2 W2) * GELU'(h)
-  TERRA_TRY(wgrad(mat(dx2, C, T), mat(s.a, 4 * C, T), T, C, 4 * C, gr.w_fc2, ws, w, st));
+  TERRA_TRY(wgrad<false>(mat(dx2, C, T), mat(s.a, 4 * C, T), T, C, 4 * C, gr.w_fc2, ws, w, st));
   TERRA_TRY(colsum(mat(dx2, C, T), C, cpart, gr.b_fc2, w, st));
   // db1 = colsum(dh) from the same epilogue: per-wave partial rows, then a
   // fixed-order sum of the 2 ceil(T / 256) partials
   ep.out[0] = dh; ep.split = 4 * C; ep.aux = (const bf16*)s.h; ep.colpart = cpart;
-  TERRA_TRY((gemm<true, true, EPI_GELU_GRAD, false, 8>(mat(dx2, C, T), mat(wt_fc2, C, 4 * C), ep, T, 4 * C, C, 1, st)));
-  TERRA_TRY(slice_sum(cpart, gr.b_fc1, 4 * C, 2 * ((T + kBM - 1) / kBM), st));
+  TERRA_TRY((gemm<true, true, EPI_GELU_GRAD>(mat(dx2, C, T), mat(wt_fc2, C, 4 * C), ep, T, 4 * C, C, st)));
+  {
+    const int bm = plan_product(T, 4 * C, C, 1).nw == 8 ? kBM : kBS;      // the dh product's row tiles
+    TERRA_TRY(slice_sum(cpart, gr.b_fc1, 4 * C, 2 * ((T + bm - 1) / bm), st));
+  }
   // h = LN2(x1) W1^T + b1:  dW1 = dh^T LN2(x1), db1 = colsum(dh), dln2 = dh W1
   TERRA_TRY(ln_apply(s.x1, s.mu2, s.rstd2, p.ln2_g, p.ln2_b, lnb, T, C, st));
-  TERRA_TRY(wgrad(mat(dh, 4 * C, T), mat(lnb, C, T), T, 4 * C, C, gr.w_fc1, ws, w, st));
+  TERRA_TRY(wgrad<false>(mat(dh, 4 * C, T), mat(lnb, C, T), T, 4 * C, C, gr.w_fc1, ws, w, st));
   // dln2 in bf16, like the other gradients the products hand on
   ep = EpiArgs{};
   ep.out[0] = dlnb; ep.split = C;
-  TERRA_TRY((gemm_rounds<true, EPI_BF16>(mat(dh, 4 * C, T), mat(wt_fc1, 4 * C, C), ep, T, C, 4 * C, st)));
+  TERRA_TRY((gemm_rounds<true, EPI_BF16>(mat(dh, 4 * C, T), mat(wt_fc1, 4 * C, C), ep, T, C, 4 * C,
+                                          reinterpret_cast<float*>(ws + w.wpart), st)));
   // dx1 = dx2 + LN2 backward
   TERRA_TRY(ln_bwd(dlnb, s.x1, s.mu2, s.rstd2, p.ln2_g, dx2, dx1, lpart, T, C, w, st));
   TERRA_TRY(ln_param_grads(lpart, gr.ln2_g, gr.ln2_b, C, w, st));
   // x1 = x + o Wp^T + bp:  dWp = dx1^T o, dbp = colsum(dx1), dO = dx1 Wp
-  TERRA_TRY(wgrad(mat(dx1, C, T), mat(s.o, C, T), T, C, C, gr.w_proj, ws, w, st));
+  TERRA_TRY(wgrad<false>(mat(dx1, C, T), mat(s.o, C, T), T, C, C, gr.w_proj, ws, w, st));
   TERRA_TRY(colsum(mat(dx1, C, T), C, cpart, gr.b_proj, w, st));
   ep = EpiArgs{};
   ep.out[0] = dO; ep.split = C;
-  TERRA_TRY((gemm<true, true, EPI_BF16, false, 8>(mat(dx1, C, T), mat(wt_proj, C, C), ep, T, C, C, 1, st)));
+  TERRA_TRY((gemm<true, true, EPI_BF16>(mat(dx1, C, T), mat(wt_proj, C, C), ep, T, C, C, st)));
   // attention backward (route fused in)
   TERRA_TRY(launch_attn_bwd(g, 1, true, s.q, s.k, s.v, s.o, nullptr, dO, s.lse, table, dqkv[0], dqkv[1],
                             dqkv[2], dtable, ws + w.attn, st));
@@ -1202,28 +1283,30 @@ hipError_t launch_block_bwd(const Geo& g, const void* dx2, const void* x, const 
   Mat dy3 = mat(dqkv[0], C, T);
   dy3.segw = C;
   dy3.segstride = (int64_t)(w.dk - w.dq) / 2;
-  const bool seg_w = C % kBM == 0 && seg_fits(T, C, dy3.segstride);
+  const bool seg_w = (C % kBM == 0 || (wgrad_plan(T, 3 * C, C).nw == 4 && C % kBS == 0)) &&
+                     seg_fits(T, C, dy3.segstride);
   const bool seg_d = C % kBK == 0 && seg_fits(T, C, dy3.segstride);
   if (seg_w) {
-    TERRA_TRY(wgrad3(dy3, mat(lnb, C, T), T, C, gr.w_qkv, ws, w, st));
+    TERRA_TRY(wgrad<true>(dy3, mat(lnb, C, T), T, 3 * C, C, gr.w_qkv, ws, w, st));
   }
   if (!seg_w) {
     for (int i = 0; i < 3; ++i)
-      TERRA_TRY(wgrad(mat(dqkv[i], C, T), mat(lnb, C, T), T, C, C, gr.w_qkv + (size_t)i * C * C, ws, w, st));
+      TERRA_TRY(wgrad<false>(mat(dqkv[i], C, T), mat(lnb, C, T), T, C, C, gr.w_qkv + (size_t)i * C * C, ws, w, st));
   }
   TERRA_TRY(colsum(dy3, 3 * C, cpart, gr.b_qkv, w, st));
   ep = EpiArgs{};
   if (seg_d) {
     ep.out[0] = dlnb; ep.split = C;
-    TERRA_TRY((gemm_rounds<true, EPI_BF16, true>(dy3, mat(wt_qkv, 3 * C, C), ep, T, C, 3 * C, st)));
+    TERRA_TRY((gemm_rounds<true, EPI_BF16, true>(dy3, mat(wt_qkv, 3 * C, C), ep, T, C, 3 * C,
+                                                reinterpret_cast<float*>(ws + w.wpart), st)));
   } else {
     ep.outf = dln;
     for (int i = 0; i < 3; ++i) {
       const bf16* wi = reinterpret_cast<const bf16*>(p.w_qkv) + (size_t)i * C * C;
       if (i == 0) {
-        TERRA_TRY((gemm<true, false, EPI_F32>(mat(dqkv[i], C, T), mat(wi, C, C), ep, T, C, C, 1, st)));
+        TERRA_TRY((gemm<true, false, EPI_F32>(mat(dqkv[i], C, T), mat(wi, C, C), ep, T, C, C, st)));
       } else {
-        TERRA_TRY((gemm<true, false, EPI_F32_ACC>(mat(dqkv[i], C, T), mat(wi, C, C), ep, T, C, C, 1, st)));
+        TERRA_TRY((gemm<true, false, EPI_F32_ACC>(mat(dqkv[i], C, T), mat(wi, C, C), ep, T, C, C, st)));
       }
     }
   }

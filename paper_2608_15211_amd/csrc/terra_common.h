@@ -293,7 +293,8 @@ __device__ inline typename Operand<T>::type pack8(const f32x16& acc, int r0) {
 // LDS write, so a wave waits for the load count (wait_vm) and the
 // workgroup then synchronises before any wave reads those bytes.
 //
-// Written as assembly (no result registers, M0 set inside): the compiler
+// Written as assembly (no result registers; M0 is set inside, and nothing
+// else in these kernels uses it): the compiler
 // tracks its built-in form as a pending LDS write and makes every LDS
 // transpose read after it wait for all loads in flight, which serialised the
 // loads and the products (weight gradient 3072 x 768 x 138240: 600 us, with
@@ -305,7 +306,7 @@ __device__ __forceinline__ void buffer_load_lds16(const i32x4& rsrc, const void*
   const uint32_t dst = (uint32_t)(uintptr_t)lds;     // the low half of a generic LDS address is the LDS offset
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                ::"s"(dst), "v"(voffset), "s"(rsrc)
-               : "memory", "m0");
+               : "memory");
 }
 
 // Buffer descriptor of a whole operand: base, size in bytes (below 2^31, so
