@@ -416,7 +416,7 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(Mat A, Mat B, EpiArgs 
   // per-column epilogue constants (LayerNorm fold: s and c; bias)
   constexpr bool kLn = EPI == EPI_LN_QKV || EPI == EPI_LN_GELU;
   constexpr int kPc = kLn ? 2 : (EPI == EPI_BIAS_RES ? 1 : 0);
-  float pc[kPc > 0 ? kPc : 1][8];
+  float pc[2][8];
 #pragma unroll
   for (int a = 0; a < kPc; ++a) {
     const float* src = kLn ? (a == 0 ? ep.lns : ep.lnc) : ep.bias;
@@ -531,11 +531,10 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(Mat A, Mat B, EpiArgs 
 // LayerNorm applied to a token matrix (the backward's weight gradients take
 // the normalised activations as an operand): out = (z - mean) rstd gamma +
 // beta, rounded to bf16; one thread per 8 channels.
-__global__ __launch_bounds__(256) void ln_apply_kernel(const bf16* __restrict__ z, const float* __restrict__ mean,
-                                                      const float* __restrict__ rstd, const float* __restrict__ gamma,
-                                                      const float* __restrict__ beta, bf16* __restrict__ out, int T,
-                                                      int C) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__device__ inline void ln_apply_rows(int block, const bf16* __restrict__ z, const float* __restrict__ mean,
+                                     const float* __restrict__ rstd, const float* __restrict__ gamma,
+                                     const float* __restrict__ beta, bf16* __restrict__ out, int T, int C) {
+  const int64_t idx = (int64_t)block * 256 + threadIdx.x;
   const int c8 = C / 8;
   if (idx >= (int64_t)T * c8) return;
   const int t = (int)(idx / c8);
@@ -547,6 +546,12 @@ __global__ __launch_bounds__(256) void ln_apply_kernel(const bf16* __restrict__ 
   for (int x = 0; x < 8; ++x) o[x] = (bf16)(((float)v[x] - mu) * rs * gamma[c + x] + beta[c + x]);
   *reinterpret_cast<bf16x8*>(out + (int64_t)t * C + c) = o;
 }
+__global__ __launch_bounds__(256) void ln_apply_kernel(const bf16* __restrict__ z, const float* __restrict__ mean,
+                                                      const float* __restrict__ rstd, const float* __restrict__ gamma,
+                                                      const float* __restrict__ beta, bf16* __restrict__ out, int T,
+                                                      int C) {
+  ln_apply_rows(blockIdx.x, z, mean, rstd, gamma, beta, out, T, C);
+}
 
 // LayerNorm folded into the following linear layer: with
 // LN(x)_k = (x_k - mean) rstd gamma_k + beta_k,
@@ -555,11 +560,11 @@ __global__ __launch_bounds__(256) void ln_apply_kernel(const bf16* __restrict__ 
 //   c_n = b_n + sum_k W[n][k] beta_k,
 // so the GEMM runs on the raw activations and the epilogue normalises.  One
 // wave per output row n.
-__global__ __launch_bounds__(256) void ln_fold_kernel(const bf16* __restrict__ W, const float* __restrict__ gamma,
-                                                     const float* __restrict__ beta, const float* __restrict__ bias,
-                                                     bf16* __restrict__ Wf, float* __restrict__ lns,
-                                                     float* __restrict__ lnc, int N, int K) {
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
+__device__ inline void ln_fold(int block, const bf16* __restrict__ W, const float* __restrict__ gamma,
+                               const float* __restrict__ beta, const float* __restrict__ bias,
+                               bf16* __restrict__ Wf, float* __restrict__ lns,
+                               float* __restrict__ lnc, int N, int K) {
+  const int n = block * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (n >= N) return;
   float sacc = 0.0f, cacc = 0.0f;
@@ -600,9 +605,9 @@ __device__ inline float wave_sum(float x) {
 // Mean and 1/std of each row, one wave a row: the row is read once into
 // registers (C <= 2048: four 8-element chunks a lane) and the variance is
 // taken about the mean from there.
-__global__ __launch_bounds__(kRowThreads) void ln_stats_kernel(const bf16* __restrict__ x, float* __restrict__ mean,
-                                                               float* __restrict__ rstd, int T, int C, float eps) {
-  const int row = blockIdx.x * (kRowThreads / 64) + (threadIdx.x >> 6);
+__device__ inline void ln_stats_rows(int block, const bf16* __restrict__ x, float* __restrict__ mean,
+                                     float* __restrict__ rstd, int T, int C, float eps) {
+  const int row = block * (kRowThreads / 64) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= T) return;
   const bf16* p = x + (int64_t)row * C;
@@ -631,6 +636,30 @@ __global__ __launch_bounds__(kRowThreads) void ln_stats_kernel(const bf16* __res
     mean[row] = mu;
     rstd[row] = 1.0f / sqrtf(var + eps);
   }
+}
+
+__global__ __launch_bounds__(kRowThreads) void ln_stats_kernel(const bf16* __restrict__ x, float* __restrict__ mean,
+                                                               float* __restrict__ rstd, int T, int C, float eps) {
+  ln_stats_rows(blockIdx.x, x, mean, rstd, T, C, eps);
+}
+
+// One launch for what the forward needs before its products: the statistics
+// of x (blocks [0, b0)) and the two folded weights (W_qkv in [b0, b1), W_fc1
+// from b1).  Three launches of about 5 us each on small grids before.
+struct FoldArgs {
+  const bf16* W;
+  const float *gamma, *beta, *bias;
+  bf16* Wf;
+  float *lns, *lnc;
+  int N;
+};
+__global__ __launch_bounds__(kRowThreads) void block_prep_kernel(const bf16* __restrict__ x, float* __restrict__ mean,
+                                                                 float* __restrict__ rstd, int T, int C, float eps,
+                                                                 FoldArgs f0, FoldArgs f1, int b0, int b1) {
+  const int b = blockIdx.x;
+  if (b < b0) return ln_stats_rows(b, x, mean, rstd, T, C, eps);
+  const FoldArgs& f = b < b1 ? f0 : f1;
+  ln_fold(b - (b < b1 ? b0 : b1), f.W, f.gamma, f.beta, f.bias, f.Wf, f.lns, f.lnc, f.N, C);
 }
 
 // ---------------------------------------------------------------------------
@@ -756,6 +785,39 @@ __global__ __launch_bounds__(kRowThreads) void colsum_kernel(Mat X, int ncols, f
     part[(int64_t)s * ncols + 8 * c8 + i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
 }
 
+// The same in one launch, for up to kColDirect rows (a second launch costs
+// more than the few workgroups' longer walk): a workgroup takes 64 columns
+// (ncols is a multiple of 64, a part's width too), thread (r, c) the rows
+// r, r + 32, ... of columns 8c .. 8c + 7; the 32 sums are added in order.
+constexpr int kColDirect = 2048;
+__global__ __launch_bounds__(256) void colsum_direct_kernel(Mat X, float* __restrict__ out) {
+  __shared__ float red[32][65];
+  const int c = threadIdx.x & 7, r0 = threadIdx.x >> 3;
+  const bf16* xb = X.p;
+  int col = 64 * blockIdx.x + 8 * c;
+  if (X.segw > 0) {
+    const int sg = col / X.segw;
+    xb += sg * X.segstride;
+    col -= sg * X.segw;
+  }
+  float acc[8] = {};
+#pragma unroll 4
+  for (int r = r0; r < X.rows; r += 32) {
+    const bf16x8 v = *reinterpret_cast<const bf16x8*>(xb + (int64_t)r * X.ld + col);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] += (float)v[i];
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) red[r0][8 * c + i] = acc[i];
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    float sum = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 32; ++r) sum += red[r][threadIdx.x];
+    out[64 * blockIdx.x + threadIdx.x] = sum;
+  }
+}
+
 // grp[g][i] = sum of part[s][i] over s in [g * per, (g + 1) * per), in
 // order (n entries per slice).
 __global__ __launch_bounds__(kRowThreads) void group_sum_kernel(const float* __restrict__ part, float* __restrict__ grp,
@@ -791,8 +853,10 @@ __global__ __launch_bounds__(kRowThreads) void slice_sum_kernel(const float* __r
 // slices): a workgroup takes 64 consecutive i; its four waves sum the slices
 // s = 4j + wave in order, and the four sums are added in wave order (a fixed
 // order for every i), so that the slice list is four short dependent chains.
+// Outputs from n0 on go to out1 (the LayerNorm shift beside the gain).
 __global__ __launch_bounds__(256) void slice_sum4_kernel(const float* __restrict__ part, float* __restrict__ out,
-                                                        int64_t n, int64_t stride, int nslice) {
+                                                        float* __restrict__ out1, int64_t n0, int64_t n,
+                                                        int64_t stride, int nslice) {
   __shared__ float red[4][64];
   const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int64_t i = (int64_t)blockIdx.x * 64 + c;
@@ -810,17 +874,18 @@ __global__ __launch_bounds__(256) void slice_sum4_kernel(const float* __restrict
   }
   red[q][c] = acc;
   __syncthreads();
-  if (q == 0 && i < n) out[i] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
+  if (q == 0 && i < n) (i < n0 ? out[i] : out1[i - n0]) = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
 }
 
 // out[c][r] = in[r][c] for a rows x cols bf16 matrix: the backward's copies
 // of the weights in [N][K] order, so that its data-gradient products read
 // their B operand with straight rather than transposed LDS reads (a few MB,
 // once per backward).
-__global__ __launch_bounds__(256) void transpose_kernel(const bf16* __restrict__ in, bf16* __restrict__ out,
-                                                        int rows, int cols) {
+__device__ inline void transpose_tile(int block, const bf16* __restrict__ in, bf16* __restrict__ out, int rows,
+                                      int cols) {
   __shared__ bf16 t[32][33];
-  const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
+  const int nc = (cols + 31) / 32;
+  const int c0 = (block % nc) * 32, r0 = (block / nc) * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   for (int y = ty; y < 32; y += 8) {
     const int r = r0 + y, c = c0 + tx;
@@ -831,6 +896,29 @@ __global__ __launch_bounds__(256) void transpose_kernel(const bf16* __restrict__
     const int c = c0 + y, r = r0 + tx;
     if (c < cols && r < rows) out[(int64_t)c * rows + r] = t[tx][y];
   }
+}
+
+
+// One launch for what the backward needs before its products: the four
+// weight copies (blocks below b[3]) and LN2's output (from b[3]).  Five
+// launches of about 5 us each on small grids before.
+struct BwdPrep {
+  const bf16* in[4];
+  bf16* out[4];
+  int rows[4], cols[4];
+  int b[4];                // first block after each matrix
+};
+__global__ __launch_bounds__(256) void block_bwd_prep_kernel(BwdPrep w, const bf16* __restrict__ z,
+                                                            const float* __restrict__ mean,
+                                                            const float* __restrict__ rstd,
+                                                            const float* __restrict__ gamma,
+                                                            const float* __restrict__ beta, bf16* __restrict__ out,
+                                                            int T, int C) {
+  const int blk = blockIdx.x;
+  if (blk >= w.b[3]) return ln_apply_rows(blk - w.b[3], z, mean, rstd, gamma, beta, out, T, C);
+  int i = 0;
+  while (blk >= w.b[i]) ++i;
+  transpose_tile(blk - (i > 0 ? w.b[i - 1] : 0), w.in[i], w.out[i], w.rows[i], w.cols[i]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1002,13 +1090,6 @@ static FwdWs fwd_ws(const Geo& g) {
 }
 size_t block_fwd_workspace(const Geo& g) { return fwd_ws(g).total; }
 
-static hipError_t ln_fold(const void* W, const float* gamma, const float* beta, const float* bias, bf16* Wf,
-                          float* lns, float* lnc, int N, int K, hipStream_t st) {
-  hipLaunchKernelGGL(ln_fold_kernel, dim3((N + 3) / 4), dim3(256), 0, st, (const bf16*)W, gamma, beta, bias, Wf, lns,
-                     lnc, N, K);
-  return hipGetLastError();
-}
-
 hipError_t launch_block_fwd(const Geo& g, const void* x, const BlockParams& p, const float* table, void* x2,
                             const BlockSaved& s, void* wsv, hipStream_t st) {
   const int T = g.B * g.H * g.W, C = g.C;
@@ -1024,10 +1105,17 @@ hipError_t launch_block_fwd(const Geo& g, const void* x, const BlockParams& p, c
   do {                                  \
     if ((e = (x)) != hipSuccess) return e; \
   } while (0)
-  // LN1 statistics; qkv = LN1(x) W_qkv^T + b_qkv with LN1 folded into the
-  // weights and the epilogue, written as Q, K, V (NHWC)
-  TERRA_TRY(ln_stats(x, s.mu1, s.rstd1, T, C, st));
-  TERRA_TRY(ln_fold(p.w_qkv, p.ln1_g, p.ln1_b, p.b_qkv, wq, sq, cq, 3 * C, C, st));
+  // LN1 statistics and both folded weights; qkv = LN1(x) W_qkv^T + b_qkv with
+  // LN1 folded into the weights and the epilogue, written as Q, K, V (NHWC)
+  {
+    const int per = kRowThreads / 64;
+    const int b0 = (T + per - 1) / per, b1 = b0 + (3 * C + 3) / 4;
+    const FoldArgs f0 = {(const bf16*)p.w_qkv, p.ln1_g, p.ln1_b, p.b_qkv, wq, sq, cq, 3 * C};
+    const FoldArgs f1 = {(const bf16*)p.w_fc1, p.ln2_g, p.ln2_b, p.b_fc1, wf, sf, cf, 4 * C};
+    hipLaunchKernelGGL(block_prep_kernel, dim3(b1 + C), dim3(kRowThreads), 0, st, (const bf16*)x, s.mu1, s.rstd1, T,
+                       C, kLnEps, f0, f1, b0, b1);
+    TERRA_TRY(hipGetLastError());
+  }
   ep.out[0] = (bf16*)s.q; ep.out[1] = (bf16*)s.k; ep.out[2] = (bf16*)s.v; ep.split = C;
   ep.mean = s.mu1; ep.rstd = s.rstd1; ep.lns = sq; ep.lnc = cq;
   TERRA_TRY((gemm<true, true, EPI_LN_QKV>(mat(x, C, T), mat(wq, C, 3 * C), ep, T, 3 * C, C, st)));
@@ -1039,7 +1127,6 @@ hipError_t launch_block_fwd(const Geo& g, const void* x, const BlockParams& p, c
   TERRA_TRY((gemm<true, true, EPI_BIAS_RES>(mat(s.o, C, T), mat(p.w_proj, C, C), ep, T, C, C, st)));
   // h = LN2(x1) W_1^T + b_1 (LN2 folded), a = GELU(h)
   TERRA_TRY(ln_stats(s.x1, s.mu2, s.rstd2, T, C, st));
-  TERRA_TRY(ln_fold(p.w_fc1, p.ln2_g, p.ln2_b, p.b_fc1, wf, sf, cf, 4 * C, C, st));
   ep = EpiArgs{};
   ep.out[0] = (bf16*)s.h; ep.split = 4 * C; ep.out2 = (bf16*)s.a;
   ep.mean = s.mu2; ep.rstd = s.rstd2; ep.lns = sf; ep.lnc = cf;
@@ -1086,9 +1173,12 @@ static BwdWs block_ws(const Geo& geo) {
   const size_t T = (size_t)g.B * g.H * g.W, C = g.C;
   w.cslices = 512;                       // row slices of the bias-gradient column sums
   w.cpart_rows = (int)((T + w.cslices - 1) / w.cslices);
-  w.lnwaves = 4096;                      // waves of the LayerNorm backward
+  // waves of the LayerNorm backward: 4096, on small grids one per four rows
+  // (with 4096 on 960 tokens the partials, 25 MB of zeros, were most of its
+  // 19 us); above 256 of them, first-level groups of 32 for their sums
+  w.lnwaves = T >= 16384 ? 4096 : (int)std::max<size_t>(64, (T / 4 + 31) / 32 * 32);
   w.rows_per_wave = (int)((T + w.lnwaves - 1) / w.lnwaves);
-  w.lgroups = 128;                       // first-level groups of the LayerNorm partials (32 waves each)
+  w.lgroups = w.lnwaves > 256 ? w.lnwaves / 32 : 0;
   size_t off = 0;
   w.dh = off; off += al(T * 4 * C * 2);
   w.dln = off; off += al(T * C * 4);
@@ -1110,41 +1200,50 @@ static BwdWs block_ws(const Geo& geo) {
   w.wpart = off; off += al(wmax * 4);
   // column-sum partials: the colsum slices, or the dh product's 2 rows a row tile
   w.cpart = off; off += al((size_t)std::max((size_t)w.cslices, 2 * ((T + kBS - 1) / kBS)) * 4 * C * 4);
-  w.lpart = off; off += al((size_t)w.lnwaves * 2 * C * 4 + (size_t)w.lgroups * 2 * C * 4);
+  w.lpart = off; off += al((size_t)(w.lnwaves + w.lgroups) * 2 * C * 4);
   w.total = off;
   return w;
 }
 
 size_t block_bwd_workspace(const Geo& g) { return block_ws(g).total; }
 
-static hipError_t slice_sum(const float* part, float* out, int64_t n, int nslice, hipStream_t st,
-                            int64_t stride = -1) {
+static hipError_t slice_sum(const float* part, float* out, int64_t n, int nslice, hipStream_t st) {
   if (nslice >= 64) {
-    hipLaunchKernelGGL(slice_sum4_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, part, out, n,
-                       stride < 0 ? n : stride, nslice);
+    hipLaunchKernelGGL(slice_sum4_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, part, out, out, n, n, n,
+                       nslice);
   } else {
     hipLaunchKernelGGL(slice_sum_kernel, dim3((unsigned)((n + kRowThreads - 1) / kRowThreads)), dim3(kRowThreads), 0,
-                       st, part, out, n, stride < 0 ? n : stride, nslice);
+                       st, part, out, n, n, nslice);
   }
   return hipGetLastError();
 }
 
 // LayerNorm parameter gradients from the per-wave partials
-// [wave][dgamma C | dbeta C]: sums over groups of consecutive waves, then
-// over the groups, each in order.
+// [wave][dgamma C | dbeta C]: with many waves first sums over groups of 32
+// consecutive ones, then one sum over the groups (or the waves), in order.
 static hipError_t ln_param_grads(const float* lpart, float* dgamma, float* dbeta, int C, const BwdWs& w,
                                  hipStream_t st) {
-  float* grp = const_cast<float*>(lpart) + (size_t)w.lnwaves * 2 * C;
-  const int per = w.lnwaves / w.lgroups;
-  hipLaunchKernelGGL(group_sum_kernel, dim3((2 * C + kRowThreads - 1) / kRowThreads, w.lgroups), dim3(kRowThreads),
-                     0, st, lpart, grp, 2 * C, per);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if ((e = slice_sum(grp, dgamma, C, w.lgroups, st, 2 * C)) != hipSuccess) return e;
-  return slice_sum(grp + C, dbeta, C, w.lgroups, st, 2 * C);
+  const float* src = lpart;
+  int n = w.lnwaves;
+  if (w.lgroups > 0) {
+    float* grp = const_cast<float*>(lpart) + (size_t)w.lnwaves * 2 * C;
+    hipLaunchKernelGGL(group_sum_kernel, dim3((2 * C + kRowThreads - 1) / kRowThreads, w.lgroups), dim3(kRowThreads),
+                       0, st, lpart, grp, 2 * C, w.lnwaves / w.lgroups);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    src = grp;
+    n = w.lgroups;
+  }
+  hipLaunchKernelGGL(slice_sum4_kernel, dim3((2 * C + 63) / 64), dim3(256), 0, st, src, dgamma, dbeta, (int64_t)C,
+                     (int64_t)2 * C, (int64_t)2 * C, n);
+  return hipGetLastError();
 }
 
 static hipError_t colsum(const Mat& X, int ncols, float* part, float* out, const BwdWs& w, hipStream_t st) {
+  if (X.rows <= kColDirect) {
+    hipLaunchKernelGGL(colsum_direct_kernel, dim3(ncols / 64), dim3(256), 0, st, X, out);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(colsum_kernel, dim3((ncols / 8 + kRowThreads - 1) / kRowThreads, w.cslices), dim3(kRowThreads),
                      0, st, X, ncols, part, w.cpart_rows);
   hipError_t e = hipGetLastError();
@@ -1197,12 +1296,6 @@ static hipError_t ln_bwd(const DY* dy, const void* z, const float* mean, const f
   return hipGetLastError();
 }
 
-static hipError_t transpose(const void* in, bf16* out, int rows, int cols, hipStream_t st) {
-  hipLaunchKernelGGL(transpose_kernel, dim3((cols + 31) / 32, (rows + 31) / 32), dim3(256), 0, st, (const bf16*)in,
-                     out, rows, cols);
-  return hipGetLastError();
-}
-
 static hipError_t ln_apply(const void* z, const float* mu, const float* rs, const float* gamma, const float* beta,
                            bf16* out, int T, int C, hipStream_t st) {
   const int64_t n = (int64_t)T * (C / 8);
@@ -1238,10 +1331,19 @@ hipError_t launch_block_bwd(const Geo& g, const void* dx2, const void* x, const 
   bf16* wt_fc1 = wt_fc2 + (size_t)4 * C * C;                // [C][4C]
   bf16* wt_proj = wt_fc1 + (size_t)4 * C * C;               // [C][C]
   bf16* wt_qkv = wt_proj + (size_t)C * C;                   // [C][3C]
-  TERRA_TRY(transpose(p.w_fc2, wt_fc2, C, 4 * C, st));
-  TERRA_TRY(transpose(p.w_fc1, wt_fc1, 4 * C, C, st));
-  TERRA_TRY(transpose(p.w_proj, wt_proj, C, C, st));
-  TERRA_TRY(transpose(p.w_qkv, wt_qkv, 3 * C, C, st));
+  {
+    BwdPrep pr = {{(const bf16*)p.w_fc2, (const bf16*)p.w_fc1, (const bf16*)p.w_proj, (const bf16*)p.w_qkv},
+                  {wt_fc2, wt_fc1, wt_proj, wt_qkv},
+                  {C, 4 * C, C, 3 * C},
+                  {4 * C, C, C, C},
+                  {}};
+    const int tl = C / 32;                                  // C is a multiple of 128
+    pr.b[0] = 4 * tl * tl; pr.b[1] = 8 * tl * tl; pr.b[2] = 9 * tl * tl; pr.b[3] = 12 * tl * tl;
+    const int64_t nln = ((int64_t)T * (C / 8) + 255) / 256;
+    hipLaunchKernelGGL(block_bwd_prep_kernel, dim3((unsigned)(pr.b[3] + nln)), dim3(256), 0, st, pr,
+                       (const bf16*)s.x1, s.mu2, s.rstd2, p.ln2_g, p.ln2_b, lnb, T, C);
+    TERRA_TRY(hipGetLastError());
+  }
   // x2 = x1 + a W2^T + b2:  dW2 = dx2^T a, db2 = colsum(dx2), dh = (dx2 W2) * GELU'(h)
   TERRA_TRY(wgrad<false>(mat(dx2, C, T), mat(s.a, 4 * C, T), T, C, 4 * C, gr.w_fc2, ws, w, st));
   TERRA_TRY(colsum(mat(dx2, C, T), C, cpart, gr.b_fc2, w, st));
@@ -1254,7 +1356,6 @@ hipError_t launch_block_bwd(const Geo& g, const void* dx2, const void* x, const 
     TERRA_TRY(slice_sum(cpart, gr.b_fc1, 4 * C, 2 * ((T + bm - 1) / bm), st));
   }
   // h = LN2(x1) W1^T + b1:  dW1 = dh^T LN2(x1), db1 = colsum(dh), dln2 = dh W1
-  TERRA_TRY(ln_apply(s.x1, s.mu2, s.rstd2, p.ln2_g, p.ln2_b, lnb, T, C, st));
   TERRA_TRY(wgrad<false>(mat(dh, 4 * C, T), mat(lnb, C, T), T, 4 * C, C, gr.w_fc1, ws, w, st));
   // dln2 in bf16, like the other gradients the products hand on
   ep = EpiArgs{};
