@@ -240,6 +240,24 @@ __device__ inline f32x16 bias_init_nb(const int* kinfo, const int* knb, const ch
   return c;
 }
 
+// The same with the labels in an array of their own.
+template <bool QUAD, bool MASK>
+__device__ inline f32x16 bias_init_lab(const int* klabs, const int* knb, const char* tabq, int kb,
+                                       int half, int qlab) {
+  f32x16 c;
+#pragma unroll
+  for (int g4 = 0; g4 < 4; ++g4) {
+    const int kk = 32 * kb + 8 * g4 + 4 * half;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int kx = QUAD ? kk : kk + x;
+      c[4 * g4 + x] = reinterpret_cast<const float*>(tabq + knb[kx])[QUAD ? x : 0];
+      if (MASK && klabs[kx] != qlab) c[4 * g4 + x] = -INFINITY;
+    }
+  }
+  return c;
+}
+
 // The key-major form (lane = key, registers = queries of query block QB):
 // qnb[t] = 4 x (offset of query t), tabk the lane's row of the forward-order
 // table in bytes.
@@ -1155,6 +1173,188 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(
 }
 
 // ---------------------------------------------------------------------------
+// Forward for the 16-bit types (windows the window-resident kernel does not
+// take): fwd_kernel's arithmetic, with the staging of bwd_dkdv16_kernel: row
+// addresses, bias offsets and labels once per workgroup, K and V through two
+// direct-to-LDS buffers, one barrier a tile, O (and O_lo) out in whole row
+// pieces, a copy of the walk for masked and unmasked windows.  FWDMEAS
+// ---------------------------------------------------------------------------
+template <typename T, int HD, bool NHWC, bool QUAD, bool SPLIT, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
+    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+    const float* __restrict__ table, T* __restrict__ o, T* __restrict__ olo,
+    float* __restrict__ lse, Geo g, int nqc, float scale_log2) {
+  constexpr int NT = NW * 64;
+  constexpr int kTB = 64 * HD * 2;                    // bytes of one tile
+  const int nP = (g.wh * g.ww + 63) & ~63;
+  extern __shared__ __align__(16) char smem[];
+  char* tiles = smem;                                 // {K, V} x 2 buffers
+  uint32_t* tokb = reinterpret_cast<uint32_t*>(smem + 4 * kTB);   // [nP] byte offsets
+  int* knb = reinterpret_cast<int*>(tokb + nP);       // [nP] 4 x bias offset
+  int* klabs = knb + nP;                              // [nP] label
+  float* tab = reinterpret_cast<float*>(klabs + nP);  // [nbins+4], reversed
+
+  int bid = xcd_item(blockIdx.x, gridDim.x);
+  if (bid >= g.B * g.nwin * g.heads * nqc) return;
+  const int qc = bid % nqc; bid /= nqc;
+  const int h = bid % g.heads; bid /= g.heads;
+  const int w = bid % g.nwin;
+  const int b = bid / g.nwin;
+  const int i = w / g.Mw, j = w - (w / g.Mw) * g.Mw;
+  const int cols = win_cols(g, j);
+  const int n = win_rows(g, i) * cols;
+  const int q0 = qc * NW * 32;
+  if (q0 >= n) return;
+  const WinTokens<NHWC> wt(g, b, i, j);
+  const int nr = (n + 63) & ~63;
+  for (int t = threadIdx.x; t < nr; t += NT) {
+    const int inf = token_info(g, i, j, cols, t, n);
+    tokb[t] = (wt.tok(g, min(t, n - 1)) - wt.img0) * (uint32_t)(g.C * 2) + (uint32_t)(h * HD * 2);
+    knb[t] = 4 * (inf & 0xFFFFFF);
+    klabs[t] = inf >> 24;
+  }
+  const float bscale = sqrtf((float)HD);
+  for (int x = threadIdx.x; x < g.nbins + 4; x += NT)
+    tab[x] = x < g.nbins ? table[(g.nbins - 1 - x) * g.heads + h] * bscale : -INFINITY;
+  const bool mask = window_has_labels(g, i, j) || (n % 64) != 0;
+
+  const int64_t img = (int64_t)wt.img0 * g.C;
+  const uint32_t ibytes = (uint32_t)g.HW * (uint32_t)(g.C * 2);
+  const i32x4 rk = buffer_rsrc(k + img, ibytes), rv = buffer_rsrc(v + img, ibytes);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int half = lane >> 5, col = lane & 31;
+  const int qi = q0 + wave * 32 + col;
+  const bool qvalid = qi < n;
+  const bool wactive = q0 + wave * 32 < n;            // else staging and barriers only
+  const int qinf = token_info(g, i, j, cols, qvalid ? qi : 0, n);
+  const int qlab = qinf >> 24;
+  const char* tabq = reinterpret_cast<const char*>(
+      tab + (g.nbins - 1 - ((qinf & 0xFFFFFF) + (g.wh - 1) * g.bstride + (g.ww - 1))));
+
+  lds_barrier();                                      // the row table
+  tile_load_direct<HD, NT>(rk, tiles, tokb, 0);
+  tile_load_direct<HD, NT>(rv, tiles + kTB, tokb, 0);
+  typename Operand<T>::type qop[HD / 16];
+  const uint32_t qtok = wt.tok(g, min(qi, n - 1)) * g.C + h * HD;
+#pragma unroll
+  for (int c = 0; c < HD / 16; ++c)
+    qop[c] = qvalid ? load_op_global<T>(q + qtok + 16 * c + 8 * half) : zero_op<T>();
+  constexpr float kPOff = __is_same(T, _Float16) ? 7.0f : 0.0f;
+
+  auto walk = [&](auto masked) {
+    constexpr bool kMask = decltype(masked)::value;
+    TileAddr<HD> ta(lane);
+    f32x16 oacc[HD / 32];
+#pragma unroll
+    for (int eb = 0; eb < HD / 32; ++eb) oacc[eb] = f32x16{};
+    float m_run = -1e30f, l_run = 0.0f;               // running max (log2 units) and sum
+    int buf = 0;
+    for (int t0 = 0; t0 < n; t0 += 64, buf ^= 1) {
+      wait_vm<0>();
+      lds_barrier();        // tile t0 is in LDS; every wave is done with the other buffer
+      if (t0 + 64 < n) {
+        tile_load_direct<HD, NT>(rk, tiles + (buf ^ 1) * 2 * kTB, tokb, t0 + 64);
+        tile_load_direct<HD, NT>(rv, tiles + (buf ^ 1) * 2 * kTB + kTB, tokb, t0 + 64);
+      }
+      if (!wactive) continue;
+      const char* kt = tiles + buf * 2 * kTB;
+      const char* vt = kt + kTB;
+      if constexpr (HD == 128) ta.opaque();
+      f32x16 s[2];
+      float mloc = -INFINITY;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        s[kb] = bias_init_lab<QUAD, kMask>(klabs + t0, knb + t0, tabq, kb, half, qlab);
+#pragma unroll
+        for (int c = 0; c < HD / 16; ++c) mma16(s[kb], tile_row_op<T, HD>(kt, ta, 32 * kb, c), qop[c]);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, s[kb][r]);
+      }
+      mloc = halves_max(mloc);
+      // the running maximum moves only past a margin of 2^8 (see fwd_kernel)
+      const float mt = mloc * scale_log2;
+      if (__builtin_amdgcn_ballot_w64(mt > m_run + (kPOff + 8.0f)) != 0) {
+        const float mnew = fmaxf(m_run, mt - kPOff);
+        const float alpha = exp2f(m_run - mnew);
+        m_run = mnew;
+        l_run *= alpha;
+#pragma unroll
+        for (int eb = 0; eb < HD / 32; ++eb) oacc[eb] *= alpha;
+      }
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float p = __builtin_amdgcn_exp2f(s[kb][r] * scale_log2 - m_run);
+          s[kb][r] = p;
+          l_run += p;
+        }
+      }
+      typename Operand<T>::type phi[2][2], plo[2][2];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          phi[kb][c] = pack8<T>(s[kb], 8 * c);
+          if constexpr (SPLIT) {
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+              plo[kb][c][x] = from_float<T>(s[kb][8 * c + x] - to_float<T>(phi[kb][c][x]));
+          }
+        }
+#pragma unroll
+      for (int eb = 0; eb < HD / 32; ++eb)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const auto vop = tile_tr_op<T, HD>(vt, ta, kb, c, eb);
+            mma16(oacc[eb], vop, phi[kb][c]);
+            if constexpr (SPLIT) mma16(oacc[eb], vop, plo[kb][c]);
+          }
+    }
+    lds_barrier();
+    if (!wactive) return;
+    l_run = halves_sum(l_run);
+    const float inv = 1.0f / l_run;
+    const unsigned opq = (unsigned)g.C >> 31;         // 0: C is positive (see fwd_kernel)
+    T* et = reinterpret_cast<T*>(tiles) + wave * 32 * HD;
+#pragma unroll
+    for (int out = 0; out < (SPLIT ? 2 : 1); ++out) {
+#pragma unroll
+      for (int eb = 0; eb < HD / 32; ++eb)
+#pragma unroll
+        for (int grp = 0; grp < 4; ++grp) {
+          typedef T v4 __attribute__((ext_vector_type(4)));
+          v4 p;
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            float val = oacc[eb][4 * grp + x] * inv;
+            if constexpr (SPLIT) val = __uint_as_float(__float_as_uint(val) | opq);
+            const T hi = from_float<T>(val);
+            p[x] = out == 0 ? hi : from_float<T>(val - to_float<T>(hi));
+          }
+          *reinterpret_cast<v4*>(et + tile_off<HD>(col, eb * 32 + 8 * grp + 4 * half)) = p;
+        }
+      __builtin_amdgcn_wave_barrier();
+      T* dst = out == 0 ? o : olo;
+      constexpr int kCpr = HD / 8;
+#pragma unroll
+      for (int u = 0; u < kCpr / 2; ++u) {
+        const int r = (u * 64 + lane) / kCpr, c = (u * 64 + lane) % kCpr;
+        const uint4 x = *reinterpret_cast<const uint4*>(et + tile_off<HD>(r, 8 * c));
+        const int t = q0 + wave * 32 + r;
+        if (t < n) *reinterpret_cast<uint4*>(reinterpret_cast<char*>(dst + img) + tokb[t] + 16 * c) = x;
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    if (qvalid && half == 0) lse[wt.lse_at(g, h, qi)] = (m_run + __log2f(l_run)) * kLn2;
+  };
+  if (mask) walk(std::true_type{});
+  else walk(std::false_type{});
+}
+
+// ---------------------------------------------------------------------------
 // dK and dV for the 16-bit types.  A workgroup of NW waves owns NW x 32 keys
 // of one (window, head) and walks the window's queries in tiles of 64.
 // What bounds it: latency, at two waves per SIMD (registers).  So
@@ -1501,27 +1701,60 @@ int bwd_nslice(const Geo& g, int dt) {
                                                                : bwd_nslice_max_t<_Float16>(g);
 }
 
+// Waves of a 16-bit workgroup whose plan takes `lds` bytes.  Four where two
+// workgroups fit a CU's LDS, else eight (dK/dV, 1024-token windows of 128
+// channels: 2267 us with four, 1381 with eight).  Windows of up to 256 tokens
+// take fewer waves where that leaves fewer of them idle; longer ones keep
+// four (dK/dV, 576 tokens of 64 channels: 1603 us with four and a half-empty
+// last chunk, 1890 with three, 1864 with eight).
+template <int HD>
+static int waves16(const Geo& g, size_t lds) {
+  const int nb = (g.wh * g.ww + 31) / 32;
+  int nw = 2 * lds <= 160 * 1024 ? 4 : 8;
+  if (nb <= 8)
+    for (int c : {4, 3, 2})
+      if (c < nw && (HD == 32 || c != 3) && (nb + c - 1) / c * c < (nb + nw - 1) / nw * nw) nw = c;
+  return nw;
+}
+
 template <typename T, int HD, bool NHWC>
 static hipError_t fwd_impl(const Geo& g, const void* q, const void* k, const void* v,
                            const float* table, void* o, void* olo, float* lse, hipStream_t st) {
-  const int nqc = num_chunks(g);
-  const int grid = grid8(g.B * g.nwin * g.heads * nqc);
   const float sl2 = kLog2e / sqrtf((float)HD);
-  const size_t lds = fwd_lds<T, HD>(g);
-#define TERRA_LAUNCH_FWD(QD, SP)                                                                  \
-  hipLaunchKernelGGL((fwd_kernel<T, HD, NHWC, QD, SP>), dim3(grid), dim3(kThreads), lds, st,       \
-                     (const T*)q, (const T*)k, (const T*)v, table, (T*)o, (T*)olo, lse, g, nqc, sl2)
   const bool quad = quad_layout(g);
   if constexpr (sizeof(T) == 2) {
-    if (olo != nullptr) {
-      if (quad) TERRA_LAUNCH_FWD(true, true);
-      else TERRA_LAUNCH_FWD(false, true);
-      return hipGetLastError();
-    }
-  }
-  if (quad) TERRA_LAUNCH_FWD(true, false);
-  else TERRA_LAUNCH_FWD(false, false);
+    const size_t nP = (g.wh * g.ww + 63) & ~63;
+    const size_t lds = 4 * 64 * HD * 2 + 12 * nP + 4 * (g.nbins + 4);
+    const int nw = waves16<HD>(g, lds);
+    const int nqc = ((g.wh * g.ww + 31) / 32 + nw - 1) / nw;
+    const int grid = grid8(g.B * g.nwin * g.heads * nqc);
+#define TERRA_LAUNCH_FWD(QD, SP, NW_)                                                               \
+  hipLaunchKernelGGL((fwd16_kernel<T, HD, NHWC, QD, SP, NW_>), dim3(grid), dim3(NW_ * 64), lds, st,  \
+                     (const T*)q, (const T*)k, (const T*)v, table, (T*)o, (T*)olo, lse, g, nqc, sl2)
+#define TERRA_LAUNCH_FWDN(NW_)                                \
+  do {                                                        \
+    if (quad && olo != nullptr) TERRA_LAUNCH_FWD(true, true, NW_);   \
+    else if (olo != nullptr) TERRA_LAUNCH_FWD(false, true, NW_);     \
+    else if (quad) TERRA_LAUNCH_FWD(true, false, NW_);               \
+    else TERRA_LAUNCH_FWD(false, false, NW_);                        \
+  } while (0)
+    if (nw == 4) TERRA_LAUNCH_FWDN(4);
+    else if (nw == 2) TERRA_LAUNCH_FWDN(2);
+    else if (nw == 8) TERRA_LAUNCH_FWDN(8);
+    else if constexpr (HD == 32) TERRA_LAUNCH_FWDN(3);
+#undef TERRA_LAUNCH_FWDN
 #undef TERRA_LAUNCH_FWD
+  } else {
+    const int nqc = num_chunks(g);
+    const int grid = grid8(g.B * g.nwin * g.heads * nqc);
+    const size_t lds = fwd_lds<T, HD>(g);
+#define TERRA_LAUNCH_FWD(QD)                                                                      \
+  hipLaunchKernelGGL((fwd_kernel<T, HD, NHWC, QD, false>), dim3(grid), dim3(kThreads), lds, st,    \
+                     (const T*)q, (const T*)k, (const T*)v, table, (T*)o, (T*)olo, lse, g, nqc, sl2)
+    if (quad) TERRA_LAUNCH_FWD(true);
+    else TERRA_LAUNCH_FWD(false);
+#undef TERRA_LAUNCH_FWD
+  }
   return hipGetLastError();
 }
 
@@ -1582,17 +1815,9 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if constexpr (sizeof(T) == 2) {
-    // Four waves where two workgroups fit a CU's LDS, else eight (1024-token
-    // windows of 128 channels: 2267 us with four, 1381 with eight).  Windows
-    // of up to 256 tokens take fewer waves where that leaves fewer of them
-    // idle; longer ones keep four (576 tokens of 64 channels: 1603 us with
-    // four and a half-empty last chunk, 1890 with three, 1864 with eight).
     const int nb = (g.wh * g.ww + 31) / 32;
     const size_t lds_kv = dkdv16_lds<HD>(g);
-    int nw = 2 * lds_kv <= 160 * 1024 ? 4 : 8;
-    if (nb <= 8)
-      for (int c : {4, 3, 2})
-        if (c < nw && (HD == 32 || c != 3) && (nb + c - 1) / c * c < (nb + nw - 1) / nw * nw) nw = c;
+    const int nw = waves16<HD>(g, lds_kv);
     const int nkc = (nb + nw - 1) / nw;
     const int grid = grid8(g.B * g.nwin * g.heads * nkc);
 #define TERRA_LAUNCH_KV(QD, NW_)                                                                    \
