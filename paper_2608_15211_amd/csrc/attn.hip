@@ -26,6 +26,7 @@
 // * The bias-table gradient is summed per workgroup in LDS (one head per
 //   workgroup, many windows per workgroup), written as per-workgroup
 //   partials, and reduced in a fixed order by a second kernel.
+#include <algorithm>
 #include <type_traits>
 
 #include "terra_common.h"
@@ -283,19 +284,18 @@ __device__ inline f32x16 bias_init_t_nb(const int* qinfo, const int* qnb, const 
 // per window, empty chunks of small windows exit at once).  The bias enters
 // the score accumulator before the QK^T product (table times sqrt(hd) in
 // reversed bin order, -inf entries for excluded pairs), so each score costs
-// one multiply-add and one exp2 outside the matrix cores.  With olo (16-bit
-// types, nullable) the PV product also takes P's rounding residual and the
-// epilogue writes O's: the backward's D = <dO, O> then needs no key sweep.
+// one multiply-add and one exp2 outside the matrix cores.  float32 only: the
+// 16-bit types have fwd16_kernel.
 // ---------------------------------------------------------------------------
-template <typename T, int HD, bool NHWC, bool QUAD, bool SPLIT>
+template <typename T, int HD, bool NHWC, bool QUAD>
 __global__ __launch_bounds__(kThreads) void fwd_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-    const float* __restrict__ table, T* __restrict__ o, T* __restrict__ olo,
+    const float* __restrict__ table, T* __restrict__ o,
     float* __restrict__ lse, Geo g, int nqc, float scale_log2) {
   constexpr int kTile = tile_of<T, HD>();
   extern __shared__ __align__(16) char smem[];
   T* kt = reinterpret_cast<T*>(smem);                          // [kTile][HD+kPad]
-  T* vt = kt + kTile * (HD + kPad);                            // V^T, or V rows (16-bit)
+  T* vt = kt + kTile * (HD + kPad);                            // V^T
   int* kinfo = reinterpret_cast<int*>(vt + vtile_size<T, HD>());
   float* tab = reinterpret_cast<float*>(kinfo + kTile);        // [nbins+4], reversed
   uint32_t* tt = reinterpret_cast<uint32_t*>(tab + g.nbins + 4);   // [wh*ww] token offsets
@@ -329,7 +329,6 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(
   const int qlab = qinf >> 24;
   const int qrev = g.nbins - 1 - ((qinf & 0xFFFFFF) + (g.wh - 1) * g.bstride + (g.ww - 1));
   const bool mask = window_has_labels(g, i, j) || (n % kTile) != 0;
-  constexpr bool split = SPLIT && sizeof(T) == 2;
 
   typename Operand<T>::type qop[HD / 16];
 #pragma unroll
@@ -341,7 +340,6 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(
 #pragma unroll
   for (int eb = 0; eb < HD / 32; ++eb) oacc[eb] = f32x16{};
   float m_run = -1e30f, l_run = 0.0f;     // running max (log2 units) and sum
-  constexpr float kPOff = __is_same(T, _Float16) ? 7.0f : 0.0f;
 
   // K, V tiles go HBM -> registers -> LDS, one tile ahead up to head dim 64
   constexpr bool kPrefetch = HD <= 64;
@@ -359,8 +357,7 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(
     }
     lds_barrier();
     tile_store<T, HD, true, false>(rk, kt, nullptr);
-    if (sizeof(T) == 2) tile_store_rows<T, HD, tr16_stride<HD>()>(rv, vt);
-    else tile_store<T, HD, false, true>(rv, nullptr, vt);
+    tile_store<T, HD, false, true>(rv, nullptr, vt);
     if (threadIdx.x < kTile) kinfo[threadIdx.x] = token_info(g, i, j, cols, k0 + threadIdx.x, n);
     lds_barrier();
     if (kPrefetch && k0 + kTile < n) {
@@ -384,15 +381,11 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(
     mloc = halves_max(mloc);
     // The running maximum moves (and O and the sum are rescaled) only when
     // some query of the wave sees a score more than 2^8 above it: between
-    // moves the weights stay below 256, which the fp32 sums and the 16-bit
-    // operands carry as exactly as weights below 1.  For float16 operands
-    // the weights run 2^kPOff higher (m_run sits kPOff below the maximum;
-    // the sum, and so the LSE, follow), so that weights down to 2^-21 of the
-    // maximum, and the low parts of the split, stay above float16's
-    // subnormal range (6.1e-5), which the operands would lose.
+    // moves the weights stay below 256, which the fp32 sums carry as exactly
+    // as weights below 1.
     const float mt = mloc * scale_log2;
-    if (__builtin_amdgcn_ballot_w64(mt > m_run + (kPOff + 8.0f)) != 0) {
-      const float mnew = fmaxf(m_run, mt - kPOff);
+    if (__builtin_amdgcn_ballot_w64(mt > m_run + 8.0f) != 0) {
+      const float mnew = fmaxf(m_run, mt);
       const float alpha = exp2f(m_run - mnew);
       m_run = mnew;
       l_run *= alpha;
@@ -408,44 +401,14 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(
         l_run += p;
       }
     }
-    if constexpr (sizeof(T) == 2) {
-      // 16-bit P operands.  When the caller keeps O_lo, P also enters as
-      // hi + lo (lo = P - hi rounded again), so that the fp32 sum carries
-      // P V to about 16 significant bits rather than the 8 of one rounding.
-      typename Operand<T>::type phi[kTile / 32][2], plo[kTile / 32][2];
 #pragma unroll
-      for (int kb = 0; kb < kTile / 32; ++kb)
+    for (int eb = 0; eb < HD / 32; ++eb) {
+#pragma unroll
+      for (int kb = 0; kb < kTile / 32; ++kb) {
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-          phi[kb][c] = pack8<T>(s[kb], 8 * c);
-          if constexpr (split) {
-#pragma unroll
-            for (int x = 0; x < 8; ++x)
-              plo[kb][c][x] = from_float<T>(s[kb][8 * c + x] - to_float<T>(phi[kb][c][x]));
-          }
-        }
-#pragma unroll
-      for (int eb = 0; eb < HD / 32; ++eb) {
-#pragma unroll
-        for (int kb = 0; kb < kTile / 32; ++kb) {
-#pragma unroll
-          for (int c = 0; c < 2; ++c) {
-            const auto vop = lds_tr_op<T, tr16_stride<HD>()>(vt, kb, c, eb, lane);
-            mma16(oacc[eb], vop, phi[kb][c]);
-            if constexpr (split) mma16(oacc[eb], vop, plo[kb][c]);
-          }
-        }
-      }
-    } else {
-#pragma unroll
-      for (int eb = 0; eb < HD / 32; ++eb) {
-#pragma unroll
-        for (int kb = 0; kb < kTile / 32; ++kb) {
-#pragma unroll
-          for (int c = 0; c < 2; ++c) {
-            const T* row = vt + tr_row<T, HD>(eb * 32 + col) + kb * 32 + 16 * c;
-            mma16(oacc[eb], load_op_lds_perm<T>(row, half), pack8<T>(s[kb], 8 * c));
-          }
+          const T* row = vt + tr_row<T, HD>(eb * 32 + col) + kb * 32 + 16 * c;
+          mma16(oacc[eb], load_op_lds_perm<T>(row, half), pack8<T>(s[kb], 8 * c));
         }
       }
     }
@@ -454,12 +417,6 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(
   if (!qvalid) return;
   const float inv = 1.0f / l_run;
   T* orow = o + wt.tok(g, qi) * g.C + hoff;
-  // O_lo: what rounding O to T left out, itself rounded to T; O + O_lo
-  // carries the fp32 output to about 16 significant bits
-  T* lrow = split ? olo + wt.tok(g, qi) * g.C + hoff : nullptr;
-  const unsigned opq = (unsigned)g.C >> 31;    // 0: C is positive
-  (void)lrow;
-  (void)opq;
 #pragma unroll
   for (int eb = 0; eb < HD / 32; ++eb) {
 #pragma unroll
@@ -467,18 +424,7 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(
       const int e = eb * 32 + 8 * grp + 4 * half;
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
-        float val = oacc[eb][4 * grp + x] * inv;
-        // The split needs one float32 value behind both halves: left to
-        // itself the compiler folds the multiply into a float16
-        // mixed-precision multiply on the O_lo side (one rounding of
-        // acc * inv) while the stored O rounds the float32 product again,
-        // and near a tie the two pick different halves.  OR-ing in a zero
-        // the compiler cannot prove (opq) stops that fold.  (An empty asm
-        // register barrier did too, but slowed the whole kernel by half.)
-        if constexpr (split) val = __uint_as_float(__float_as_uint(val) | opq);
-        const T hi = from_float<T>(val);
-        orow[e + x] = hi;
-        if constexpr (split) lrow[e + x] = from_float<T>(val - to_float<T>(hi));
+        orow[e + x] = from_float<T>(oacc[eb][4 * grp + x] * inv);
       }
     }
   }
@@ -1174,10 +1120,13 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(
 
 // ---------------------------------------------------------------------------
 // Forward for the 16-bit types (windows the window-resident kernel does not
-// take): fwd_kernel's arithmetic, with the staging of bwd_dkdv16_kernel: row
+// take): fwd_kernel's plan with the staging of bwd_dkdv16_kernel: row
 // addresses, bias offsets and labels once per workgroup, K and V through two
 // direct-to-LDS buffers, one barrier a tile, O (and O_lo) out in whole row
-// pieces, a copy of the walk for masked and unmasked windows.  FWDMEAS
+// pieces, a copy of the walk for masked and unmasked windows.  Bound by vector
+// instructions (576 tokens).  Measured (us, before -> now): 144 tokens of 32
+// channels 42 -> 34, 576 of 64 with O_lo 1332 -> 1224, 64 of 128 309 -> 273,
+// 1024 of 128 with O_lo 1260 -> 1100.
 // ---------------------------------------------------------------------------
 template <typename T, int HD, bool NHWC, bool QUAD, bool SPLIT, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
@@ -1271,7 +1220,12 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
         for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, s[kb][r]);
       }
       mloc = halves_max(mloc);
-      // the running maximum moves only past a margin of 2^8 (see fwd_kernel)
+      // The running maximum moves only past a margin of 2^8: weights below
+      // 256 are carried as exactly as weights below 1.  For float16 operands
+      // the weights run 2^kPOff higher (m_run sits kPOff below the maximum;
+      // the sum, and so the LSE, follow), so that weights down to 2^-21 of
+      // the maximum, and the low parts of the split, stay above float16's
+      // subnormal range (6.1e-5), which the operands would lose.
       const float mt = mloc * scale_log2;
       if (__builtin_amdgcn_ballot_w64(mt > m_run + (kPOff + 8.0f)) != 0) {
         const float mnew = fmaxf(m_run, mt - kPOff);
@@ -1290,6 +1244,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
           l_run += p;
         }
       }
+      // With SPLIT, P also enters as hi + lo (lo = P - hi rounded again), so
+      // that the fp32 sum carries P V to about 16 significant bits.
       typename Operand<T>::type phi[2][2], plo[2][2];
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
@@ -1317,7 +1273,12 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
     if (!wactive) return;
     l_run = halves_sum(l_run);
     const float inv = 1.0f / l_run;
-    const unsigned opq = (unsigned)g.C >> 31;         // 0: C is positive (see fwd_kernel)
+    // The split needs one float32 value behind both halves: left to itself
+    // the compiler folds the multiply into a float16 mixed-precision multiply
+    // on the O_lo side (one rounding of acc * inv) while the stored O rounds
+    // the float32 product again, and near a tie the two pick different
+    // halves.  OR-ing in a zero the compiler cannot prove (opq) stops that.
+    const unsigned opq = (unsigned)g.C >> 31;         // 0: C is positive
     T* et = reinterpret_cast<T*>(tiles) + wave * 32 * HD;
 #pragma unroll
     for (int out = 0; out < (SPLIT ? 2 : 1); ++out) {
@@ -1352,6 +1313,396 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
   };
   if (mask) walk(std::true_type{});
   else walk(std::false_type{});
+}
+
+// ---------------------------------------------------------------------------
+// Backward, step 1 for the 16-bit types and windows of more than 256 tokens:
+// bwd_dq_kernel's arithmetic and bins with the staging of bwd_dkdv16_kernel.
+// (Smaller windows keep bwd_dq_kernel: an item is then mostly its own start,
+// which the tables here make longer: 64 tokens 31 -> 35 us, 144 tokens 90 ->
+// 99, 64 tokens of 128 channels 403 -> 459.)
+// NW = 8: where the plan fits a CU once, eight waves share the four bias
+// copies in pairs (w, w + 4) by turns: between barriers A and B of a tile
+// the first half computes and the second half adds the bins of the tile
+// before, between B and the next A they swap.  The order of additions stays
+// fixed, and a SIMD has two waves instead of one: 1024 tokens of 128 channels
+// 2412 -> 1631 us.  NW = 4: 576 tokens of 64 channels 2096 -> 1930 us.
+// ---------------------------------------------------------------------------
+template <typename T, int HD, bool NHWC, bool QUAD, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void bwd_dq16_kernel(
+    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+    const T* __restrict__ o, const T* __restrict__ olo,
+    const T* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ D,
+    const float* __restrict__ table, T* __restrict__ dq, float* __restrict__ partial,
+    Geo g, int nqc, int nslice, float scale_log2, float scale) {
+  constexpr int NT = NW * 64, kCopies = 4;
+  constexpr bool kTurns = NW == 8;
+  constexpr int kTB = 64 * HD * 2;                    // bytes of one tile
+  const int nP = (g.wh * g.ww + 63) & ~63;
+  extern __shared__ __align__(16) char smem[];
+  char* tiles = smem;                                 // {K, V} x 2 buffers
+  uint32_t* tokb = reinterpret_cast<uint32_t*>(smem + 4 * kTB);   // [nP] byte offsets
+  float* tab = reinterpret_cast<float*>(tokb + nP);   // [nbins+4], reversed
+  float* dtab = tab + g.nbins + 4;                    // [kCopies][nbins]
+  uint16_t* knball = reinterpret_cast<uint16_t*>(dtab + kCopies * g.nbins);   // [nP] 4 x bias offset
+  uint8_t* klaball = reinterpret_cast<uint8_t*>(knball + nP);                 // [nP] label
+
+  const int bid = xcd_item(blockIdx.x, gridDim.x);
+  const int h = bid / nslice;
+  const int slice = bid - h * nslice;
+  if (h >= g.heads) return;
+  const float bscale = sqrtf((float)HD);
+  for (int x = threadIdx.x; x < g.nbins + 4; x += NT)
+    tab[x] = x < g.nbins ? table[(g.nbins - 1 - x) * g.heads + h] * bscale : -INFINITY;
+  for (int x = threadIdx.x; x < kCopies * g.nbins; x += NT) dtab[x] = 0.0f;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = lane >> 5, col = lane & 31;
+  const bool second = kTurns && wave >= 4;
+  const int nitems = g.B * g.nwin * nqc;
+  TileAddr<HD> ta(lane);
+  const bool fold = (g.ww % 4 == 0) && (g.W % g.ww) % 4 == 0;   // uniform
+
+  for (int it = slice; it < nitems; it += nslice) {
+    const int qc = it % nqc;
+    const int w = (it / nqc) % g.nwin;
+    const int b = it / (nqc * g.nwin);
+    const int i = w / g.Mw, j = w - (w / g.Mw) * g.Mw;
+    const int cols = win_cols(g, j);
+    const int n = win_rows(g, i) * cols;
+    const int q0 = qc * NW * 32;
+    if (q0 >= n) continue;
+    const WinTokens<NHWC> wt(g, b, i, j);
+    const int nt = (n + 63) >> 6;
+    lds_barrier();                    // the previous item is done with the tables and tiles
+    for (int t = threadIdx.x; t < 64 * nt; t += NT) {
+      const int inf = token_info(g, i, j, cols, t, n);
+      tokb[t] = (wt.tok(g, min(t, n - 1)) - wt.img0) * (uint32_t)(g.C * 2) + (uint32_t)(h * HD * 2);
+      knball[t] = (uint16_t)(4 * (inf & 0xFFFFFF));
+      klaball[t] = (uint8_t)(inf >> 24);
+    }
+    const int64_t img = (int64_t)wt.img0 * g.C;
+    const uint32_t ibytes = (uint32_t)g.HW * (uint32_t)(g.C * 2);
+    const i32x4 rk = buffer_rsrc(k + img, ibytes), rv = buffer_rsrc(v + img, ibytes);
+    auto load = [&](int tix, int buf) {
+      tile_load_direct<HD, NT>(rk, tiles + buf * 2 * kTB, tokb, 64 * tix);
+      tile_load_direct<HD, NT>(rv, tiles + buf * 2 * kTB + kTB, tokb, 64 * tix);
+    };
+    const int qi = q0 + wave * 32 + col;
+    const bool qvalid = qi < n;
+    const bool wactive = q0 + wave * 32 < n;          // else staging and barriers only
+    const int qinf = token_info(g, i, j, cols, qvalid ? qi : 0, n);
+    const int qlab = (qinf >> 24) & 0xFF;
+    const int qoff = (qinf & 0xFFFFFF) + (g.wh - 1) * g.bstride + (g.ww - 1);
+    const char* tabq = reinterpret_cast<const char*>(tab + (g.nbins - 1 - qoff));
+    const uint32_t qtokn = wt.tok(g, min(qi, n - 1));
+    const int64_t lidx = wt.img0 * (uint32_t)g.heads + (uint32_t)(h * g.HW) + (qtokn - wt.img0);
+    // +inf for padding queries: their P is exactly 0
+    const float lse2 = qvalid ? lse[lidx] * kLog2e : INFINITY;
+    const uint32_t qtok = qtokn * g.C + h * HD;
+    typename Operand<T>::type qop[HD / 16], dop[HD / 16];
+#pragma unroll
+    for (int c = 0; c < HD / 16; ++c) {
+      qop[c] = qvalid ? load_op_global<T>(q + qtok + 16 * c + 8 * half) : zero_op<T>();
+      dop[c] = qvalid ? load_op_global<T>(dout + qtok + 16 * c + 8 * half) : zero_op<T>();
+    }
+    lds_barrier();                    // the tables
+    load(0, 0);
+    float dsum = 0.0f;
+    const bool sweep = olo == nullptr;
+    if (!sweep && qvalid) {
+      // D from the forward's output: the two halves of a lane pair hold
+      // alternate 8-element runs of the query's row, like dop
+#pragma unroll
+      for (int c = 0; c < HD / 16; ++c) {
+        const auto ov = load_op_global<T>(o + qtok + 16 * c + 8 * half);
+        const auto lv = load_op_global<T>(olo + qtok + 16 * c + 8 * half);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) dsum += to_float<T>(dop[c][x]) * (to_float<T>(ov[x]) + to_float<T>(lv[x]));
+      }
+    }
+    const int cq = qi - fast_div(qi, cols, win_rcols(g, j)) * cols;
+    // runs: lanes of one 32-lane half holding consecutive queries of one
+    // window row; run = lanes before this one in its run, rest = lanes after
+    const int run = cq < col ? cq : col;
+    const int rest = (cols - 1 - cq) < (31 - col) ? (cols - 1 - cq) : (31 - col);
+    const float fnext = rest > 0 ? 1.0f : 0.0f;          // lane l+1 is in the run
+    const float fsend = fnext;                           // this lane may pass to l+1
+    const float fkeep = run < 3 ? 1.0f : 0.0f;           // one of the run's first three
+
+    auto sweeps = [&](auto masked) {
+      constexpr bool kMask = decltype(masked)::value;
+      auto bias = [&](int t0, int kb) {
+        f32x16 c;
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+          const int kk = t0 + 32 * kb + 8 * g4 + 4 * half;
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            const int kx = QUAD ? kk : kk + x;
+            c[4 * g4 + x] = reinterpret_cast<const float*>(tabq + knball[kx])[QUAD ? x : 0];
+            if (kMask && klaball[kx] != qlab) c[4 * g4 + x] = -INFINITY;
+          }
+        }
+        return c;
+      };
+      int vis = 0;                    // tiles visited by this item; its parity is the buffer
+      const int last = (sweep ? 2 : 1) * nt - 1;
+      // hands over the tile of visit vis and starts the next visit's load
+      auto turn = [&]() {
+        wait_vm<0>();
+        lds_barrier();
+        if (vis < last) load((vis + 1) % nt, (vis + 1) & 1);
+      };
+      if (sweep) {
+        for (int tix = 0; tix < nt; ++tix, ++vis) {
+          turn();
+          if (!wactive) continue;
+          const char* kt = tiles + (vis & 1) * 2 * kTB;
+          const char* vr = kt + kTB;
+          if constexpr (HD == 128) ta.opaque();
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb) {
+            f32x16 s = bias(64 * tix, kb);
+            f32x16 dp = f32x16{};
+#pragma unroll
+            for (int c = 0; c < HD / 16; ++c) {
+              mma16(s, tile_row_op<T, HD>(kt, ta, 32 * kb, c), qop[c]);
+              mma16(dp, tile_row_op<T, HD>(vr, ta, 32 * kb, c), dop[c]);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) dsum += __builtin_amdgcn_exp2f(s[r] * scale_log2 - lse2) * dp[r];
+          }
+        }
+      }
+      const float Dq = halves_sum(dsum);
+      if (qvalid && half == 0) D[lidx] = Dq;
+      // main sweep; kPart 0: all waves alike, 1 and 2: the halves of a
+      // workgroup that take turns (each with its own copy of the code, so
+      // that no accumulator is merged between them)
+      auto main_sweep = [&](auto part) {
+        constexpr int kPart = decltype(part)::value;
+        f32x16 dqacc[HD / 32];
+#pragma unroll
+        for (int eb = 0; eb < HD / 32; ++eb) dqacc[eb] = f32x16{};
+        f32x16 dsb[2];
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) dsb[kb] = f32x16{};
+        auto compute = [&](int tix, int vbuf) {
+          const int t0 = 64 * tix;
+          const char* kt = tiles + vbuf * 2 * kTB;
+          const char* vr = kt + kTB;
+          if constexpr (HD == 128) ta.opaque();
+          // Head dim 64: the S and dP products of both key blocks first, so
+          // that one block's exp runs while the other's are on the matrix cores
+          constexpr int kG = HD == 64 ? 2 : 1;
+#pragma unroll
+          for (int k2 = 0; k2 < 2; k2 += kG) {
+            f32x16 sb[kG];
+#pragma unroll
+            for (int u = 0; u < kG; ++u) {
+              const int kb = k2 + u;
+              sb[u] = bias(t0, kb);
+#pragma unroll
+              for (int r = 0; r < 16; ++r) dsb[kb][r] = -Dq;      // dP - D straight from the product
+#pragma unroll
+              for (int c = 0; c < HD / 16; ++c) {
+                mma16(sb[u], tile_row_op<T, HD>(kt, ta, 32 * kb, c), qop[c]);
+                mma16(dsb[kb], tile_row_op<T, HD>(vr, ta, 32 * kb, c), dop[c]);
+              }
+            }
+#pragma unroll
+            for (int u = 0; u < kG; ++u) {
+              const int kb = k2 + u;
+#pragma unroll
+              for (int r = 0; r < 16; ++r) dsb[kb][r] *= __builtin_amdgcn_exp2f(sb[u][r] * scale_log2 - lse2);
+#pragma unroll
+              for (int c = 0; c < 2; ++c) {
+                const auto dop_ = pack8<T>(dsb[kb], 8 * c);
+#pragma unroll
+                for (int eb = 0; eb < HD / 32; ++eb) mma16(dqacc[eb], tile_tr_op<T, HD>(kt, ta, kb, c, eb), dop_);
+              }
+            }
+          }
+        };
+        // bias bins of the tile at t0 (see bwd_dq_kernel)
+        auto add_bins = [&](int t0) {
+          const uint16_t* knb = knball + t0;
+          float* mybins = dtab + (wave & 3) * g.nbins;
+          // bin of (this lane's query, key kk): qbins - knb[kk] in bytes
+          char* qbins = reinterpret_cast<char*>(mybins + qoff);
+          auto bin = [&](int kk) -> float& { return *reinterpret_cast<float*>(qbins - knb[kk]); };
+          if (fold) {
+            float fa[2][4], fb[2][4];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+              for (int g4 = 0; g4 < 4; ++g4) {
+                const float d0 = dsb[kb][4 * g4], d1 = dsb[kb][4 * g4 + 1];
+                const float d2 = dsb[kb][4 * g4 + 2], d3 = dsb[kb][4 * g4 + 3];
+                float f = d3;
+                f = d2 + fnext * dpp_lane<kDppNext>(f);
+                f = d1 + fnext * dpp_lane<kDppNext>(f);
+                fa[kb][g4] = d0 + fnext * dpp_lane<kDppNext>(f);
+                const float p1 = dpp_lane<kDppWavePrev>(d2 * fsend);
+                const float p2 = dpp_lane<kDppWavePrev>(dpp_lane<kDppWavePrev>(d1 * fsend) * fsend);
+                fb[kb][g4] = fkeep * (d3 + p1 + p2);
+              }
+            // One update of this lane: the folded pair sums of key block kb,
+            // group g4 (fa at (q, k), fb at (q, k+3)).
+            auto upd = [&](int kb, int g4, float va, float vb) {
+              const int kk = kb * 32 + 8 * g4 + 4 * half;
+              if (va != 0.0f) bin(kk) += va;
+              if (vb != 0.0f) bin(kk + 3) += vb;
+            };
+            {
+              // Both halves update with one instruction when their keys are at
+              // least 32 tokens apart: the 32 queries of a half are consecutive
+              // tokens, so (q, k) and (q', k') share a bin only if |k - k'| =
+              // |q - q'| < 32.  Half 0 takes block 0 group t while half 1 takes
+              // block 1 group t (keys 32 + 4 or more apart), then half 0 takes
+              // block 1 group t while half 1 takes block 0 group t - 1 (36 or
+              // more), and the two updates left over go alone.
+              if (q0 + wave * kWaveQ + kWaveQ <= n && t0 + 64 <= n) {
+                // Every query of the wave and every key of the tile is a window
+                // token: the updates need no guard (adding 0 to a bin that no
+                // other lane of the instruction touches changes nothing), and
+                // the key words are read before the first update.  Word index of
+                // this lane's group: 36 half + 8t in the first round, 32 - 36 half
+                // + 8t in the second, 32 (half 0) or 28 (half 1) left over.
+                float* w1[4][2];
+                float* w2[3][2];
+                float* wl[2];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                  const int kk = 36 * half + 8 * t;
+                  w1[t][0] = &bin(kk);
+                  w1[t][1] = &bin(kk + 3);
+                }
+#pragma unroll
+                for (int t = 1; t < 4; ++t) {
+                  const int kk = 32 - 36 * half + 8 * t;
+                  w2[t - 1][0] = &bin(kk);
+                  w2[t - 1][1] = &bin(kk + 3);
+                }
+                {
+                  const int kk = half ? 28 : 32;
+                  wl[0] = &bin(kk);
+                  wl[1] = &bin(kk + 3);
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                  *w1[t][0] += half ? fa[1][t] : fa[0][t];
+                  *w1[t][1] += half ? fb[1][t] : fb[0][t];
+                }
+#pragma unroll
+                for (int t = 1; t < 4; ++t) {
+                  *w2[t - 1][0] += half ? fa[0][t - 1] : fa[1][t];
+                  *w2[t - 1][1] += half ? fb[0][t - 1] : fb[1][t];
+                }
+                if (half == 0) { *wl[0] += fa[1][0]; *wl[1] += fb[1][0]; }
+                __builtin_amdgcn_wave_barrier();
+                if (half == 1) { *wl[0] += fa[0][3]; *wl[1] += fb[0][3]; }
+                __builtin_amdgcn_wave_barrier();
+              } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                  const int kb = half, gt = t;
+                  upd(kb, gt, half ? fa[1][t] : fa[0][t], half ? fb[1][t] : fb[0][t]);
+                }
+#pragma unroll
+                for (int t = 1; t < 4; ++t) {
+                  const int kb = 1 - half, gt = t - half;
+                  upd(kb, gt, half ? fa[0][t - 1] : fa[1][t], half ? fb[0][t - 1] : fb[1][t]);
+                }
+                if (half == 0) upd(1, 0, fa[1][0], fb[1][0]);
+                __builtin_amdgcn_wave_barrier();
+                if (half == 1) upd(0, 3, fa[0][3], fb[0][3]);
+                __builtin_amdgcn_wave_barrier();
+              }
+            }
+            // pairs of runs shorter than three lanes that the fold left out
+            if (__builtin_amdgcn_ballot_w64((run < 1 && rest < 2) || (run < 2 && rest < 1)) != 0) {
+#pragma unroll 1
+              for (int hh = 0; hh < 2; ++hh) {
+                if (half == hh) {
+#pragma unroll
+                  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int g4 = 0; g4 < 4; ++g4) {
+                      const int kk = kb * 32 + 8 * g4 + 4 * half;
+#pragma unroll
+                      for (int x = 1; x < 3; ++x)
+                        if (run < x && rest < 3 - x && dsb[kb][4 * g4 + x] != 0.0f)
+                          bin(kk + x) += dsb[kb][4 * g4 + x];
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+              }
+            }
+          } else {
+#pragma unroll 1
+            for (int hh = 0; hh < 2; ++hh) {
+              if (half == hh) {
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                  for (int r = 0; r < 16; ++r) {
+                    if (dsb[kb][r] != 0.0f) bin(kb * 32 + acc_row(r, half)) += dsb[kb][r];
+                  }
+              }
+              __builtin_amdgcn_wave_barrier();
+            }
+          }
+        };
+        for (int tix = 0; tix < nt; ++tix, ++vis) {
+          turn();                                     // barrier A
+          const int buf = vis & 1;
+          if constexpr (kPart == 0) {
+            if (!wactive) continue;
+            compute(tix, buf);
+            add_bins(64 * tix);
+          } else if constexpr (kPart == 1) {
+            if (wactive) compute(tix, buf);
+            lds_barrier();                            // barrier B
+            if (wactive) add_bins(64 * tix);
+          } else {
+            if (wactive && tix > 0) add_bins(64 * (tix - 1));
+            lds_barrier();
+            if (wactive) compute(tix, buf);
+          }
+        }
+        if constexpr (kPart != 0) lds_barrier();
+        if constexpr (kPart == 2)
+          if (wactive) add_bins(64 * (nt - 1));
+        if (qvalid) {
+          T* row = dq + qtok;
+#pragma unroll
+          for (int eb = 0; eb < HD / 32; ++eb)
+#pragma unroll
+            for (int grp = 0; grp < 4; ++grp) {
+              typedef T v4 __attribute__((ext_vector_type(4)));
+              v4 p;
+#pragma unroll
+              for (int x = 0; x < 4; ++x) p[x] = from_float<T>(dqacc[eb][4 * grp + x] * scale);
+              *reinterpret_cast<v4*>(row + eb * 32 + 8 * grp + 4 * half) = p;
+            }
+        }
+      };
+      if constexpr (!kTurns) main_sweep(std::integral_constant<int, 0>{});
+      else if (!second) main_sweep(std::integral_constant<int, 1>{});
+      else main_sweep(std::integral_constant<int, 2>{});
+    };
+    if (window_has_labels(g, i, j) || (n & 63) != 0) sweeps(std::true_type{});
+    else sweeps(std::false_type{});
+  }
+  lds_barrier();
+  float* out = partial + ((int64_t)h * nslice + slice) * g.nbins;
+  for (int x = threadIdx.x; x < g.nbins; x += NT) {
+    float sum = dtab[x];
+#pragma unroll
+    for (int c = 1; c < kCopies; ++c) sum += dtab[c * g.nbins + x];
+    out[x] = sum;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1664,6 +2015,13 @@ static size_t dkdv_lds(const Geo& g) {
          (HD > 64 ? 4 * g.wh * g.ww : 0);    // token table (head dim 128 only)
 }
 
+// The 16-bit dQ kernel: two {K, V} tile pairs, seven bytes per window token,
+// the bias table and four copies of the bins.
+template <int HD>
+static size_t dq16_lds(const Geo& g) {
+  const size_t nP = (g.wh * g.ww + 63) & ~63;
+  return 4 * 64 * HD * 2 + 7 * nP + 4 * (g.nbins + 4) + 16 * g.nbins;
+}
 // The 16-bit dK/dV kernel: two {Q, dO} tile pairs, five words per window
 // token, the bias table.  Never more than a workgroup has where the dQ
 // kernel's plan (whose five bias copies decide which windows are accepted)
@@ -1749,8 +2107,8 @@ static hipError_t fwd_impl(const Geo& g, const void* q, const void* k, const voi
     const int grid = grid8(g.B * g.nwin * g.heads * nqc);
     const size_t lds = fwd_lds<T, HD>(g);
 #define TERRA_LAUNCH_FWD(QD)                                                                      \
-  hipLaunchKernelGGL((fwd_kernel<T, HD, NHWC, QD, false>), dim3(grid), dim3(kThreads), lds, st,    \
-                     (const T*)q, (const T*)k, (const T*)v, table, (T*)o, (T*)olo, lse, g, nqc, sl2)
+  hipLaunchKernelGGL((fwd_kernel<T, HD, NHWC, QD>), dim3(grid), dim3(kThreads), lds, st,           \
+                     (const T*)q, (const T*)k, (const T*)v, table, (T*)o, lse, g, nqc, sl2)
     if (quad) TERRA_LAUNCH_FWD(true);
     else TERRA_LAUNCH_FWD(false);
 #undef TERRA_LAUNCH_FWD
@@ -1774,44 +2132,66 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
   float* D = reinterpret_cast<float*>(ws);
   float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + ((dbytes + 255) / 256) * 256);
   hipError_t e;
-  const int nqc = num_chunks(g);
   const float sl2 = kLog2e / sqrtf((float)HD);
   const float scale = 1.0f / sqrtf((float)HD);
-  const size_t lds_dq = dq_lds<T, HD>(g);
   const bool quad = quad_layout(g);
-  const bool res = dq_tiles<T, HD>(g) > 1;
-  const void* dq_fn;
-  if constexpr (sizeof(T) == 2 && HD <= 64) {
-    dq_fn = quad ? (res ? reinterpret_cast<const void*>(&bwd_dq_kernel<T, HD, NHWC, true, true>)
-                        : reinterpret_cast<const void*>(&bwd_dq_kernel<T, HD, NHWC, true, false>))
-                 : (res ? reinterpret_cast<const void*>(&bwd_dq_kernel<T, HD, NHWC, false, true>)
-                        : reinterpret_cast<const void*>(&bwd_dq_kernel<T, HD, NHWC, false, false>));
-  } else {
-    dq_fn = quad ? reinterpret_cast<const void*>(&bwd_dq_kernel<T, HD, NHWC, true, false>)
-                 : reinterpret_cast<const void*>(&bwd_dq_kernel<T, HD, NHWC, false, false>);
-  }
-  int resident = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, dq_fn, kThreads, lds_dq) != hipSuccess) {
-    (void)hipGetLastError();
-    resident = 2;
-  }
-  int nslice = slices_for(g, resident < 1 ? 1 : resident);
   const int nmax = bwd_nslice_max_t<T>(g);
-  if (nslice > nmax) nslice = nmax;
-#define TERRA_LAUNCH_DQ(QD, RS)                                                                 \
-  hipLaunchKernelGGL((bwd_dq_kernel<T, HD, NHWC, QD, RS>), dim3(g.heads * nslice), dim3(kThreads),  \
-                     lds_dq, st, (const T*)q, (const T*)k, (const T*)v, (const T*)o, (const T*)olo,  \
-                     (const T*)dout, lse, D, table, (T*)dq, partial, g, nqc, nslice, sl2, scale)
-  if constexpr (sizeof(T) == 2 && HD <= 64) {
-    if (quad && res) TERRA_LAUNCH_DQ(true, true);
-    else if (quad) TERRA_LAUNCH_DQ(true, false);
-    else if (res) TERRA_LAUNCH_DQ(false, true);
-    else TERRA_LAUNCH_DQ(false, false);
-  } else {
-    if (quad) TERRA_LAUNCH_DQ(true, false);
-    else TERRA_LAUNCH_DQ(false, false);
-  }
+  // one round of resident workgroups, whole heads
+  auto slices = [&](const void* fn, int threads, size_t lds, int nqc) {
+    int resident = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, fn, threads, lds) != hipSuccess) {
+      (void)hipGetLastError();
+      resident = 2;
+    }
+    const int n = std::min(g.B * g.nwin * nqc, g.cus * std::max(resident, 1) / g.heads);
+    return std::max(1, std::min(n, nmax));
+  };
+  int nslice = 1;
+  // (the largest windows at 128 channels do not fit the 16-bit kernel's two
+  // tile pairs beside four bin copies and keep the general kernel)
+  if (sizeof(T) == 2 && g.wh * g.ww > 256 && dq16_lds<HD>(g) <= 160 * 1024) {
+    if constexpr (sizeof(T) == 2) {
+      const size_t lds = dq16_lds<HD>(g);
+      const int nw = 2 * lds <= 160 * 1024 ? 4 : 8;
+      const int nqc = ((g.wh * g.ww + 31) / 32 + nw - 1) / nw;
+#define TERRA_LAUNCH_DQ(QD, NW_)                                                                      \
+  do {                                                                                                \
+    nslice = slices(reinterpret_cast<const void*>(&bwd_dq16_kernel<T, HD, NHWC, QD, NW_>), NW_ * 64,   \
+                    lds, nqc);                                                                        \
+    hipLaunchKernelGGL((bwd_dq16_kernel<T, HD, NHWC, QD, NW_>), dim3(grid8(g.heads * nslice)),          \
+                       dim3(NW_ * 64), lds, st, (const T*)q, (const T*)k, (const T*)v, (const T*)o,     \
+                       (const T*)olo, (const T*)dout, lse, D, table, (T*)dq, partial, g, nqc, nslice,   \
+                       sl2, scale);                                                                   \
+  } while (0)
+      if (quad && nw == 4) TERRA_LAUNCH_DQ(true, 4);
+      else if (quad) TERRA_LAUNCH_DQ(true, 8);
+      else if (nw == 4) TERRA_LAUNCH_DQ(false, 4);
+      else TERRA_LAUNCH_DQ(false, 8);
 #undef TERRA_LAUNCH_DQ
+    }
+  } else {
+    const int nqc = num_chunks(g);
+    const size_t lds_dq = dq_lds<T, HD>(g);
+#define TERRA_LAUNCH_DQ(QD, RS)                                                                       \
+  do {                                                                                                \
+    nslice = slices(reinterpret_cast<const void*>(&bwd_dq_kernel<T, HD, NHWC, QD, RS>), kThreads,      \
+                    lds_dq, nqc);                                                                     \
+    hipLaunchKernelGGL((bwd_dq_kernel<T, HD, NHWC, QD, RS>), dim3(g.heads * nslice), dim3(kThreads),    \
+                       lds_dq, st, (const T*)q, (const T*)k, (const T*)v, (const T*)o, (const T*)olo,   \
+                       (const T*)dout, lse, D, table, (T*)dq, partial, g, nqc, nslice, sl2, scale);     \
+  } while (0)
+    const bool res = dq_tiles<T, HD>(g) > 1;
+    if constexpr (sizeof(T) == 2 && HD <= 64) {
+      if (quad && res) TERRA_LAUNCH_DQ(true, true);
+      else if (quad) TERRA_LAUNCH_DQ(true, false);
+      else if (res) TERRA_LAUNCH_DQ(false, true);
+      else TERRA_LAUNCH_DQ(false, false);
+    } else {
+      if (quad) TERRA_LAUNCH_DQ(true, false);
+      else TERRA_LAUNCH_DQ(false, false);
+    }
+#undef TERRA_LAUNCH_DQ
+  }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if constexpr (sizeof(T) == 2) {
@@ -1836,6 +2216,7 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
 #undef TERRA_LAUNCH_KVN
 #undef TERRA_LAUNCH_KV
   } else {
+    const int nqc = num_chunks(g);
     const int grid = g.B * g.nwin * g.heads * nqc;
     const size_t lds_kv = dkdv_lds<T, HD>(g);
     if (quad)
