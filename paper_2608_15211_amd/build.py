@@ -14,7 +14,11 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libterra_swin.so")
-SOURCES = ["route.hip", "attn.hip", "attn_win.hip", "dtab.hip", "plan.hip", "block.hip", "abi.hip"]
+# attn.hip holds one element type's kernels per compilation (0 float, 1
+# bfloat16, 2 float16), so that they build in parallel.
+SOURCES = [("attn.hip", ["-DTERRA_ATTN_T=1"]), ("attn.hip", ["-DTERRA_ATTN_T=2"]), ("attn.hip", ["-DTERRA_ATTN_T=0"]),
+           ("route.hip", []), ("attn_win.hip", []), ("dtab.hip", []), ("plan.hip", []), ("block.hip", []),
+           ("abi.hip", [])]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -40,13 +44,13 @@ def build(verbose=False):
     """Compile every source and link libterra_swin.so.  Always rebuilds."""
     bdir = os.path.join(ROOT, "_build")
     os.makedirs(bdir, exist_ok=True)
-    objs = [os.path.join(bdir, s.replace(".hip", ".o")) for s in SOURCES]
+    objs = [os.path.join(bdir, s.replace(".hip", "") + "".join(d[-1] for d in defs) + ".o") for s, defs in SOURCES]
 
     def comp(pair):
-        src, obj = pair
-        return _run([HIPCC] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj])
+        (src, defs), obj = pair
+        return _run([HIPCC] + FLAGS + defs + ["-c", os.path.join(CSRC, src), "-o", obj])
 
-    with ThreadPoolExecutor(max_workers=min(4, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(6, len(SOURCES))) as ex:
         outs = list(ex.map(comp, zip(SOURCES, objs)))
     tmp = LIB + ".tmp"
     outs.append(_run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs))

@@ -2054,10 +2054,12 @@ static int bwd_nslice_max_t(const Geo& g) {
   if (per_cu > 8) per_cu = 8;
   return slices_for(g, per_cu < 1 ? 1 : per_cu);
 }
+#if TERRA_ATTN_T == 0
 int bwd_nslice(const Geo& g, int dt) {
   return dt == kF32 ? bwd_nslice_max_t<float>(g) : dt == kBF16 ? bwd_nslice_max_t<__bf16>(g)
                                                                : bwd_nslice_max_t<_Float16>(g);
 }
+#endif
 
 // Waves of a 16-bit workgroup whose plan takes `lds` bytes.  Four where two
 // workgroups fit a CU's LDS, else eight (dK/dV, 1024-token windows of 128
@@ -2091,12 +2093,15 @@ static hipError_t fwd_impl(const Geo& g, const void* q, const void* k, const voi
                      (const T*)q, (const T*)k, (const T*)v, table, (T*)o, (T*)olo, lse, g, nqc, sl2)
 #define TERRA_LAUNCH_FWDN(NW_)                                \
   do {                                                        \
-    if (quad && olo != nullptr) TERRA_LAUNCH_FWD(true, true, NW_);   \
-    else if (olo != nullptr) TERRA_LAUNCH_FWD(false, true, NW_);     \
-    else if (quad) TERRA_LAUNCH_FWD(true, false, NW_);               \
-    else TERRA_LAUNCH_FWD(false, false, NW_);                        \
+    if (quad) TERRA_LAUNCH_FWD(true, false, NW_);             \
+    else TERRA_LAUNCH_FWD(false, false, NW_);                 \
   } while (0)
-    if (nw == 4) TERRA_LAUNCH_FWDN(4);
+    if (olo != nullptr) {      // windows of more than 256 tokens: four or eight waves
+      if (quad && nw == 8) TERRA_LAUNCH_FWD(true, true, 8);
+      else if (quad) TERRA_LAUNCH_FWD(true, true, 4);
+      else if (nw == 8) TERRA_LAUNCH_FWD(false, true, 8);
+      else TERRA_LAUNCH_FWD(false, true, 4);
+    } else if (nw == 4) TERRA_LAUNCH_FWDN(4);
     else if (nw == 2) TERRA_LAUNCH_FWDN(2);
     else if (nw == 8) TERRA_LAUNCH_FWDN(8);
     else if constexpr (HD == 32) TERRA_LAUNCH_FWDN(3);
@@ -2116,12 +2121,14 @@ static hipError_t fwd_impl(const Geo& g, const void* q, const void* k, const voi
   return hipGetLastError();
 }
 
+#if TERRA_ATTN_T == 0
 size_t bwd_workspace(const Geo& g, int dt) {
   if (win_bwd_ok(g, dt == 1)) return (size_t)g.heads * win_bwd_nslice(g) * g.nbins * sizeof(float);
   const size_t dbytes = (size_t)g.B * g.heads * g.HW * sizeof(float);
   const size_t pbytes = (size_t)g.heads * bwd_nslice(g, dt) * g.nbins * sizeof(float);
   return ((dbytes + 255) / 256) * 256 + pbytes;
 }
+#endif
 
 template <typename T, int HD, bool NHWC>
 static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const void* v,
@@ -2235,6 +2242,7 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
 
 // Element type codes of the C ABI: 0 float, 1 bfloat16, 2 float16.
 
+#if TERRA_ATTN_T == 0
 template <typename T>
 static size_t max_lds_t(const Geo& g) {
   size_t m, d;
@@ -2253,6 +2261,7 @@ size_t attn_max_lds(const Geo& g, int dt) {
   if (win_bwd_ok(g, bf) && win_bwd_lds(g) > m) m = win_bwd_lds(g);
   return m;
 }
+#endif
 
 template <typename T, bool NHWC>
 static hipError_t fwd_generic(const Geo& g, const void* q, const void* k, const void* v,
@@ -2276,25 +2285,35 @@ static hipError_t bwd_generic(const Geo& g, const void* q, const void* k, const 
   }
 }
 
-template <bool NHWC>
-static hipError_t fwd_dispatch(const Geo& g, int dt, const void* q, const void* k, const void* v,
-                               const float* table, void* o, void* olo, float* lse, hipStream_t st) {
-  if (dt == kF32) return fwd_generic<float, NHWC>(g, q, k, v, table, o, nullptr, lse, st);
-  if (dt == kBF16) return fwd_generic<__bf16, NHWC>(g, q, k, v, table, o, olo, lse, st);
-  return fwd_generic<_Float16, NHWC>(g, q, k, v, table, o, olo, lse, st);
-}
-
-template <bool NHWC>
-static hipError_t bwd_dispatch(const Geo& g, int dt, const void* q, const void* k, const void* v,
-                               const void* o, const void* olo, const void* dout, const float* lse,
-                               const float* table, void* dq, void* dk, void* dv, float* dtab, void* ws,
-                               hipStream_t st) {
-  if (dt == kF32)
-    return bwd_generic<float, NHWC>(g, q, k, v, o, nullptr, dout, lse, table, dq, dk, dv, dtab, ws, st);
-  if (dt == kBF16)
-    return bwd_generic<__bf16, NHWC>(g, q, k, v, o, olo, dout, lse, table, dq, dk, dv, dtab, ws, st);
-  return bwd_generic<_Float16, NHWC>(g, q, k, v, o, olo, dout, lse, table, dq, dk, dv, dtab, ws, st);
-}
+// The launchers of one element type (this file is compiled once per type,
+// TERRA_ATTN_T = 0 float, 1 bfloat16, 2 float16, so that the kernels build in
+// parallel; the type-independent rest belongs to type 0).
+#define TERRA_ATTN_FWD(name)                                                                          \
+  hipError_t name(const Geo& g, bool nhwc, const void* q, const void* k, const void* v,               \
+                  const float* table, void* o, void* olo, float* lse, hipStream_t st)
+#define TERRA_ATTN_BWD(name)                                                                          \
+  hipError_t name(const Geo& g, bool nhwc, const void* q, const void* k, const void* v, const void* o, \
+                  const void* olo, const void* dout, const float* lse, const float* table, void* dq,   \
+                  void* dk, void* dv, float* dtab, void* ws, hipStream_t st)
+#define TERRA_ATTN_DEFINE(T, fwd, bwd)                                                                \
+  TERRA_ATTN_FWD(fwd) {                                                                               \
+    return nhwc ? fwd_generic<T, true>(g, q, k, v, table, o, olo, lse, st)                             \
+                : fwd_generic<T, false>(g, q, k, v, table, o, olo, lse, st);                           \
+  }                                                                                                   \
+  TERRA_ATTN_BWD(bwd) {                                                                               \
+    return nhwc ? bwd_generic<T, true>(g, q, k, v, o, olo, dout, lse, table, dq, dk, dv, dtab, ws, st)  \
+                : bwd_generic<T, false>(g, q, k, v, o, olo, dout, lse, table, dq, dk, dv, dtab, ws, st); \
+  }
+#if TERRA_ATTN_T == 1
+TERRA_ATTN_DEFINE(__bf16, attn_fwd_bf16, attn_bwd_bf16)
+#elif TERRA_ATTN_T == 2
+TERRA_ATTN_DEFINE(_Float16, attn_fwd_f16, attn_bwd_f16)
+#else
+TERRA_ATTN_FWD(attn_fwd_bf16);
+TERRA_ATTN_BWD(attn_bwd_bf16);
+TERRA_ATTN_FWD(attn_fwd_f16);
+TERRA_ATTN_BWD(attn_bwd_f16);
+TERRA_ATTN_DEFINE(float, attn_fwd_f32, attn_bwd_f32)
 
 // True when the forward writes the rounding residual O_lo and the backward
 // takes D from it: 16-bit types on the generic kernels with windows of more
@@ -2316,8 +2335,9 @@ hipError_t launch_attn_fwd(const Geo& g, int dt, bool nhwc, const void* q, const
                            hipStream_t st) {
   if (win_fwd_ok(g, dt == kBF16)) return launch_win_fwd(g, nhwc, q, k, v, table, o, lse, st);
   if (!attn_uses_olo(g, dt)) olo = nullptr;
-  return nhwc ? fwd_dispatch<true>(g, dt, q, k, v, table, o, olo, lse, st)
-              : fwd_dispatch<false>(g, dt, q, k, v, table, o, olo, lse, st);
+  if (dt == kF32) return attn_fwd_f32(g, nhwc, q, k, v, table, o, nullptr, lse, st);
+  if (dt == kBF16) return attn_fwd_bf16(g, nhwc, q, k, v, table, o, olo, lse, st);
+  return attn_fwd_f16(g, nhwc, q, k, v, table, o, olo, lse, st);
 }
 
 hipError_t launch_attn_bwd(const Geo& g, int dt, bool nhwc, const void* q, const void* k,
@@ -2332,8 +2352,11 @@ hipError_t launch_attn_bwd(const Geo& g, int dt, bool nhwc, const void* q, const
     return launch_dtab_reduce(g, partial, dtab, nslice, st);
   }
   if (!attn_uses_olo(g, dt)) olo = nullptr;
-  return nhwc ? bwd_dispatch<true>(g, dt, q, k, v, o, olo, dout, lse, table, dq, dk, dv, dtab, ws, st)
-              : bwd_dispatch<false>(g, dt, q, k, v, o, olo, dout, lse, table, dq, dk, dv, dtab, ws, st);
+  if (dt == kF32) return attn_bwd_f32(g, nhwc, q, k, v, o, nullptr, dout, lse, table, dq, dk, dv, dtab, ws, st);
+  if (dt == kBF16) return attn_bwd_bf16(g, nhwc, q, k, v, o, olo, dout, lse, table, dq, dk, dv, dtab, ws, st);
+  return attn_bwd_f16(g, nhwc, q, k, v, o, olo, dout, lse, table, dq, dk, dv, dtab, ws, st);
 }
+
+#endif  // TERRA_ATTN_T
 
 }  // namespace terra
