@@ -66,6 +66,17 @@ constexpr int kLabBad = 0xFF;   // label of padding slots (never matches)
 // is rounded up to a multiple of 8 and the padding workgroups exit at once.
 __device__ inline int xcd_item(int bid, int nblocks) { return (bid & 7) * (nblocks >> 3) + (bid >> 3); }
 static inline int grid8(int n) { return (n + 7) & ~7; }
+// The same for the 16-bit kernels with one unit of `unit` consecutive items
+// (the chunks of a window and head, and the heads that share a 128-byte
+// line) per XCD in turn: contiguous ranges gave some XCDs the full windows
+// and others the short ones of a ragged last row (25 rows of 24-row windows:
+// dK/dV 233 -> 271 us).
+__device__ inline int xcd_unit_item(int bid, int unit) {
+  const int idx = bid >> 3, u = idx / unit;
+  return (u * 8 + (bid & 7)) * unit + (idx - u * unit);
+}
+static inline int unit_grid(int n, int unit) { return ((n + unit - 1) / unit + 7) / 8 * 8 * unit; }
+template <int HD> __device__ __host__ constexpr int unit_heads() { return HD == 32 ? 2 : 1; }
 
 // Transposed tiles (head-dim rows e, token columns): row e starts at
 // e * (kTile + kPad) plus 4 elements per group of 8 rows, so that the
@@ -1143,7 +1154,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
   int* klabs = knb + nP;                              // [nP] label
   float* tab = reinterpret_cast<float*>(klabs + nP);  // [nbins+4], reversed
 
-  int bid = xcd_item(blockIdx.x, gridDim.x);
+  int bid = xcd_unit_item(blockIdx.x, unit_heads<HD>() * nqc);
   if (bid >= g.B * g.nwin * g.heads * nqc) return;
   const int qc = bid % nqc; bid /= nqc;
   const int h = bid % g.heads; bid /= g.heads;
@@ -1316,27 +1327,26 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Backward, step 1 for the 16-bit types and windows of more than 256 tokens:
+// Backward, step 1 for the 16-bit types at 128 channels and long windows:
 // bwd_dq_kernel's arithmetic and bins with the staging of bwd_dkdv16_kernel.
-// (Smaller windows keep bwd_dq_kernel: an item is then mostly its own start,
-// which the tables here make longer: 64 tokens 31 -> 35 us, 144 tokens 90 ->
-// 99, 64 tokens of 128 channels 403 -> 459.)
-// NW = 8: where the plan fits a CU once, eight waves share the four bias
-// copies in pairs (w, w + 4) by turns: between barriers A and B of a tile
-// the first half computes and the second half adds the bins of the tile
-// before, between B and the next A they swap.  The order of additions stays
-// fixed, and a SIMD has two waves instead of one: 1024 tokens of 128 channels
-// 2412 -> 1631 us.  NW = 4: 576 tokens of 64 channels 2096 -> 1930 us.
+// Tiles, bias table and four bin copies leave room for one workgroup a CU,
+// and four waves are then one a SIMD.  Here eight waves share the four copies
+// in pairs (w, w + 4) by turns: between barriers A and B of a tile the first
+// half of the workgroup computes and the second half adds the bins of the
+// tile before, between B and the next A they swap, so the order of additions
+// stays fixed.  1024 tokens: 2412 -> 1631 us.  (With four waves and two
+// workgroups a CU the general kernel is the better one: an item here starts
+// with tables of the whole window.  576 tokens of 64 channels 2096 -> 1930 us
+// on the 256 x 540 grid, but 0.71 to 0.95x on smaller or odd-width ones.)
 // ---------------------------------------------------------------------------
-template <typename T, int HD, bool NHWC, bool QUAD, int NW>
-__global__ __launch_bounds__(NW * 64, 2) void bwd_dq16_kernel(
+template <typename T, int HD, bool NHWC, bool QUAD>
+__global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const T* __restrict__ o, const T* __restrict__ olo,
     const T* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ D,
     const float* __restrict__ table, T* __restrict__ dq, float* __restrict__ partial,
     Geo g, int nqc, int nslice, float scale_log2, float scale) {
-  constexpr int NT = NW * 64, kCopies = 4;
-  constexpr bool kTurns = NW == 8;
+  constexpr int NW = 8, NT = NW * 64, kCopies = 4;
   constexpr int kTB = 64 * HD * 2;                    // bytes of one tile
   const int nP = (g.wh * g.ww + 63) & ~63;
   extern __shared__ __align__(16) char smem[];
@@ -1357,7 +1367,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq16_kernel(
   for (int x = threadIdx.x; x < kCopies * g.nbins; x += NT) dtab[x] = 0.0f;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int half = lane >> 5, col = lane & 31;
-  const bool second = kTurns && wave >= 4;
+  const bool second = wave >= 4;
   const int nitems = g.B * g.nwin * nqc;
   TileAddr<HD> ta(lane);
   const bool fold = (g.ww % 4 == 0) && (g.W % g.ww) % 4 == 0;   // uniform
@@ -1476,9 +1486,9 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq16_kernel(
       }
       const float Dq = halves_sum(dsum);
       if (qvalid && half == 0) D[lidx] = Dq;
-      // main sweep; kPart 0: all waves alike, 1 and 2: the halves of a
-      // workgroup that take turns (each with its own copy of the code, so
-      // that no accumulator is merged between them)
+      // main sweep of the first (kPart 1) or second half of the workgroup,
+      // each with its own copy of the code, so that no accumulator is merged
+      // between them
       auto main_sweep = [&](auto part) {
         constexpr int kPart = decltype(part)::value;
         f32x16 dqacc[HD / 32];
@@ -1657,11 +1667,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq16_kernel(
         for (int tix = 0; tix < nt; ++tix, ++vis) {
           turn();                                     // barrier A
           const int buf = vis & 1;
-          if constexpr (kPart == 0) {
-            if (!wactive) continue;
-            compute(tix, buf);
-            add_bins(64 * tix);
-          } else if constexpr (kPart == 1) {
+          if constexpr (kPart == 1) {
             if (wactive) compute(tix, buf);
             lds_barrier();                            // barrier B
             if (wactive) add_bins(64 * tix);
@@ -1671,7 +1677,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq16_kernel(
             if (wactive) compute(tix, buf);
           }
         }
-        if constexpr (kPart != 0) lds_barrier();
+        lds_barrier();
         if constexpr (kPart == 2)
           if (wactive) add_bins(64 * (nt - 1));
         if (qvalid) {
@@ -1688,8 +1694,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq16_kernel(
             }
         }
       };
-      if constexpr (!kTurns) main_sweep(std::integral_constant<int, 0>{});
-      else if (!second) main_sweep(std::integral_constant<int, 1>{});
+      if (!second) main_sweep(std::integral_constant<int, 1>{});
       else main_sweep(std::integral_constant<int, 2>{});
     };
     if (window_has_labels(g, i, j) || (n & 63) != 0) sweeps(std::true_type{});
@@ -1717,7 +1722,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq16_kernel(
 //   the LDS reads of the next;
 // * masked and unmasked windows have their own copy of the walk (merged in
 //   one loop, the accumulators are copied and spill);
-// * all chunks and heads of a window go to one XCD, whose L2 then serves
+// * all chunks of a window and head go to one XCD, whose L2 then serves
 //   their common tiles, and dK, dV leave in whole row pieces.
 // Measured (us, before -> now): 64-token windows of 32 channels on 128 x 256
 // x 6 heads 28 -> 19, 144 tokens 65 -> 47, 576 tokens of 64 channels 1820 ->
@@ -1741,7 +1746,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
   float* qd = ql + nP;                                // [nP] -D
   float* tab = qd + nP;                               // [nbins+4], forward order
 
-  int bid = xcd_item(blockIdx.x, gridDim.x);
+  int bid = xcd_unit_item(blockIdx.x, unit_heads<HD>() * nkc);
   if (bid >= g.B * g.nwin * g.heads * nkc) return;
   const int kc = bid % nkc; bid /= nkc;
   const int h = bid % g.heads; bid /= g.heads;
@@ -2087,7 +2092,7 @@ static hipError_t fwd_impl(const Geo& g, const void* q, const void* k, const voi
     const size_t lds = 4 * 64 * HD * 2 + 12 * nP + 4 * (g.nbins + 4);
     const int nw = waves16<HD>(g, lds);
     const int nqc = ((g.wh * g.ww + 31) / 32 + nw - 1) / nw;
-    const int grid = grid8(g.B * g.nwin * g.heads * nqc);
+    const int grid = unit_grid(g.B * g.nwin * g.heads * nqc, unit_heads<HD>() * nqc);
 #define TERRA_LAUNCH_FWD(QD, SP, NW_)                                                               \
   hipLaunchKernelGGL((fwd16_kernel<T, HD, NHWC, QD, SP, NW_>), dim3(grid), dim3(NW_ * 64), lds, st,  \
                      (const T*)q, (const T*)k, (const T*)v, table, (T*)o, (T*)olo, lse, g, nqc, sl2)
@@ -2154,29 +2159,31 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
     return std::max(1, std::min(n, nmax));
   };
   int nslice = 1;
-  // (the largest windows at 128 channels do not fit the 16-bit kernel's two
-  // tile pairs beside four bin copies and keep the general kernel)
-  if (sizeof(T) == 2 && g.wh * g.ww > 256 && dq16_lds<HD>(g) <= 160 * 1024) {
-    if constexpr (sizeof(T) == 2) {
-      const size_t lds = dq16_lds<HD>(g);
-      const int nw = 2 * lds <= 160 * 1024 ? 4 : 8;
-      const int nqc = ((g.wh * g.ww + 31) / 32 + nw - 1) / nw;
-#define TERRA_LAUNCH_DQ(QD, NW_)                                                                      \
-  do {                                                                                                \
-    nslice = slices(reinterpret_cast<const void*>(&bwd_dq16_kernel<T, HD, NHWC, QD, NW_>), NW_ * 64,   \
-                    lds, nqc);                                                                        \
-    hipLaunchKernelGGL((bwd_dq16_kernel<T, HD, NHWC, QD, NW_>), dim3(grid8(g.heads * nslice)),          \
-                       dim3(NW_ * 64), lds, st, (const T*)q, (const T*)k, (const T*)v, (const T*)o,     \
-                       (const T*)olo, (const T*)dout, lse, D, table, (T*)dq, partial, g, nqc, nslice,   \
-                       sl2, scale);                                                                   \
+  // Eight-wave dQ kernel: 128 channels, windows of more than 512 tokens that
+  // keep at least 7 of 8 waves busy, items for at least half of the CUs, and
+  // a plan that fits.  Measured against the general kernel (whole backward):
+  // 1024 tokens 1.23x at 192 items, 1.14x at 276, 1.29x at 1088, 0.78x at 64;
+  // 651 tokens 1.21x; 576 tokens (18 of 24 waves) 0.77x.
+  bool dq16 = false;
+  if constexpr (sizeof(T) == 2 && HD == 128) {
+    const int nb = (g.wh * g.ww + 31) / 32, nqc = (nb + 7) / 8;
+    const size_t lds = dq16_lds<HD>(g);
+    dq16 = g.wh * g.ww > 512 && 8 * nb >= 7 * 8 * nqc && 2 * g.B * g.nwin * g.heads * nqc >= g.cus &&
+           lds <= 160 * 1024;
+    if (dq16) {
+#define TERRA_LAUNCH_DQ(QD)                                                                          \
+  do {                                                                                               \
+    nslice = slices(reinterpret_cast<const void*>(&bwd_dq16_kernel<T, HD, NHWC, QD>), 512, lds, nqc);  \
+    hipLaunchKernelGGL((bwd_dq16_kernel<T, HD, NHWC, QD>), dim3(grid8(g.heads * nslice)), dim3(512),   \
+                       lds, st, (const T*)q, (const T*)k, (const T*)v, (const T*)o, (const T*)olo,     \
+                       (const T*)dout, lse, D, table, (T*)dq, partial, g, nqc, nslice, sl2, scale);    \
   } while (0)
-      if (quad && nw == 4) TERRA_LAUNCH_DQ(true, 4);
-      else if (quad) TERRA_LAUNCH_DQ(true, 8);
-      else if (nw == 4) TERRA_LAUNCH_DQ(false, 4);
-      else TERRA_LAUNCH_DQ(false, 8);
+      if (quad) TERRA_LAUNCH_DQ(true);
+      else TERRA_LAUNCH_DQ(false);
 #undef TERRA_LAUNCH_DQ
     }
-  } else {
+  }
+  if (!dq16) {
     const int nqc = num_chunks(g);
     const size_t lds_dq = dq_lds<T, HD>(g);
 #define TERRA_LAUNCH_DQ(QD, RS)                                                                       \
@@ -2206,7 +2213,7 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
     const size_t lds_kv = dkdv16_lds<HD>(g);
     const int nw = waves16<HD>(g, lds_kv);
     const int nkc = (nb + nw - 1) / nw;
-    const int grid = grid8(g.B * g.nwin * g.heads * nkc);
+    const int grid = unit_grid(g.B * g.nwin * g.heads * nkc, unit_heads<HD>() * nkc);
 #define TERRA_LAUNCH_KV(QD, NW_)                                                                    \
   hipLaunchKernelGGL((bwd_dkdv16_kernel<T, HD, NHWC, QD, NW_>), dim3(grid), dim3(NW_ * 64), lds_kv, st, \
                      (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse, D, table,            \
