@@ -76,7 +76,12 @@ __device__ inline int xcd_unit_item(int bid, int unit) {
   return (u * 8 + (bid & 7)) * unit + (idx - u * unit);
 }
 static inline int unit_grid(int n, int unit) { return ((n + unit - 1) / unit + 7) / 8 * 8 * unit; }
-template <int HD> __device__ __host__ constexpr int unit_heads() { return HD == 32 ? 2 : 1; }
+// Up to two workgroups a CU, whole units would leave some XCDs short: single
+// items then (240 workgroups of 768 tokens: forward 26 us in units of 12).
+template <int HD>
+static int xcd_unit(const Geo& g, int chunks) {
+  return g.B * g.nwin * g.heads * chunks <= 2 * g.cus ? 1 : (HD == 32 ? 2 : 1) * chunks;
+}
 
 // Transposed tiles (head-dim rows e, token columns): row e starts at
 // e * (kTile + kPad) plus 4 elements per group of 8 rows, so that the
@@ -1143,7 +1148,7 @@ template <typename T, int HD, bool NHWC, bool QUAD, bool SPLIT, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const float* __restrict__ table, T* __restrict__ o, T* __restrict__ olo,
-    float* __restrict__ lse, Geo g, int nqc, float scale_log2) {
+    float* __restrict__ lse, Geo g, int nqc, int unit, float scale_log2) {
   constexpr int NT = NW * 64;
   constexpr int kTB = 64 * HD * 2;                    // bytes of one tile
   const int nP = (g.wh * g.ww + 63) & ~63;
@@ -1154,7 +1159,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
   int* klabs = knb + nP;                              // [nP] label
   float* tab = reinterpret_cast<float*>(klabs + nP);  // [nbins+4], reversed
 
-  int bid = xcd_unit_item(blockIdx.x, unit_heads<HD>() * nqc);
+  int bid = xcd_unit_item(blockIdx.x, unit);
   if (bid >= g.B * g.nwin * g.heads * nqc) return;
   const int qc = bid % nqc; bid /= nqc;
   const int h = bid % g.heads; bid /= g.heads;
@@ -1733,7 +1738,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const T* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ D,
     const float* __restrict__ table, T* __restrict__ dk, T* __restrict__ dv,
-    Geo g, int nkc, float scale_log2, float scale) {
+    Geo g, int nkc, int unit, float scale_log2, float scale) {
   constexpr int NT = NW * 64;
   constexpr int kTB = 64 * HD * 2;                    // bytes of one tile
   const int nP = (g.wh * g.ww + 63) & ~63;
@@ -1746,7 +1751,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
   float* qd = ql + nP;                                // [nP] -D
   float* tab = qd + nP;                               // [nbins+4], forward order
 
-  int bid = xcd_unit_item(blockIdx.x, unit_heads<HD>() * nkc);
+  int bid = xcd_unit_item(blockIdx.x, unit);
   if (bid >= g.B * g.nwin * g.heads * nkc) return;
   const int kc = bid % nkc; bid /= nkc;
   const int h = bid % g.heads; bid /= g.heads;
@@ -2069,7 +2074,9 @@ int bwd_nslice(const Geo& g, int dt) {
 // Waves of a 16-bit workgroup whose plan takes `lds` bytes.  Four where two
 // workgroups fit a CU's LDS, else eight (dK/dV, 1024-token windows of 128
 // channels: 2267 us with four, 1381 with eight).  Windows of up to 256 tokens
-// take fewer waves where that leaves fewer of them idle; longer ones keep
+// take fewer waves where that leaves fewer of them idle (at 128 channels only
+// up to 64 tokens: LDS holds two workgroups a CU whatever their waves; 144
+// tokens forward 23 us with two waves, 19 with four); longer ones keep
 // four (dK/dV, 576 tokens of 64 channels: 1603 us with four and a half-empty
 // last chunk, 1890 with three, 1864 with eight).
 template <int HD>
@@ -2078,7 +2085,7 @@ static int waves16(const Geo& g, size_t lds) {
   int nw = 2 * lds <= 160 * 1024 ? 4 : 8;
   if (nb <= 8)
     for (int c : {4, 3, 2})
-      if (c < nw && (HD == 32 || c != 3) && (nb + c - 1) / c * c < (nb + nw - 1) / nw * nw) nw = c;
+      if (c < nw && (HD == 32 || c != 3) && (HD < 128 || nb <= 2) && (nb + c - 1) / c * c < (nb + nw - 1) / nw * nw) nw = c;
   return nw;
 }
 
@@ -2092,10 +2099,11 @@ static hipError_t fwd_impl(const Geo& g, const void* q, const void* k, const voi
     const size_t lds = 4 * 64 * HD * 2 + 12 * nP + 4 * (g.nbins + 4);
     const int nw = waves16<HD>(g, lds);
     const int nqc = ((g.wh * g.ww + 31) / 32 + nw - 1) / nw;
-    const int grid = unit_grid(g.B * g.nwin * g.heads * nqc, unit_heads<HD>() * nqc);
+    const int unit = xcd_unit<HD>(g, nqc);
+    const int grid = unit_grid(g.B * g.nwin * g.heads * nqc, unit);
 #define TERRA_LAUNCH_FWD(QD, SP, NW_)                                                               \
   hipLaunchKernelGGL((fwd16_kernel<T, HD, NHWC, QD, SP, NW_>), dim3(grid), dim3(NW_ * 64), lds, st,  \
-                     (const T*)q, (const T*)k, (const T*)v, table, (T*)o, (T*)olo, lse, g, nqc, sl2)
+                     (const T*)q, (const T*)k, (const T*)v, table, (T*)o, (T*)olo, lse, g, nqc, unit, sl2)
 #define TERRA_LAUNCH_FWDN(NW_)                                \
   do {                                                        \
     if (quad) TERRA_LAUNCH_FWD(true, false, NW_);             \
@@ -2213,11 +2221,12 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
     const size_t lds_kv = dkdv16_lds<HD>(g);
     const int nw = waves16<HD>(g, lds_kv);
     const int nkc = (nb + nw - 1) / nw;
-    const int grid = unit_grid(g.B * g.nwin * g.heads * nkc, unit_heads<HD>() * nkc);
+    const int unit = xcd_unit<HD>(g, nkc);
+    const int grid = unit_grid(g.B * g.nwin * g.heads * nkc, unit);
 #define TERRA_LAUNCH_KV(QD, NW_)                                                                    \
   hipLaunchKernelGGL((bwd_dkdv16_kernel<T, HD, NHWC, QD, NW_>), dim3(grid), dim3(NW_ * 64), lds_kv, st, \
                      (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse, D, table,            \
-                     (T*)dk, (T*)dv, g, nkc, sl2, scale)
+                     (T*)dk, (T*)dv, g, nkc, unit, sl2, scale)
 #define TERRA_LAUNCH_KVN(NW_)             \
   do {                                    \
     if (quad) TERRA_LAUNCH_KV(true, NW_); \
