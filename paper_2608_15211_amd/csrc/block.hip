@@ -196,13 +196,12 @@ struct Stager {
   // koff: byte offset of the stage's first contraction index; krem:
   // contraction indices left from there
   __device__ void load(const i32x4& rs, bf16* tile, int koff, int krem) const {
+    static_assert(T::kPer == 4, "one group of four loads");
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: the LDS base goes to M0
+    int v[4];
 #pragma unroll
-    for (int u = 0; u < T::kPer; ++u) {
-      const int v = kpos[u] < krem ? voff[u] + koff : (int)0x80000000;
-      bf16* dst = tile + 8 * (u * NT + wave * 64);       // wave-uniform base of 64 slots
-      buffer_load_lds16(rs, dst, v);
-    }
+    for (int u = 0; u < 4; ++u) v[u] = kpos[u] < krem ? voff[u] + koff : (int)0x80000000;
+    buffer_load_lds16x4<16 * NT>(rs, tile + 8 * wave * 64, v);   // wave-uniform bases of 64 slots
   }
 };
 

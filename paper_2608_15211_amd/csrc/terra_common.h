@@ -293,20 +293,39 @@ __device__ inline typename Operand<T>::type pack8(const f32x16& acc, int r0) {
 // LDS write, so a wave waits for the load count (wait_vm) and the
 // workgroup then synchronises before any wave reads those bytes.
 //
-// Written as assembly (no result registers; M0 is set inside, and nothing
-// else in these kernels uses it): the compiler
-// tracks its built-in form as a pending LDS write and makes every LDS
-// transpose read after it wait for all loads in flight, which serialised the
-// loads and the products (weight gradient 3072 x 768 x 138240: 600 us, with
-// this form 551 us).  Loads the compiler does not count only make its own
-// counted waits longer, never shorter.
+// Written as assembly (no result registers): the compiler tracks its built-in
+// form as a pending LDS write and makes every LDS transpose read after it wait
+// for all loads in flight, which serialised the loads and the products (weight
+// gradient 3072 x 768 x 138240: 600 us, with this form 551 us).  What the
+// compiler does for the built-in load the assembly has to do itself:
+// * it does not count these loads: its own counted waits only get longer by
+//   them, never shorter;
+// * wait states: a descriptor word that a vector instruction wrote (a spilled
+//   scalar read back by v_readlane) may be read by a vector-memory instruction
+//   five wait states later at the earliest, and the hardware does not wait.
+//   The move to M0 and s_nop 3 make five whatever comes before (M0 itself
+//   needs one before a load that uses it).
 // ---------------------------------------------------------------------------
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void buffer_load_lds16(const i32x4& rsrc, const void* lds, int voffset) {
   const uint32_t dst = (uint32_t)(uintptr_t)lds;     // the low half of a generic LDS address is the LDS offset
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                ::"s"(dst), "v"(voffset), "s"(rsrc)
-               : "memory");
+               : "memory", "m0");
+}
+// Four of them, STEP bytes apart in LDS: no vector instruction comes between,
+// so the first one's wait states serve all (with five for each, the block's
+// backward at 128 x 1080 and 768 channels 1.1 % slower).
+template <int STEP>
+__device__ __forceinline__ void buffer_load_lds16x4(const i32x4& rsrc, const void* lds, const int (&voffset)[4]) {
+  const uint32_t dst = (uint32_t)(uintptr_t)lds;
+  asm volatile(
+      "s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %5, 0 offen lds\n\t"
+      "s_add_u32 m0, m0, %6\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %5, 0 offen lds\n\t"
+      "s_add_u32 m0, m0, %6\n\ts_nop 0\n\tbuffer_load_dwordx4 %3, %5, 0 offen lds\n\t"
+      "s_add_u32 m0, m0, %6\n\ts_nop 0\n\tbuffer_load_dwordx4 %4, %5, 0 offen lds"
+      ::"s"(dst), "v"(voffset[0]), "v"(voffset[1]), "v"(voffset[2]), "v"(voffset[3]), "s"(rsrc), "n"(STEP)
+      : "memory", "m0", "scc");
 }
 
 // Buffer descriptor of a whole operand: base, size in bytes (below 2^31, so
