@@ -1171,10 +1171,11 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
   const int q0 = qc * NW * 32;
   if (q0 >= n) return;
   const WinTokens<NHWC> wt(g, b, i, j);
+  const uint32_t ibytes = (uint32_t)g.HW * (uint32_t)(g.C * 2);
   const int nr = (n + 63) & ~63;
   for (int t = threadIdx.x; t < nr; t += NT) {
     const int inf = token_info(g, i, j, cols, t, n);
-    tokb[t] = (wt.tok(g, min(t, n - 1)) - wt.img0) * (uint32_t)(g.C * 2) + (uint32_t)(h * HD * 2);
+    tokb[t] = t < n ? (wt.tok(g, t) - wt.img0) * (uint32_t)(g.C * 2) + (uint32_t)(h * HD * 2) : tile_pad_row<HD>(ibytes);
     knb[t] = 4 * (inf & 0xFFFFFF);
     klabs[t] = inf >> 24;
   }
@@ -1184,7 +1185,6 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
   const bool mask = window_has_labels(g, i, j) || (n % 64) != 0;
 
   const int64_t img = (int64_t)wt.img0 * g.C;
-  const uint32_t ibytes = (uint32_t)g.HW * (uint32_t)(g.C * 2);
   const i32x4 rk = buffer_rsrc(k + img, ibytes), rv = buffer_rsrc(v + img, ibytes);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, col = lane & 31;
@@ -1388,15 +1388,16 @@ __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
     if (q0 >= n) continue;
     const WinTokens<NHWC> wt(g, b, i, j);
     const int nt = (n + 63) >> 6;
+    const uint32_t ibytes = (uint32_t)g.HW * (uint32_t)(g.C * 2);
     lds_barrier();                    // the previous item is done with the tables and tiles
     for (int t = threadIdx.x; t < 64 * nt; t += NT) {
       const int inf = token_info(g, i, j, cols, t, n);
-      tokb[t] = (wt.tok(g, min(t, n - 1)) - wt.img0) * (uint32_t)(g.C * 2) + (uint32_t)(h * HD * 2);
+      tokb[t] =
+          t < n ? (wt.tok(g, t) - wt.img0) * (uint32_t)(g.C * 2) + (uint32_t)(h * HD * 2) : tile_pad_row<HD>(ibytes);
       knball[t] = (uint16_t)(4 * (inf & 0xFFFFFF));
       klaball[t] = (uint8_t)(inf >> 24);
     }
     const int64_t img = (int64_t)wt.img0 * g.C;
-    const uint32_t ibytes = (uint32_t)g.HW * (uint32_t)(g.C * 2);
     const i32x4 rk = buffer_rsrc(k + img, ibytes), rv = buffer_rsrc(v + img, ibytes);
     auto load = [&](int tix, int buf) {
       tile_load_direct<HD, NT>(rk, tiles + buf * 2 * kTB, tokb, 64 * tix);
@@ -1765,12 +1766,13 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
   const WinTokens<NHWC> wt(g, b, i, j);
   // bias and log-sum-exp in score units (head dim 128) or log2 units
   const float lscale = HD == 128 ? sqrtf((float)HD) : kLog2e;
+  const uint32_t ibytes = (uint32_t)g.HW * (uint32_t)(g.C * 2);
   const int nr = (n + 63) & ~63;
   for (int t = threadIdx.x; t < nr; t += NT) {
     const uint32_t tok = wt.tok(g, min(t, n - 1));
     const int inf = token_info(g, i, j, cols, t, n);
     const uint32_t li = wt.img0 * (uint32_t)g.heads + (uint32_t)(h * g.HW) + (tok - wt.img0);
-    tokb[t] = (tok - wt.img0) * (uint32_t)(g.C * 2) + (uint32_t)(h * HD * 2);
+    tokb[t] = t < n ? (tok - wt.img0) * (uint32_t)(g.C * 2) + (uint32_t)(h * HD * 2) : tile_pad_row<HD>(ibytes);
     qnb[t] = 4 * (inf & 0xFFFFFF);
     qlab[t] = inf >> 24;
     ql[t] = t < n ? lse[li] * lscale : INFINITY;      // padding queries: P = 0
@@ -1781,7 +1783,6 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
   const bool mask = window_has_labels(g, i, j) || (n % 64) != 0;
 
   const int64_t img = (int64_t)wt.img0 * g.C;
-  const uint32_t ibytes = (uint32_t)g.HW * (uint32_t)(g.C * 2);
   const i32x4 rq = buffer_rsrc(q + img, ibytes), rd = buffer_rsrc(dout + img, ibytes);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, col = lane & 31;

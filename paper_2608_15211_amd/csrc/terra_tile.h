@@ -62,10 +62,18 @@ __device__ inline typename Operand<T>::type tile_tr_op(const char* t, const Tile
   return __builtin_bit_cast(typename Operand<T>::type, o);
 }
 
+// Row address of a tile row past the window's n tokens: one token past the
+// image (ibytes, below 2^32), where the load reads zeros.  The row's weights
+// are zero, and zero times a token's infinity would not be.  An image that
+// ends within two rows of 2^32 bytes has no room for that address and takes a
+// row of its last token.
+template <int HD>
+__device__ inline uint32_t tile_pad_row(uint32_t ibytes) { return min(ibytes, 0u - 4u * HD); }
+
 // Moves rows r0 .. r0 + 63 of one tensor into a tile: NT threads, each
 // 16-byte chunk written by the load itself.  tokb[r] is the byte offset of
-// token r's channels from the resource's base (padded to a multiple of 64
-// rows with the last token, whose values no result uses).
+// token r's channels from the resource's base (tile_pad_row from the window's
+// end to a multiple of 64 rows).
 template <int HD, int NT>
 __device__ inline void tile_load_direct(const i32x4& rs, char* tile, const uint32_t* tokb, int r0) {
   constexpr int kChunks = 64 * HD / 8;
