@@ -1144,7 +1144,7 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(
 // channels 42 -> 34, 576 of 64 with O_lo 1332 -> 1224, 64 of 128 309 -> 273,
 // 1024 of 128 with O_lo 1260 -> 1100.
 // ---------------------------------------------------------------------------
-template <typename T, int HD, bool NHWC, bool QUAD, bool SPLIT, int NW>
+template <typename T, int HD, bool NHWC, bool QUAD, bool SPLIT, int NW, bool DIRECT = true>
 __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const float* __restrict__ table, T* __restrict__ o, T* __restrict__ olo,
@@ -1197,8 +1197,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
       tab + (g.nbins - 1 - ((qinf & 0xFFFFFF) + (g.wh - 1) * g.bstride + (g.ww - 1))));
 
   lds_barrier();                                      // the row table
-  tile_load_direct<HD, NT>(rk, tiles, tokb, 0);
-  tile_load_direct<HD, NT>(rv, tiles + kTB, tokb, 0);
+  tile_load<HD, NT, DIRECT>(rk, tiles, tokb, 0);
+  tile_load<HD, NT, DIRECT>(rv, tiles + kTB, tokb, 0);
   typename Operand<T>::type qop[HD / 16];
   const uint32_t qtok = wt.tok(g, min(qi, n - 1)) * g.C + h * HD;
 #pragma unroll
@@ -1218,8 +1218,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
       wait_vm<0>();
       lds_barrier();        // tile t0 is in LDS; every wave is done with the other buffer
       if (t0 + 64 < n) {
-        tile_load_direct<HD, NT>(rk, tiles + (buf ^ 1) * 2 * kTB, tokb, t0 + 64);
-        tile_load_direct<HD, NT>(rv, tiles + (buf ^ 1) * 2 * kTB + kTB, tokb, t0 + 64);
+        tile_load<HD, NT, DIRECT>(rk, tiles + (buf ^ 1) * 2 * kTB, tokb, t0 + 64);
+        tile_load<HD, NT, DIRECT>(rv, tiles + (buf ^ 1) * 2 * kTB + kTB, tokb, t0 + 64);
       }
       if (!wactive) continue;
       const char* kt = tiles + buf * 2 * kTB;
@@ -1400,8 +1400,8 @@ __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
     const int64_t img = (int64_t)wt.img0 * g.C;
     const i32x4 rk = buffer_rsrc(k + img, ibytes), rv = buffer_rsrc(v + img, ibytes);
     auto load = [&](int tix, int buf) {
-      tile_load_direct<HD, NT>(rk, tiles + buf * 2 * kTB, tokb, 64 * tix);
-      tile_load_direct<HD, NT>(rv, tiles + buf * 2 * kTB + kTB, tokb, 64 * tix);
+      tile_load<HD, NT, true>(rk, tiles + buf * 2 * kTB, tokb, 64 * tix);
+      tile_load<HD, NT, true>(rv, tiles + buf * 2 * kTB + kTB, tokb, 64 * tix);
     };
     const int qi = q0 + wave * 32 + col;
     const bool qvalid = qi < n;
@@ -1734,7 +1734,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
 // x 6 heads 28 -> 19, 144 tokens 65 -> 47, 576 tokens of 64 channels 1820 ->
 // 1603, 1024 tokens of 128 channels 1650 -> 1381, 64 tokens 458 -> 434.
 // ---------------------------------------------------------------------------
-template <typename T, int HD, bool NHWC, bool QUAD, int NW>
+template <typename T, int HD, bool NHWC, bool QUAD, int NW, bool DIRECT = true>
 __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const T* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ D,
@@ -1795,8 +1795,8 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
   const char* tabk = reinterpret_cast<const char*>(tab + kfwd);
 
   lds_barrier();                                      // the row table
-  tile_load_direct<HD, NT>(rq, tiles, tokb, 0);
-  tile_load_direct<HD, NT>(rd, tiles + kTB, tokb, 0);
+  tile_load<HD, NT, DIRECT>(rq, tiles, tokb, 0);
+  tile_load<HD, NT, DIRECT>(rd, tiles + kTB, tokb, 0);
   typename Operand<T>::type kop[HD / 16], vop[HD / 16];
   const uint32_t ktok = wt.tok(g, min(ki, n - 1)) * g.C + h * HD;
 #pragma unroll
@@ -1946,8 +1946,8 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
       wait_vm<0>();
       lds_barrier();        // tile t0 is in LDS; every wave is done with the other buffer
       if (t0 + 64 < n) {
-        tile_load_direct<HD, NT>(rq, tiles + (buf ^ 1) * 2 * kTB, tokb, t0 + 64);
-        tile_load_direct<HD, NT>(rd, tiles + (buf ^ 1) * 2 * kTB + kTB, tokb, t0 + 64);
+        tile_load<HD, NT, DIRECT>(rq, tiles + (buf ^ 1) * 2 * kTB, tokb, t0 + 64);
+        tile_load<HD, NT, DIRECT>(rd, tiles + (buf ^ 1) * 2 * kTB + kTB, tokb, t0 + 64);
       }
       if (!wactive) continue;
       const char* qr = tiles + buf * 2 * kTB;
@@ -2090,6 +2090,11 @@ static int waves16(const Geo& g, size_t lds) {
   return nw;
 }
 
+// Tensors that the 16-bit kernels may load straight into LDS.  Others (views
+// at an odd element of a larger buffer) take one form for all windows: eight
+// waves, tiles through registers, pairs one by one.
+static bool direct_ok(const void* a, const void* b) { return (((uintptr_t)a | (uintptr_t)b) & 15) == 0; }
+
 template <typename T, int HD, bool NHWC>
 static hipError_t fwd_impl(const Geo& g, const void* q, const void* k, const void* v,
                            const float* table, void* o, void* olo, float* lse, hipStream_t st) {
@@ -2098,19 +2103,23 @@ static hipError_t fwd_impl(const Geo& g, const void* q, const void* k, const voi
   if constexpr (sizeof(T) == 2) {
     const size_t nP = (g.wh * g.ww + 63) & ~63;
     const size_t lds = 4 * 64 * HD * 2 + 12 * nP + 4 * (g.nbins + 4);
-    const int nw = waves16<HD>(g, lds);
+    const bool direct = direct_ok(k, v);
+    const int nw = direct ? waves16<HD>(g, lds) : 8;
     const int nqc = ((g.wh * g.ww + 31) / 32 + nw - 1) / nw;
     const int unit = xcd_unit<HD>(g, nqc);
     const int grid = unit_grid(g.B * g.nwin * g.heads * nqc, unit);
-#define TERRA_LAUNCH_FWD(QD, SP, NW_)                                                               \
-  hipLaunchKernelGGL((fwd16_kernel<T, HD, NHWC, QD, SP, NW_>), dim3(grid), dim3(NW_ * 64), lds, st,  \
+#define TERRA_LAUNCH_FWD(QD, SP, NW_, ...)                                                          \
+  hipLaunchKernelGGL((fwd16_kernel<T, HD, NHWC, QD, SP, NW_, ##__VA_ARGS__>), dim3(grid), dim3(NW_ * 64), lds, st,  \
                      (const T*)q, (const T*)k, (const T*)v, table, (T*)o, (T*)olo, lse, g, nqc, unit, sl2)
 #define TERRA_LAUNCH_FWDN(NW_)                                \
   do {                                                        \
     if (quad) TERRA_LAUNCH_FWD(true, false, NW_);             \
     else TERRA_LAUNCH_FWD(false, false, NW_);                 \
   } while (0)
-    if (olo != nullptr) {      // windows of more than 256 tokens: four or eight waves
+    if (!direct) {
+      if (olo != nullptr) TERRA_LAUNCH_FWD(false, true, 8, false);
+      else TERRA_LAUNCH_FWD(false, false, 8, false);
+    } else if (olo != nullptr) {      // windows of more than 256 tokens: four or eight waves
       if (quad && nw == 8) TERRA_LAUNCH_FWD(true, true, 8);
       else if (quad) TERRA_LAUNCH_FWD(true, true, 4);
       else if (nw == 8) TERRA_LAUNCH_FWD(false, true, 8);
@@ -2177,7 +2186,7 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
   if constexpr (sizeof(T) == 2 && HD == 128) {
     const int nb = (g.wh * g.ww + 31) / 32, nqc = (nb + 7) / 8;
     const size_t lds = dq16_lds<HD>(g);
-    dq16 = g.wh * g.ww > 512 && 8 * nb >= 7 * 8 * nqc && 2 * g.B * g.nwin * g.heads * nqc >= g.cus &&
+    dq16 = direct_ok(k, v) && g.wh * g.ww > 512 && 8 * nb >= 7 * 8 * nqc && 2 * g.B * g.nwin * g.heads * nqc >= g.cus &&
            lds <= 160 * 1024;
     if (dq16) {
 #define TERRA_LAUNCH_DQ(QD)                                                                          \
@@ -2220,12 +2229,13 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
   if constexpr (sizeof(T) == 2) {
     const int nb = (g.wh * g.ww + 31) / 32;
     const size_t lds_kv = dkdv16_lds<HD>(g);
-    const int nw = waves16<HD>(g, lds_kv);
+    const bool direct = direct_ok(q, dout);
+    const int nw = direct ? waves16<HD>(g, lds_kv) : 8;
     const int nkc = (nb + nw - 1) / nw;
     const int unit = xcd_unit<HD>(g, nkc);
     const int grid = unit_grid(g.B * g.nwin * g.heads * nkc, unit);
-#define TERRA_LAUNCH_KV(QD, NW_)                                                                    \
-  hipLaunchKernelGGL((bwd_dkdv16_kernel<T, HD, NHWC, QD, NW_>), dim3(grid), dim3(NW_ * 64), lds_kv, st, \
+#define TERRA_LAUNCH_KV(QD, NW_, ...)                                                               \
+  hipLaunchKernelGGL((bwd_dkdv16_kernel<T, HD, NHWC, QD, NW_, ##__VA_ARGS__>), dim3(grid), dim3(NW_ * 64), lds_kv, st, \
                      (const T*)q, (const T*)k, (const T*)v, (const T*)dout, lse, D, table,            \
                      (T*)dk, (T*)dv, g, nkc, unit, sl2, scale)
 #define TERRA_LAUNCH_KVN(NW_)             \
@@ -2233,7 +2243,8 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
     if (quad) TERRA_LAUNCH_KV(true, NW_); \
     else TERRA_LAUNCH_KV(false, NW_);     \
   } while (0)
-    if (nw == 4) TERRA_LAUNCH_KVN(4);
+    if (!direct) TERRA_LAUNCH_KV(false, 8, false);
+    else if (nw == 4) TERRA_LAUNCH_KVN(4);
     else if (nw == 2) TERRA_LAUNCH_KVN(2);
     else if (nw == 8) TERRA_LAUNCH_KVN(8);
     else if constexpr (HD == 32) TERRA_LAUNCH_KVN(3);

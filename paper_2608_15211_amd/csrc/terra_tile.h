@@ -71,11 +71,14 @@ template <int HD>
 __device__ inline uint32_t tile_pad_row(uint32_t ibytes) { return min(ibytes, 0u - 4u * HD); }
 
 // Moves rows r0 .. r0 + 63 of one tensor into a tile: NT threads, each
-// 16-byte chunk written by the load itself.  tokb[r] is the byte offset of
-// token r's channels from the resource's base (tile_pad_row from the window's
-// end to a multiple of 64 rows).
-template <int HD, int NT>
-__device__ inline void tile_load_direct(const i32x4& rs, char* tile, const uint32_t* tokb, int r0) {
+// 16-byte chunk written by the load itself (DIRECT) or, for tensors that do
+// not start at a multiple of 16 bytes, loaded into registers and stored: what
+// a direct-to-LDS load does with an address that is not a multiple of its
+// element size is not documented.  tokb[r] is the byte offset of token r's
+// channels from the resource's base (tile_pad_row from the window's end to a
+// multiple of 64 rows).
+template <int HD, int NT, bool DIRECT>
+__device__ inline void tile_load(const i32x4& rs, char* tile, const uint32_t* tokb, int r0) {
   constexpr int kChunks = 64 * HD / 8;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
@@ -84,8 +87,16 @@ __device__ inline void tile_load_direct(const i32x4& rs, char* tile, const uint3
     const int q = u * NT + threadIdx.x;
     const int row = q / (HD / 8), p = q % (HD / 8);
     const uint32_t voff = tokb[r0 + row] + 16u * (uint32_t)(p ^ tile_swz<HD>(row));
-    char* dst = tile + 16 * (u * NT + wave * 64);
-    buffer_load_lds16(rs, dst, (int)voff);
+    if constexpr (DIRECT) {
+      buffer_load_lds16(rs, tile + 16 * (u * NT + wave * 64), (int)voff);
+    } else {
+      typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+      typedef u32x4 u32x4_2 __attribute__((aligned(2)));
+      const char* base = reinterpret_cast<const char*>((uint64_t)(uint32_t)rs[1] << 32 | (uint32_t)rs[0]);
+      u32x4 x = {};
+      if (voff < (uint32_t)rs[2]) x = *reinterpret_cast<const u32x4_2*>(base + voff);
+      *reinterpret_cast<u32x4*>(tile + 16 * q) = x;
+    }
   }
 }
 

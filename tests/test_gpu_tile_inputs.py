@@ -1,6 +1,8 @@
 """What the 16-bit attention kernels' staged tiles must not change: an
 infinity in a window's last token reaches the outputs it belongs to as an
-infinity, whatever the rows that pad the window's last tile hold."""
+infinity, whatever the rows that pad the window's last tile hold, and tensors
+that start at any element of a larger buffer give the results of aligned
+ones."""
 
 import pytest
 
@@ -56,3 +58,42 @@ def test_infinity_in_the_last_token(heads, hd, win, grid, dtype):
         want = finite.clone()
         want[0, rows[:, None].cuda(), cols.cuda(), c] = float("inf")    # every weight of the window is positive
         assert bool((got == want).all()), name
+
+
+# (heads, hd, window, grid)
+VIEWS = [
+    (2, 32, (3, 5), (9, 17)),
+    (3, 32, (12, 12), (24, 31)),
+    (2, 64, (17, 16), (34, 37)),
+    (2, 128, (8, 8), (16, 19)),
+    (1, 128, (23, 29), (25, 33)),
+]
+
+
+@pytest.mark.parametrize("layout", ["nhwc", "win"])
+@pytest.mark.parametrize("start", [1, 2, 4])
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("heads,hd,win,grid", VIEWS)
+def test_views_at_any_element(heads, hd, win, grid, dtype, start, layout):
+    cfg, x, table = _inputs(dtype, heads, hd, win, grid)
+    fwd, bwd = (P.terra_winattn_fwd, P.terra_winattn_bwd) if layout == "win" else \
+        (P.terra_winattn_fwd_nhwc, P.terra_winattn_bwd_nhwc)
+    if layout == "win":
+        x = {n: P.terra_window_route(t, cfg) for n, t in x.items()}
+    like = x["q"]
+    use_lo = P.terra_winattn_uses_o_lo(cfg, like.dtype)
+
+    def results(new):
+        def view(t=None):
+            v = new(like.numel()).view(like.shape)
+            return v if t is None else v.copy_(t)
+        q, k, v, dout = (view(x[n]) for n in ("q", "k", "v", "dout"))
+        lo = view() if use_lo else None
+        o, lse = fwd(q, k, v, table, cfg, out=view(), o_lo=lo)
+        grads = bwd(q, k, v, o, dout, lse, table, cfg, out=(view(), view(), view(), torch.empty_like(table)), o_lo=lo)
+        return (o, lse) + tuple(grads) + ((lo,) if use_lo else ())
+
+    base = results(lambda n: torch.empty(n, dtype=like.dtype, device="cuda"))
+    moved = results(lambda n: torch.empty(n + start, dtype=like.dtype, device="cuda")[start:])
+    for i, (a, b) in enumerate(zip(base, moved)):
+        assert torch.equal(a, b), i
