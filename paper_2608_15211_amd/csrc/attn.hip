@@ -1153,8 +1153,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
   constexpr int kTB = 64 * HD * 2;                    // bytes of one tile
   const int nP = (g.wh * g.ww + 63) & ~63;
   extern __shared__ __align__(16) char smem[];
-  char* tiles = smem;                                 // {K, V} x 2 buffers
-  uint32_t* tokb = reinterpret_cast<uint32_t*>(smem + 4 * kTB);   // [nP] byte offsets
+  char* tiles = smem;                                 // {K, V} x tile_pairs
+  uint32_t* tokb = reinterpret_cast<uint32_t*>(smem + tile_pairs(nP) * 2 * kTB);   // [nP] byte offsets
   int* knb = reinterpret_cast<int*>(tokb + nP);       // [nP] 4 x bias offset
   int* klabs = knb + nP;                              // [nP] label
   float* tab = reinterpret_cast<float*>(klabs + nP);  // [nbins+4], reversed
@@ -1744,8 +1744,8 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
   constexpr int kTB = 64 * HD * 2;                    // bytes of one tile
   const int nP = (g.wh * g.ww + 63) & ~63;
   extern __shared__ __align__(16) char smem[];
-  char* tiles = smem;                                 // {Q, dO} x 2 buffers
-  uint32_t* tokb = reinterpret_cast<uint32_t*>(smem + 4 * kTB);   // [nP] byte offsets
+  char* tiles = smem;                                 // {Q, dO} x tile_pairs
+  uint32_t* tokb = reinterpret_cast<uint32_t*>(smem + tile_pairs(nP) * 2 * kTB);   // [nP] byte offsets
   int* qnb = reinterpret_cast<int*>(tokb + nP);       // [nP] 4 x bias offset
   int* qlab = qnb + nP;                               // [nP] label
   float* ql = reinterpret_cast<float*>(qlab + nP);     // [nP] log-sum-exp, log2 units
@@ -2033,14 +2033,14 @@ static size_t dq16_lds(const Geo& g) {
   const size_t nP = (g.wh * g.ww + 63) & ~63;
   return 4 * 64 * HD * 2 + 7 * nP + 4 * (g.nbins + 4) + 16 * g.nbins;
 }
-// The 16-bit dK/dV kernel: two {Q, dO} tile pairs, five words per window
+// The 16-bit dK/dV kernel: one or two {Q, dO} tile pairs, five words per window
 // token, the bias table.  Never more than a workgroup has where the dQ
 // kernel's plan (whose five bias copies decide which windows are accepted)
 // fits.
 template <int HD>
 static size_t dkdv16_lds(const Geo& g) {
   const size_t nP = (g.wh * g.ww + 63) & ~63;
-  return 4 * 64 * HD * 2 + 20 * nP + 4 * (g.nbins + 4);
+  return tile_pairs((int)nP) * 2 * 64 * HD * 2 + 20 * nP + 4 * (g.nbins + 4);
 }
 
 // Per-head slices of the dQ / bias-gradient kernel.  The grid is one round
@@ -2102,7 +2102,7 @@ static hipError_t fwd_impl(const Geo& g, const void* q, const void* k, const voi
   const bool quad = quad_layout(g);
   if constexpr (sizeof(T) == 2) {
     const size_t nP = (g.wh * g.ww + 63) & ~63;
-    const size_t lds = 4 * 64 * HD * 2 + 12 * nP + 4 * (g.nbins + 4);
+    const size_t lds = tile_pairs((int)nP) * 2 * 64 * HD * 2 + 12 * nP + 4 * (g.nbins + 4);
     const bool direct = direct_ok(k, v);
     const int nw = direct ? waves16<HD>(g, lds) : 8;
     const int nqc = ((g.wh * g.ww + 31) / 32 + nw - 1) / nw;

@@ -62,6 +62,13 @@ __device__ inline typename Operand<T>::type tile_tr_op(const char* t, const Tile
   return __builtin_bit_cast(typename Operand<T>::type, o);
 }
 
+// Pairs of tile buffers of a workgroup: two, one being filled while the other
+// is read; one for windows of a single tile, whose LDS plan then fits a CU
+// four times at 128 channels instead of twice (16-token windows, 2 x 128 x 256
+// tokens of 3 heads: forward 120 -> 68 us, backward 395 ->
+// 328; 64 tokens, 256 x 540 of 8 heads, a step 1133 -> 1020).
+__device__ __host__ inline int tile_pairs(int nP) { return nP > 64 ? 2 : 1; }
+
 // Row address of a tile row past the window's n tokens: one token past the
 // image (ibytes, below 2^32), where the load reads zeros.  The row's weights
 // are zero, and zero times a token's infinity would not be.  An image that
