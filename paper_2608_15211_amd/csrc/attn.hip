@@ -1995,7 +1995,6 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
 // ---------------------------------------------------------------------------
 static inline int num_chunks(const Geo& g) { return (g.wh * g.ww + kChunk - 1) / kChunk; }
 
-
 template <typename T, int HD>
 static size_t fwd_lds(const Geo& g) {
   constexpr int kTile = tile_of<T, HD>();
@@ -2071,6 +2070,25 @@ int bwd_nslice(const Geo& g, int dt) {
                                                                : bwd_nslice_max_t<_Float16>(g);
 }
 #endif
+
+// True when a slice of the general dQ kernel, per_cu workgroups a CU, holds
+// more than 1.2 chunks of a full window: its items in the slice's order, each
+// as long as its window has key tiles (the windows of ragged edges count as
+// what they are: 21 x 31 windows on 64 x 96 tokens, 3 heads, are 183 chunks of
+// at most 256, though 16 full windows a head would be 288).
+static bool dq_past_one_round(const Geo& g, int per_cu) {
+  constexpr int kMax = 2048;
+  const int nqc = num_chunks(g), full = (g.wh * g.ww + 63) / 64;
+  const int slices = std::min(kMax, std::max(1, g.cus * per_cu / g.heads));
+  if ((int64_t)g.B * (g.H / g.wh) * (g.W / g.ww) * nqc > slices) return true;   // two full chunks in some slice
+  int tiles[kMax] = {};
+  for (int it = 0; it < g.B * g.nwin * nqc; ++it) {
+    const int w = it / nqc % g.nwin, n = win_rows(g, w / g.Mw) * win_cols(g, w % g.Mw);
+    if (it % nqc * kChunk >= n) continue;
+    if ((tiles[it % slices] += (n + 63) / 64) * 5 > 6 * full) return true;
+  }
+  return false;
+}
 
 // Waves of a 16-bit workgroup whose plan takes `lds` bytes.  Four where two
 // workgroups fit a CU's LDS, else eight (dK/dV, 1024-token windows of 128
@@ -2178,16 +2196,19 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
   };
   int nslice = 1;
   // Eight-wave dQ kernel: 128 channels, windows of more than 512 tokens that
-  // keep at least 7 of 8 waves busy, items for at least half of the CUs, and
-  // a plan that fits.  Measured against the general kernel (whole backward):
-  // 1024 tokens 1.23x at 192 items, 1.14x at 276, 1.29x at 1088, 0.78x at 64;
-  // 651 tokens 1.21x; 576 tokens (18 of 24 waves) 0.77x.
+  // keep at least 7 of 8 waves busy, a plan that fits, and work that the
+  // general kernel would not do in one round.  Measured against the general
+  // kernel (whole backward), 256 compute units: where that one has a chunk of
+  // 128 queries a unit or fewer, it is ahead (1024 tokens 0.91x, 651 tokens
+  // 0.77 to 0.85x, 768 tokens 0.92x: a chunk of 256 is the longer chain);
+  // beyond, this one (1024 tokens 1.10 to 1.28x, 651 tokens 1.00 to 1.23x, 768
+  // tokens 1.12x; 576 tokens, 18 of 24 waves, 0.77x).
   bool dq16 = false;
   if constexpr (sizeof(T) == 2 && HD == 128) {
     const int nb = (g.wh * g.ww + 31) / 32, nqc = (nb + 7) / 8;
     const size_t lds = dq16_lds<HD>(g);
-    dq16 = direct_ok(k, v) && g.wh * g.ww > 512 && 8 * nb >= 7 * 8 * nqc && 2 * g.B * g.nwin * g.heads * nqc >= g.cus &&
-           lds <= 160 * 1024;
+    dq16 = direct_ok(k, v) && g.wh * g.ww > 512 && 8 * nb >= 7 * 8 * nqc && lds <= 160 * 1024 &&
+           dq_past_one_round(g, (int)((160 * 1024) / dq_lds<T, HD>(g)));
     if (dq16) {
 #define TERRA_LAUNCH_DQ(QD)                                                                          \
   do {                                                                                               \

@@ -65,8 +65,8 @@ __device__ inline typename Operand<T>::type tile_tr_op(const char* t, const Tile
 // Pairs of tile buffers of a workgroup: two, one being filled while the other
 // is read; one for windows of a single tile, whose LDS plan then fits a CU
 // four times at 128 channels instead of twice (16-token windows, 2 x 128 x 256
-// tokens of 3 heads: forward 120 -> 68 us, backward 395 ->
-// 328; 64 tokens, 256 x 540 of 8 heads, a step 1133 -> 1020).
+// tokens of 3 heads: forward 120 -> 68 us, backward 395 -> 328; 64 tokens,
+// 256 x 540 of 8 heads, a step 1133 -> 1020).
 __device__ __host__ inline int tile_pairs(int nP) { return nP > 64 ? 2 : 1; }
 
 // Row address of a tile row past the window's n tokens: one token past the
