@@ -2091,8 +2091,11 @@ static bool dq_past_one_round(const Geo& g, int per_cu) {
 }
 
 // Waves of a 16-bit workgroup whose plan takes `lds` bytes.  Four where two
-// workgroups fit a CU's LDS, else eight (dK/dV, 1024-token windows of 128
-// channels: 2267 us with four, 1381 with eight).  Windows of up to 256 tokens
+// workgroups fit a CU's LDS, or where those of four leave no CU a second one
+// (1024 tokens of 128 channels, 128 workgroups of four against 64 of eight:
+// forward 48 us against 56, backward 147.5 against 150.5; 288 against 144:
+// 87 against 58 and 223 against 172), else eight (dK/dV, 1024-token windows of
+// 128 channels: 2267 us with four, 1381 with eight).  Windows of up to 256 tokens
 // take fewer waves where that leaves fewer of them idle (at 128 channels only
 // up to 64 tokens: LDS holds two workgroups a CU whatever their waves; 144
 // tokens forward 23 us with two waves, 19 with four); longer ones keep
@@ -2101,7 +2104,7 @@ static bool dq_past_one_round(const Geo& g, int per_cu) {
 template <int HD>
 static int waves16(const Geo& g, size_t lds) {
   const int nb = (g.wh * g.ww + 31) / 32;
-  int nw = 2 * lds <= 160 * 1024 ? 4 : 8;
+  int nw = 2 * lds <= 160 * 1024 || g.B * g.nwin * g.heads * ((nb + 3) / 4) <= g.cus ? 4 : 8;
   if (nb <= 8)
     for (int c : {4, 3, 2})
       if (c < nw && (HD == 32 || c != 3) && (HD < 128 || nb <= 2) && (nb + c - 1) / c * c < (nb + nw - 1) / nw * nw) nw = c;
