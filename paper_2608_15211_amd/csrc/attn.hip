@@ -92,24 +92,10 @@ __device__ __host__ constexpr int tr_row(int e) { return e * (tile_of<T, HD>() +
 template <typename T, int HD>
 __device__ __host__ constexpr int tr_size() { return tr_row<T, HD>(HD); }
 
-// 16-bit V tiles stay row-major and give their transposed operands through
-// the LDS transpose read: in each 16-lane group G of that read, lane i
-// receives element i % 4 of the 8 bytes addressed by lane 16 G + 4 x + i / 4,
-// x = 0..3.  Row stride 16 mod 64 dwords, so the 4 rows x 64 bytes of two
-// groups fall in distinct LDS banks.
-template <int HD> constexpr int tr16_stride() { return HD == 32 ? 32 : HD == 64 ? 96 : 160; }
-template <typename T, int HD>
-__device__ __host__ constexpr int vtile_size() {
-  return sizeof(T) == 2 ? tile_of<T, HD>() * tr16_stride<HD>() : tr_size<T, HD>();
-}
 // Transposed copy of a tile: needed for fp32 only (16-bit tiles are read
 // transposed straight from their row-major copy).
 template <typename T, int HD>
 __device__ __host__ constexpr int ttile_size() { return sizeof(T) == 2 ? 0 : tr_size<T, HD>(); }
-
-// Slot s (0..7) of lane half h inside a 16-deep contraction chunk, when the
-// operand comes from 32x32 result registers 8c..8c+7: row acc_row(s, h).
-__device__ inline int perm_slot(int s, int h) { return 8 * (s / 4) + 4 * h + (s % 4); }
 
 template <typename T>
 __device__ inline typename Operand<T>::type load_op_global(const T* p) {
@@ -194,18 +180,6 @@ __device__ inline void tile_load_tt(TileRegs<T, HD>& t, const T* __restrict__ sr
       if (row < n)
         t.r[u] = *reinterpret_cast<const uint4*>(src + tt[row] + hoff + ch * (16 / (int)sizeof(T)));
     }
-  }
-}
-
-// Row-major store of a staged tile with row stride RS elements.
-template <typename T, int HD, int RS>
-__device__ inline void tile_store_rows(const TileRegs<T, HD>& t, T* lds) {
-  constexpr int kCpr = TileRegs<T, HD>::kCpr;
-#pragma unroll
-  for (int u = 0; u < TileRegs<T, HD>::kPer; ++u) {
-    const int idx = threadIdx.x + u * kThreads;
-    const int rr = idx / kCpr, ch = idx % kCpr;
-    *reinterpret_cast<uint4*>(lds + rr * RS + ch * (16 / (int)sizeof(T))) = t.r[u];
   }
 }
 
@@ -312,7 +286,7 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(
   extern __shared__ __align__(16) char smem[];
   T* kt = reinterpret_cast<T*>(smem);                          // [kTile][HD+kPad]
   T* vt = kt + kTile * (HD + kPad);                            // V^T
-  int* kinfo = reinterpret_cast<int*>(vt + vtile_size<T, HD>());
+  int* kinfo = reinterpret_cast<int*>(vt + tr_size<T, HD>());
   float* tab = reinterpret_cast<float*>(kinfo + kTile);        // [nbins+4], reversed
   uint32_t* tt = reinterpret_cast<uint32_t*>(tab + g.nbins + 4);   // [wh*ww] token offsets
 
@@ -1344,14 +1318,14 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
 // with tables of the whole window.  576 tokens of 64 channels 2096 -> 1930 us
 // on the 256 x 540 grid, but 0.71 to 0.95x on smaller or odd-width ones.)
 // ---------------------------------------------------------------------------
-template <typename T, int HD, bool NHWC, bool QUAD>
+template <typename T, bool NHWC, bool QUAD>
 __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const T* __restrict__ o, const T* __restrict__ olo,
     const T* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ D,
     const float* __restrict__ table, T* __restrict__ dq, float* __restrict__ partial,
     Geo g, int nqc, int nslice, float scale_log2, float scale) {
-  constexpr int NW = 8, NT = NW * 64, kCopies = 4;
+  constexpr int HD = 128, NW = 8, NT = NW * 64, kCopies = 4;
   constexpr int kTB = 64 * HD * 2;                    // bytes of one tile
   const int nP = (g.wh * g.ww + 63) & ~63;
   extern __shared__ __align__(16) char smem[];
@@ -1475,7 +1449,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
           if (!wactive) continue;
           const char* kt = tiles + (vis & 1) * 2 * kTB;
           const char* vr = kt + kTB;
-          if constexpr (HD == 128) ta.opaque();
+          ta.opaque();
 #pragma unroll
           for (int kb = 0; kb < 2; ++kb) {
             f32x16 s = bias(64 * tix, kb);
@@ -1507,36 +1481,24 @@ __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
           const int t0 = 64 * tix;
           const char* kt = tiles + vbuf * 2 * kTB;
           const char* vr = kt + kTB;
-          if constexpr (HD == 128) ta.opaque();
-          // Head dim 64: the S and dP products of both key blocks first, so
-          // that one block's exp runs while the other's are on the matrix cores
-          constexpr int kG = HD == 64 ? 2 : 1;
+          ta.opaque();
 #pragma unroll
-          for (int k2 = 0; k2 < 2; k2 += kG) {
-            f32x16 sb[kG];
+          for (int kb = 0; kb < 2; ++kb) {
+            f32x16 s = bias(t0, kb);
 #pragma unroll
-            for (int u = 0; u < kG; ++u) {
-              const int kb = k2 + u;
-              sb[u] = bias(t0, kb);
+            for (int r = 0; r < 16; ++r) dsb[kb][r] = -Dq;      // dP - D straight from the product
 #pragma unroll
-              for (int r = 0; r < 16; ++r) dsb[kb][r] = -Dq;      // dP - D straight from the product
-#pragma unroll
-              for (int c = 0; c < HD / 16; ++c) {
-                mma16(sb[u], tile_row_op<T, HD>(kt, ta, 32 * kb, c), qop[c]);
-                mma16(dsb[kb], tile_row_op<T, HD>(vr, ta, 32 * kb, c), dop[c]);
-              }
+            for (int c = 0; c < HD / 16; ++c) {
+              mma16(s, tile_row_op<T, HD>(kt, ta, 32 * kb, c), qop[c]);
+              mma16(dsb[kb], tile_row_op<T, HD>(vr, ta, 32 * kb, c), dop[c]);
             }
 #pragma unroll
-            for (int u = 0; u < kG; ++u) {
-              const int kb = k2 + u;
+            for (int r = 0; r < 16; ++r) dsb[kb][r] *= __builtin_amdgcn_exp2f(s[r] * scale_log2 - lse2);
 #pragma unroll
-              for (int r = 0; r < 16; ++r) dsb[kb][r] *= __builtin_amdgcn_exp2f(sb[u][r] * scale_log2 - lse2);
+            for (int c = 0; c < 2; ++c) {
+              const auto dop_ = pack8<T>(dsb[kb], 8 * c);
 #pragma unroll
-              for (int c = 0; c < 2; ++c) {
-                const auto dop_ = pack8<T>(dsb[kb], 8 * c);
-#pragma unroll
-                for (int eb = 0; eb < HD / 32; ++eb) mma16(dqacc[eb], tile_tr_op<T, HD>(kt, ta, kb, c, eb), dop_);
-              }
+              for (int eb = 0; eb < HD / 32; ++eb) mma16(dqacc[eb], tile_tr_op<T, HD>(kt, ta, kb, c, eb), dop_);
             }
           }
         };
@@ -1998,7 +1960,7 @@ static inline int num_chunks(const Geo& g) { return (g.wh * g.ww + kChunk - 1) /
 template <typename T, int HD>
 static size_t fwd_lds(const Geo& g) {
   constexpr int kTile = tile_of<T, HD>();
-  return sizeof(T) * (kTile * (HD + kPad) + vtile_size<T, HD>()) + 4 * kTile + 4 * (g.nbins + 4) +
+  return sizeof(T) * (kTile * (HD + kPad) + tr_size<T, HD>()) + 4 * kTile + 4 * (g.nbins + 4) +
          4 * g.wh * g.ww;
 }
 // Key tiles the dQ kernel keeps resident for a whole item: every tile of the
@@ -2215,8 +2177,8 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
     if (dq16) {
 #define TERRA_LAUNCH_DQ(QD)                                                                          \
   do {                                                                                               \
-    nslice = slices(reinterpret_cast<const void*>(&bwd_dq16_kernel<T, HD, NHWC, QD>), 512, lds, nqc);  \
-    hipLaunchKernelGGL((bwd_dq16_kernel<T, HD, NHWC, QD>), dim3(grid8(g.heads * nslice)), dim3(512),   \
+    nslice = slices(reinterpret_cast<const void*>(&bwd_dq16_kernel<T, NHWC, QD>), 512, lds, nqc);  \
+    hipLaunchKernelGGL((bwd_dq16_kernel<T, NHWC, QD>), dim3(grid8(g.heads * nslice)), dim3(512),   \
                        lds, st, (const T*)q, (const T*)k, (const T*)v, (const T*)o, (const T*)olo,     \
                        (const T*)dout, lse, D, table, (T*)dq, partial, g, nqc, nslice, sl2, scale);    \
   } while (0)
