@@ -421,6 +421,176 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(
   if (half == 0) lse[wt.lse_at(g, h, qi)] = (m_run + __log2f(l_run)) * kLn2;
 }
 
+// What the bias bins' fold (add_bins) needs to know of a lane: runs are lanes
+// of one 32-lane half holding consecutive queries of one window row.
+struct BinFold {
+  bool on;               // every window width is a multiple of 4 (uniform)
+  int run, rest;         // lanes before and after this one in its run
+  float fnext;           // 1: lane l+1 is in the run, and this lane may pass to it
+  float fkeep;           // 1: one of the run's first three
+  __device__ BinFold(const Geo& g, int j, int cols, int qi, int col)
+      : on((g.ww % 4 == 0) && (g.W % g.ww) % 4 == 0) {
+    const int cq = qi - fast_div(qi, cols, win_rcols(g, j)) * cols;
+    run = cq < col ? cq : col;
+    rest = (cols - 1 - cq) < (31 - col) ? (cols - 1 - cq) : (31 - col);
+    fnext = rest > 0 ? 1.0f : 0.0f;
+    fkeep = run < 3 ? 1.0f : 0.0f;
+  }
+};
+
+// Bias bins of one key tile: a wave adds dsb into the copy behind qbins (bin
+// of (this lane's query, key kk): qbins - knb[kk] in bytes), and the two lane
+// halves add with separate instructions.  Within one half, lanes hold distinct
+// queries of the same key, hence distinct bins, so the additions are plain
+// read-modify-writes (an LDS float atomic costs about three clocks per lane,
+// some 170 times a store) and every bin receives them in program order; lanes
+// with nothing to add (padding queries, excluded pairs) stay out.  When every
+// window width is a multiple of 4, registers 4g..4g+3 hold four consecutive
+// keys k..k+3 of one window row and (q, k+x), (q+1, k+x+1) share a bin.
+// Within a run of consecutive lanes holding consecutive queries of one window
+// row, a DPP chain towards lower lanes folds each group into one value (bin of
+// (q, k)); the pairs it cannot reach (fewer than x lanes before q in the run)
+// move towards higher lanes into the run's first three lanes (bin of
+// (q', k+3)), and the few that would leave a run shorter than three lanes are
+// added on their own.
+// full: every query of the wave and every key of the tile is a window token.
+template <int KB, typename NB>
+__device__ __forceinline__ void add_bins(const f32x16 (&dsb)[KB], char* qbins, const NB* knb, const BinFold& bf,
+                                         bool full, int half) {
+  auto bin = [&](int kk) -> float& { return *reinterpret_cast<float*>(qbins - knb[kk]); };
+  if (bf.on) {
+    float fa[KB][4], fb[KB][4];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const float d0 = dsb[kb][4 * g4], d1 = dsb[kb][4 * g4 + 1];
+        const float d2 = dsb[kb][4 * g4 + 2], d3 = dsb[kb][4 * g4 + 3];
+        float f = d3;
+        f = d2 + bf.fnext * dpp_lane<kDppNext>(f);
+        f = d1 + bf.fnext * dpp_lane<kDppNext>(f);
+        fa[kb][g4] = d0 + bf.fnext * dpp_lane<kDppNext>(f);
+        const float p1 = dpp_lane<kDppWavePrev>(d2 * bf.fnext);
+        const float p2 = dpp_lane<kDppWavePrev>(dpp_lane<kDppWavePrev>(d1 * bf.fnext) * bf.fnext);
+        fb[kb][g4] = bf.fkeep * (d3 + p1 + p2);
+      }
+    // One update of this lane: the folded pair sums of key block kb,
+    // group g4 (fa at (q, k), fb at (q, k+3)).
+    auto upd = [&](int kb, int g4, float va, float vb) {
+      const int kk = kb * 32 + 8 * g4 + 4 * half;
+      if (va != 0.0f) bin(kk) += va;
+      if (vb != 0.0f) bin(kk + 3) += vb;
+    };
+    if constexpr (KB == 2) {
+      // Both halves update with one instruction when their keys are at
+      // least 32 tokens apart: the 32 queries of a half are consecutive
+      // tokens, so (q, k) and (q', k') share a bin only if |k - k'| =
+      // |q - q'| < 32.  Half 0 takes block 0 group t while half 1 takes
+      // block 1 group t (keys 32 + 4 or more apart), then half 0 takes
+      // block 1 group t while half 1 takes block 0 group t - 1 (36 or
+      // more), and the two updates left over go alone.
+      if (full) {
+        // Every query of the wave and every key of the tile is a window
+        // token: the updates need no guard (adding 0 to a bin that no
+        // other lane of the instruction touches changes nothing), and
+        // the key words are read before the first update.  Word index of
+        // this lane's group: 36 half + 8t in the first round, 32 - 36 half
+        // + 8t in the second, 32 (half 0) or 28 (half 1) left over.
+        float* w1[4][2];
+        float* w2[3][2];
+        float* wl[2];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int kk = 36 * half + 8 * t;
+          w1[t][0] = &bin(kk);
+          w1[t][1] = &bin(kk + 3);
+        }
+#pragma unroll
+        for (int t = 1; t < 4; ++t) {
+          const int kk = 32 - 36 * half + 8 * t;
+          w2[t - 1][0] = &bin(kk);
+          w2[t - 1][1] = &bin(kk + 3);
+        }
+        {
+          const int kk = half ? 28 : 32;
+          wl[0] = &bin(kk);
+          wl[1] = &bin(kk + 3);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          *w1[t][0] += half ? fa[1][t] : fa[0][t];
+          *w1[t][1] += half ? fb[1][t] : fb[0][t];
+        }
+#pragma unroll
+        for (int t = 1; t < 4; ++t) {
+          *w2[t - 1][0] += half ? fa[0][t - 1] : fa[1][t];
+          *w2[t - 1][1] += half ? fb[0][t - 1] : fb[1][t];
+        }
+        if (half == 0) { *wl[0] += fa[1][0]; *wl[1] += fb[1][0]; }
+        __builtin_amdgcn_wave_barrier();
+        if (half == 1) { *wl[0] += fa[0][3]; *wl[1] += fb[0][3]; }
+        __builtin_amdgcn_wave_barrier();
+      } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int kb = half, gt = t;
+          upd(kb, gt, half ? fa[1][t] : fa[0][t], half ? fb[1][t] : fb[0][t]);
+        }
+#pragma unroll
+        for (int t = 1; t < 4; ++t) {
+          const int kb = 1 - half, gt = t - half;
+          upd(kb, gt, half ? fa[0][t - 1] : fa[1][t], half ? fb[0][t - 1] : fb[1][t]);
+        }
+        if (half == 0) upd(1, 0, fa[1][0], fb[1][0]);
+        __builtin_amdgcn_wave_barrier();
+        if (half == 1) upd(0, 3, fa[0][3], fb[0][3]);
+        __builtin_amdgcn_wave_barrier();
+      }
+    } else {
+#pragma unroll 1
+      for (int hh = 0; hh < 2; ++hh) {
+        if (half == hh) {
+#pragma unroll
+          for (int g4 = 0; g4 < 4; ++g4) upd(0, g4, fa[0][g4], fb[0][g4]);
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    // pairs of runs shorter than three lanes that the fold left out
+    if (__builtin_amdgcn_ballot_w64((bf.run < 1 && bf.rest < 2) || (bf.run < 2 && bf.rest < 1)) != 0) {
+#pragma unroll 1
+      for (int hh = 0; hh < 2; ++hh) {
+        if (half == hh) {
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+              const int kk = kb * 32 + 8 * g4 + 4 * half;
+#pragma unroll
+              for (int x = 1; x < 3; ++x)
+                if (bf.run < x && bf.rest < 3 - x && dsb[kb][4 * g4 + x] != 0.0f)
+                  bin(kk + x) += dsb[kb][4 * g4 + x];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+  } else {
+#pragma unroll 1
+    for (int hh = 0; hh < 2; ++hh) {
+      if (half == hh) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            if (dsb[kb][r] != 0.0f) bin(kb * 32 + acc_row(r, half)) += dsb[kb][r];
+          }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Backward, step 1: D, dQ and the bias-table partials.  One head per
 // workgroup; the workgroup walks items (image, window, query chunk)
@@ -602,15 +772,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_kernel(
     if (qvalid && half == 0) D[lidx] = Dq;
 
     // main sweep: dS, dQ, bias bins
-    const bool fold = (g.ww % 4 == 0) && (g.W % g.ww) % 4 == 0;   // uniform
-    const int cq = qi - fast_div(qi, cols, win_rcols(g, j)) * cols;
-    // runs: lanes of one 32-lane half holding consecutive queries of one
-    // window row; run = lanes before this one in its run, rest = lanes after
-    const int run = cq < col ? cq : col;
-    const int rest = (cols - 1 - cq) < (31 - col) ? (cols - 1 - cq) : (31 - col);
-    const float fnext = rest > 0 ? 1.0f : 0.0f;          // lane l+1 is in the run
-    const float fsend = fnext;                           // this lane may pass to l+1
-    const float fkeep = run < 3 ? 1.0f : 0.0f;           // one of the run's first three
+    const BinFold bf(g, j, cols, qi, col);
     f32x16 dqacc[HD / 32];
 #pragma unroll
     for (int eb = 0; eb < HD / 32; ++eb) dqacc[eb] = f32x16{};
@@ -717,156 +879,8 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_kernel(
           }
         }
       }
-      // Bias bins: each wave adds into its own copy, and the two lane halves
-      // add with separate instructions.  Within one half, lanes hold distinct
-      // queries of the same key, hence distinct bins, so the additions are
-      // plain read-modify-writes (an LDS float atomic costs about three
-      // clocks per lane, some 170 times a store) and every bin receives them
-      // in program order; lanes with nothing to add (padding queries,
-      // excluded pairs) stay out.  When every window width is a
-      // multiple of 4, registers 4g..4g+3 hold four consecutive keys k..k+3
-      // of one window row and (q, k+x), (q+1, k+x+1) share a bin.  Within a
-      // run of consecutive lanes holding consecutive queries of one window
-      // row, a DPP chain towards lower lanes folds each group into one value
-      // (bin of (q, k)); the pairs it cannot reach (fewer than x lanes
-      // before q in the run) move towards higher lanes into the run's first
-      // three lanes (bin of (q', k+3)), and the few that would leave a run
-      // shorter than three lanes are added on their own.
-      float* mybins = dtab + wave * g.nbins;
-      // bin of (this lane's query, key kk): qbins - knb[kk] in bytes
-      char* qbins = reinterpret_cast<char*>(mybins + qoff);
-      auto bin = [&](int kk) -> float& { return *reinterpret_cast<float*>(qbins - knb[kk]); };
-      if (fold) {
-        float fa[kTile / 32][4], fb[kTile / 32][4];
-#pragma unroll
-        for (int kb = 0; kb < kTile / 32; ++kb)
-#pragma unroll
-          for (int g4 = 0; g4 < 4; ++g4) {
-            const float d0 = dsb[kb][4 * g4], d1 = dsb[kb][4 * g4 + 1];
-            const float d2 = dsb[kb][4 * g4 + 2], d3 = dsb[kb][4 * g4 + 3];
-            float f = d3;
-            f = d2 + fnext * dpp_lane<kDppNext>(f);
-            f = d1 + fnext * dpp_lane<kDppNext>(f);
-            fa[kb][g4] = d0 + fnext * dpp_lane<kDppNext>(f);
-            const float p1 = dpp_lane<kDppWavePrev>(d2 * fsend);
-            const float p2 = dpp_lane<kDppWavePrev>(dpp_lane<kDppWavePrev>(d1 * fsend) * fsend);
-            fb[kb][g4] = fkeep * (d3 + p1 + p2);
-          }
-        // One update of this lane: the folded pair sums of key block kb,
-        // group g4 (fa at (q, k), fb at (q, k+3)).
-        auto upd = [&](int kb, int g4, float va, float vb) {
-          const int kk = kb * 32 + 8 * g4 + 4 * half;
-          if (va != 0.0f) bin(kk) += va;
-          if (vb != 0.0f) bin(kk + 3) += vb;
-        };
-        if constexpr (kTile == 64) {
-          // Both halves update with one instruction when their keys are at
-          // least 32 tokens apart: the 32 queries of a half are consecutive
-          // tokens, so (q, k) and (q', k') share a bin only if |k - k'| =
-          // |q - q'| < 32.  Half 0 takes block 0 group t while half 1 takes
-          // block 1 group t (keys 32 + 4 or more apart), then half 0 takes
-          // block 1 group t while half 1 takes block 0 group t - 1 (36 or
-          // more), and the two updates left over go alone.
-          if (q0 + wave * kWaveQ + kWaveQ <= n && k0 + kTile <= n) {
-            // Every query of the wave and every key of the tile is a window
-            // token: the updates need no guard (adding 0 to a bin that no
-            // other lane of the instruction touches changes nothing), and
-            // the key words are read before the first update.  Word index of
-            // this lane's group: 36 half + 8t in the first round, 32 - 36 half
-            // + 8t in the second, 32 (half 0) or 28 (half 1) left over.
-            float* w1[4][2];
-            float* w2[3][2];
-            float* wl[2];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              const int kk = 36 * half + 8 * t;
-              w1[t][0] = &bin(kk);
-              w1[t][1] = &bin(kk + 3);
-            }
-#pragma unroll
-            for (int t = 1; t < 4; ++t) {
-              const int kk = 32 - 36 * half + 8 * t;
-              w2[t - 1][0] = &bin(kk);
-              w2[t - 1][1] = &bin(kk + 3);
-            }
-            {
-              const int kk = half ? 28 : 32;
-              wl[0] = &bin(kk);
-              wl[1] = &bin(kk + 3);
-            }
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              *w1[t][0] += half ? fa[1][t] : fa[0][t];
-              *w1[t][1] += half ? fb[1][t] : fb[0][t];
-            }
-#pragma unroll
-            for (int t = 1; t < 4; ++t) {
-              *w2[t - 1][0] += half ? fa[0][t - 1] : fa[1][t];
-              *w2[t - 1][1] += half ? fb[0][t - 1] : fb[1][t];
-            }
-            if (half == 0) { *wl[0] += fa[1][0]; *wl[1] += fb[1][0]; }
-            __builtin_amdgcn_wave_barrier();
-            if (half == 1) { *wl[0] += fa[0][3]; *wl[1] += fb[0][3]; }
-            __builtin_amdgcn_wave_barrier();
-          } else {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              const int kb = half, gt = t;
-              upd(kb, gt, half ? fa[1][t] : fa[0][t], half ? fb[1][t] : fb[0][t]);
-            }
-#pragma unroll
-            for (int t = 1; t < 4; ++t) {
-              const int kb = 1 - half, gt = t - half;
-              upd(kb, gt, half ? fa[0][t - 1] : fa[1][t], half ? fb[0][t - 1] : fb[1][t]);
-            }
-            if (half == 0) upd(1, 0, fa[1][0], fb[1][0]);
-            __builtin_amdgcn_wave_barrier();
-            if (half == 1) upd(0, 3, fa[0][3], fb[0][3]);
-            __builtin_amdgcn_wave_barrier();
-          }
-        } else {
-#pragma unroll 1
-          for (int hh = 0; hh < 2; ++hh) {
-            if (half == hh) {
-#pragma unroll
-              for (int g4 = 0; g4 < 4; ++g4) upd(0, g4, fa[0][g4], fb[0][g4]);
-            }
-            __builtin_amdgcn_wave_barrier();
-          }
-        }
-        // pairs of runs shorter than three lanes that the fold left out
-        if (__builtin_amdgcn_ballot_w64((run < 1 && rest < 2) || (run < 2 && rest < 1)) != 0) {
-#pragma unroll 1
-          for (int hh = 0; hh < 2; ++hh) {
-            if (half == hh) {
-#pragma unroll
-              for (int kb = 0; kb < kTile / 32; ++kb)
-#pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4) {
-                  const int kk = kb * 32 + 8 * g4 + 4 * half;
-#pragma unroll
-                  for (int x = 1; x < 3; ++x)
-                    if (run < x && rest < 3 - x && dsb[kb][4 * g4 + x] != 0.0f)
-                      bin(kk + x) += dsb[kb][4 * g4 + x];
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-          }
-        }
-      } else {
-#pragma unroll 1
-        for (int hh = 0; hh < 2; ++hh) {
-          if (half == hh) {
-#pragma unroll
-            for (int kb = 0; kb < kTile / 32; ++kb)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) {
-                if (dsb[kb][r] != 0.0f) bin(kb * 32 + acc_row(r, half)) += dsb[kb][r];
-              }
-          }
-          __builtin_amdgcn_wave_barrier();
-        }
-      }
+      add_bins(dsb, reinterpret_cast<char*>(dtab + wave * g.nbins + qoff), knb, bf,
+               q0 + wave * kWaveQ + kWaveQ <= n && k0 + kTile <= n, half);
     }
     if (qvalid) {
       T* row = dq + wt.tok(g, qi) * g.C + hoff;
@@ -1349,7 +1363,6 @@ __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
   const bool second = wave >= 4;
   const int nitems = g.B * g.nwin * nqc;
   TileAddr<HD> ta(lane);
-  const bool fold = (g.ww % 4 == 0) && (g.W % g.ww) % 4 == 0;   // uniform
 
   for (int it = slice; it < nitems; it += nslice) {
     const int qc = it % nqc;
@@ -1410,14 +1423,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
         for (int x = 0; x < 8; ++x) dsum += to_float<T>(dop[c][x]) * (to_float<T>(ov[x]) + to_float<T>(lv[x]));
       }
     }
-    const int cq = qi - fast_div(qi, cols, win_rcols(g, j)) * cols;
-    // runs: lanes of one 32-lane half holding consecutive queries of one
-    // window row; run = lanes before this one in its run, rest = lanes after
-    const int run = cq < col ? cq : col;
-    const int rest = (cols - 1 - cq) < (31 - col) ? (cols - 1 - cq) : (31 - col);
-    const float fnext = rest > 0 ? 1.0f : 0.0f;          // lane l+1 is in the run
-    const float fsend = fnext;                           // this lane may pass to l+1
-    const float fkeep = run < 3 ? 1.0f : 0.0f;           // one of the run's first three
+    const BinFold bf(g, j, cols, qi, col);
 
     auto sweeps = [&](auto masked) {
       constexpr bool kMask = decltype(masked)::value;
@@ -1502,135 +1508,9 @@ __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
             }
           }
         };
-        // bias bins of the tile at t0 (see bwd_dq_kernel)
-        auto add_bins = [&](int t0) {
-          const uint16_t* knb = knball + t0;
-          float* mybins = dtab + (wave & 3) * g.nbins;
-          // bin of (this lane's query, key kk): qbins - knb[kk] in bytes
-          char* qbins = reinterpret_cast<char*>(mybins + qoff);
-          auto bin = [&](int kk) -> float& { return *reinterpret_cast<float*>(qbins - knb[kk]); };
-          if (fold) {
-            float fa[2][4], fb[2][4];
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-              for (int g4 = 0; g4 < 4; ++g4) {
-                const float d0 = dsb[kb][4 * g4], d1 = dsb[kb][4 * g4 + 1];
-                const float d2 = dsb[kb][4 * g4 + 2], d3 = dsb[kb][4 * g4 + 3];
-                float f = d3;
-                f = d2 + fnext * dpp_lane<kDppNext>(f);
-                f = d1 + fnext * dpp_lane<kDppNext>(f);
-                fa[kb][g4] = d0 + fnext * dpp_lane<kDppNext>(f);
-                const float p1 = dpp_lane<kDppWavePrev>(d2 * fsend);
-                const float p2 = dpp_lane<kDppWavePrev>(dpp_lane<kDppWavePrev>(d1 * fsend) * fsend);
-                fb[kb][g4] = fkeep * (d3 + p1 + p2);
-              }
-            // One update of this lane: the folded pair sums of key block kb,
-            // group g4 (fa at (q, k), fb at (q, k+3)).
-            auto upd = [&](int kb, int g4, float va, float vb) {
-              const int kk = kb * 32 + 8 * g4 + 4 * half;
-              if (va != 0.0f) bin(kk) += va;
-              if (vb != 0.0f) bin(kk + 3) += vb;
-            };
-            {
-              // Both halves update with one instruction when their keys are at
-              // least 32 tokens apart: the 32 queries of a half are consecutive
-              // tokens, so (q, k) and (q', k') share a bin only if |k - k'| =
-              // |q - q'| < 32.  Half 0 takes block 0 group t while half 1 takes
-              // block 1 group t (keys 32 + 4 or more apart), then half 0 takes
-              // block 1 group t while half 1 takes block 0 group t - 1 (36 or
-              // more), and the two updates left over go alone.
-              if (q0 + wave * kWaveQ + kWaveQ <= n && t0 + 64 <= n) {
-                // Every query of the wave and every key of the tile is a window
-                // token: the updates need no guard (adding 0 to a bin that no
-                // other lane of the instruction touches changes nothing), and
-                // the key words are read before the first update.  Word index of
-                // this lane's group: 36 half + 8t in the first round, 32 - 36 half
-                // + 8t in the second, 32 (half 0) or 28 (half 1) left over.
-                float* w1[4][2];
-                float* w2[3][2];
-                float* wl[2];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                  const int kk = 36 * half + 8 * t;
-                  w1[t][0] = &bin(kk);
-                  w1[t][1] = &bin(kk + 3);
-                }
-#pragma unroll
-                for (int t = 1; t < 4; ++t) {
-                  const int kk = 32 - 36 * half + 8 * t;
-                  w2[t - 1][0] = &bin(kk);
-                  w2[t - 1][1] = &bin(kk + 3);
-                }
-                {
-                  const int kk = half ? 28 : 32;
-                  wl[0] = &bin(kk);
-                  wl[1] = &bin(kk + 3);
-                }
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                  *w1[t][0] += half ? fa[1][t] : fa[0][t];
-                  *w1[t][1] += half ? fb[1][t] : fb[0][t];
-                }
-#pragma unroll
-                for (int t = 1; t < 4; ++t) {
-                  *w2[t - 1][0] += half ? fa[0][t - 1] : fa[1][t];
-                  *w2[t - 1][1] += half ? fb[0][t - 1] : fb[1][t];
-                }
-                if (half == 0) { *wl[0] += fa[1][0]; *wl[1] += fb[1][0]; }
-                __builtin_amdgcn_wave_barrier();
-                if (half == 1) { *wl[0] += fa[0][3]; *wl[1] += fb[0][3]; }
-                __builtin_amdgcn_wave_barrier();
-              } else {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                  const int kb = half, gt = t;
-                  upd(kb, gt, half ? fa[1][t] : fa[0][t], half ? fb[1][t] : fb[0][t]);
-                }
-#pragma unroll
-                for (int t = 1; t < 4; ++t) {
-                  const int kb = 1 - half, gt = t - half;
-                  upd(kb, gt, half ? fa[0][t - 1] : fa[1][t], half ? fb[0][t - 1] : fb[1][t]);
-                }
-                if (half == 0) upd(1, 0, fa[1][0], fb[1][0]);
-                __builtin_amdgcn_wave_barrier();
-                if (half == 1) upd(0, 3, fa[0][3], fb[0][3]);
-                __builtin_amdgcn_wave_barrier();
-              }
-            }
-            // pairs of runs shorter than three lanes that the fold left out
-            if (__builtin_amdgcn_ballot_w64((run < 1 && rest < 2) || (run < 2 && rest < 1)) != 0) {
-#pragma unroll 1
-              for (int hh = 0; hh < 2; ++hh) {
-                if (half == hh) {
-#pragma unroll
-                  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int g4 = 0; g4 < 4; ++g4) {
-                      const int kk = kb * 32 + 8 * g4 + 4 * half;
-#pragma unroll
-                      for (int x = 1; x < 3; ++x)
-                        if (run < x && rest < 3 - x && dsb[kb][4 * g4 + x] != 0.0f)
-                          bin(kk + x) += dsb[kb][4 * g4 + x];
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
-              }
-            }
-          } else {
-#pragma unroll 1
-            for (int hh = 0; hh < 2; ++hh) {
-              if (half == hh) {
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                  for (int r = 0; r < 16; ++r) {
-                    if (dsb[kb][r] != 0.0f) bin(kb * 32 + acc_row(r, half)) += dsb[kb][r];
-                  }
-              }
-              __builtin_amdgcn_wave_barrier();
-            }
-          }
+        auto bins = [&](int t0) {
+          add_bins(dsb, reinterpret_cast<char*>(dtab + (wave & 3) * g.nbins + qoff), knball + t0, bf,
+                   q0 + wave * kWaveQ + kWaveQ <= n && t0 + 64 <= n, half);
         };
         for (int tix = 0; tix < nt; ++tix, ++vis) {
           turn();                                     // barrier A
@@ -1638,16 +1518,16 @@ __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
           if constexpr (kPart == 1) {
             if (wactive) compute(tix, buf);
             lds_barrier();                            // barrier B
-            if (wactive) add_bins(64 * tix);
+            if (wactive) bins(64 * tix);
           } else {
-            if (wactive && tix > 0) add_bins(64 * (tix - 1));
+            if (wactive && tix > 0) bins(64 * (tix - 1));
             lds_barrier();
             if (wactive) compute(tix, buf);
           }
         }
         lds_barrier();
         if constexpr (kPart == 2)
-          if (wactive) add_bins(64 * (nt - 1));
+          if (wactive) bins(64 * (nt - 1));
         if (qvalid) {
           T* row = dq + qtok;
 #pragma unroll
