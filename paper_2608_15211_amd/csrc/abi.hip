@@ -34,6 +34,7 @@ hipError_t launch_attn_bwd(const Geo& g, int dt, bool nhwc, const void* q, const
 bool attn_uses_olo(const Geo& g, int dt);
 size_t bwd_workspace(const Geo& g, int dt);
 size_t attn_max_lds(const Geo& g, int dt);
+int attn_waves(const Geo& g, int dt, int which);
 hipError_t launch_route_rank(const Geo& g, int row_bytes, const RankPlan& plan, const Frag* frags,
                              void* stripe, void* fbuf, void* y, bool forward, hipStream_t st);
 hipError_t launch_frag_copy(const Geo& g, int row_bytes, const RankPlan& plan, const Frag* frags,
@@ -298,6 +299,14 @@ int terra_winattn_uses_o_lo(const terra_geom* g, int dtype) {
 size_t terra_winattn_bwd_workspace_bytes(const terra_geom* g, int dtype) {
   if (check_attn(g, dtype)) return 0;
   return terra::bwd_workspace(make_geo(g), dtype);
+}
+
+// Which form of a kernel a call takes on this device (256 compute units where
+// there is none): no part of the interface, for tests that have to reach a
+// given form.  Host only.
+int terra_internal_attn_waves(const terra_geom* g, int dtype, int which) {
+  const int s = check_attn(g, dtype);
+  return s ? -s : terra::attn_waves(launch_geo(g), dtype, which);
 }
 
 int terra_winattn_bwd(const terra_geom* g, int dtype, const void* q, const void* k, const void* v,

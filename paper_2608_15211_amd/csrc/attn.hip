@@ -1867,6 +1867,13 @@ static size_t dkdv_lds(const Geo& g) {
          (HD > 64 ? 4 * g.wh * g.ww : 0);    // token table (head dim 128 only)
 }
 
+// The 16-bit forward: one or two {K, V} tile pairs, three words per window
+// token, the bias table.
+template <int HD>
+static size_t fwd16_lds(const Geo& g) {
+  const size_t nP = (g.wh * g.ww + 63) & ~63;
+  return tile_pairs((int)nP) * 2 * 64 * HD * 2 + 12 * nP + 4 * (g.nbins + 4);
+}
 // The 16-bit dQ kernel: two {K, V} tile pairs, seven bytes per window token,
 // the bias table and four copies of the bins.
 template <int HD>
@@ -1875,9 +1882,7 @@ static size_t dq16_lds(const Geo& g) {
   return 4 * 64 * HD * 2 + 7 * nP + 4 * (g.nbins + 4) + 16 * g.nbins;
 }
 // The 16-bit dK/dV kernel: one or two {Q, dO} tile pairs, five words per window
-// token, the bias table.  Never more than a workgroup has where the dQ
-// kernel's plan (whose five bias copies decide which windows are accepted)
-// fits.
+// token, the bias table.
 template <int HD>
 static size_t dkdv16_lds(const Geo& g) {
   const size_t nP = (g.wh * g.ww + 63) & ~63;
@@ -1932,6 +1937,20 @@ static bool dq_past_one_round(const Geo& g, int per_cu) {
   return false;
 }
 
+// Eight-wave dQ kernel: 128 channels, windows of more than 512 tokens that
+// keep at least 7 of 8 waves busy, a plan that fits, and work that the
+// general kernel would not do in one round.  Measured against the general
+// kernel (whole backward), 256 compute units: where that one has a chunk of
+// 128 queries a unit or fewer, it is ahead (1024 tokens 0.91x, 651 tokens
+// 0.77 to 0.85x, 768 tokens 0.92x: a chunk of 256 is the longer chain);
+// beyond, this one (1024 tokens 1.10 to 1.28x, 651 tokens 1.00 to 1.23x, 768
+// tokens 1.12x; 576 tokens, 18 of 24 waves, 0.77x).
+static bool dq16_takes(const Geo& g) {
+  const int nb = (g.wh * g.ww + 31) / 32, nqc = (nb + 7) / 8;
+  return g.hd == 128 && g.wh * g.ww > 512 && 8 * nb >= 7 * 8 * nqc && dq16_lds<128>(g) <= 160 * 1024 &&
+         dq_past_one_round(g, (int)((160 * 1024) / dq_lds<__bf16, 128>(g)));
+}
+
 // Waves of a 16-bit workgroup whose plan takes `lds` bytes.  Four where two
 // workgroups fit a CU's LDS, or where those of four leave no CU a second one
 // (1024 tokens of 128 channels, 128 workgroups of four against 64 of eight:
@@ -1964,8 +1983,7 @@ static hipError_t fwd_impl(const Geo& g, const void* q, const void* k, const voi
   const float sl2 = kLog2e / sqrtf((float)HD);
   const bool quad = quad_layout(g);
   if constexpr (sizeof(T) == 2) {
-    const size_t nP = (g.wh * g.ww + 63) & ~63;
-    const size_t lds = tile_pairs((int)nP) * 2 * 64 * HD * 2 + 12 * nP + 4 * (g.nbins + 4);
+    const size_t lds = fwd16_lds<HD>(g);
     const bool direct = direct_ok(k, v);
     const int nw = direct ? waves16<HD>(g, lds) : 8;
     const int nqc = ((g.wh * g.ww + 31) / 32 + nw - 1) / nw;
@@ -2040,20 +2058,11 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
     return std::max(1, std::min(n, nmax));
   };
   int nslice = 1;
-  // Eight-wave dQ kernel: 128 channels, windows of more than 512 tokens that
-  // keep at least 7 of 8 waves busy, a plan that fits, and work that the
-  // general kernel would not do in one round.  Measured against the general
-  // kernel (whole backward), 256 compute units: where that one has a chunk of
-  // 128 queries a unit or fewer, it is ahead (1024 tokens 0.91x, 651 tokens
-  // 0.77 to 0.85x, 768 tokens 0.92x: a chunk of 256 is the longer chain);
-  // beyond, this one (1024 tokens 1.10 to 1.28x, 651 tokens 1.00 to 1.23x, 768
-  // tokens 1.12x; 576 tokens, 18 of 24 waves, 0.77x).
   bool dq16 = false;
   if constexpr (sizeof(T) == 2 && HD == 128) {
-    const int nb = (g.wh * g.ww + 31) / 32, nqc = (nb + 7) / 8;
+    const int nqc = (g.wh * g.ww + 255) / 256;
     const size_t lds = dq16_lds<HD>(g);
-    dq16 = direct_ok(k, v) && g.wh * g.ww > 512 && 8 * nb >= 7 * 8 * nqc && lds <= 160 * 1024 &&
-           dq_past_one_round(g, (int)((160 * 1024) / dq_lds<T, HD>(g)));
+    dq16 = dq16_takes(g) && direct_ok(k, v);
     if (dq16) {
 #define TERRA_LAUNCH_DQ(QD)                                                                          \
   do {                                                                                               \
@@ -2137,15 +2146,29 @@ static hipError_t bwd_impl(const Geo& g, const void* q, const void* k, const voi
 // Element type codes of the C ABI: 0 float, 1 bfloat16, 2 float16.
 
 #if TERRA_ATTN_T == 0
+// Largest LDS plan of the kernels that a geometry may be given (the eight-wave
+// dQ kernel's rule asks for its own plan).
+template <typename T, int HD>
+static size_t max_lds_hd(const Geo& g) {
+  if constexpr (sizeof(T) == 2) return std::max({fwd16_lds<HD>(g), dkdv16_lds<HD>(g), dq_lds<T, HD>(g)});
+  else return std::max({fwd_lds<T, HD>(g), dkdv_lds<T, HD>(g), dq_lds<T, HD>(g)});
+}
 template <typename T>
 static size_t max_lds_t(const Geo& g) {
-  size_t m, d;
-  switch (g.hd) {
-    case 32: m = dkdv_lds<T, 32>(g); d = dq_lds<T, 32>(g); break;
-    case 64: m = dkdv_lds<T, 64>(g); d = dq_lds<T, 64>(g); break;
-    default: m = dkdv_lds<T, 128>(g); d = dq_lds<T, 128>(g); break;
-  }
-  return m > d ? m : d;
+  return g.hd == 32 ? max_lds_hd<T, 32>(g) : g.hd == 64 ? max_lds_hd<T, 64>(g) : max_lds_hd<T, 128>(g);
+}
+
+// Waves of a workgroup of the forward (0), dQ (1) or dK/dV (2) kernel for
+// tensors that start at a multiple of 16 bytes; 0 where a window-resident
+// kernel runs.
+template <int HD>
+static int waves_of(const Geo& g, int which) {
+  return which == 1 ? (dq16_takes(g) ? 8 : 4) : waves16<HD>(g, which == 0 ? fwd16_lds<HD>(g) : dkdv16_lds<HD>(g));
+}
+int attn_waves(const Geo& g, int dt, int which) {
+  if (which == 0 ? win_fwd_ok(g, dt == kBF16) : win_bwd_ok(g, dt == kBF16)) return 0;
+  if (dt == kF32) return 4;
+  return g.hd == 32 ? waves_of<32>(g, which) : g.hd == 64 ? waves_of<64>(g, which) : waves_of<128>(g, which);
 }
 
 size_t attn_max_lds(const Geo& g, int dt) {
