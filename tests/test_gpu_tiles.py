@@ -1,7 +1,7 @@
 """16-bit dK/dV kernel at the edges of its plan: fewer keys than one wave,
 two, three and four waves a workgroup, a window one token past a 64-token
-tile, chunks whose last waves own no key, eight waves (windows whose LDS
-plan fits a CU once), widths that are and are not multiples of 4, both wrap
+tile, chunks whose last waves own no key, windows whose LDS plan fits a CU once
+(four waves on grids this small), widths that are and are not multiples of 4, both wrap
 masks; bf16 and fp16, both layouts, against the fp64 oracle.
 
 The bars are those of one attention call in 16-bit storage (max abs 2e-2,
@@ -27,7 +27,7 @@ CASES = [
     (2, 64, (17, 16), (34, 37), 1),      # 272 tokens: the last chunk owns 16 keys
     (1, 64, (24, 24), (30, 41), 3),      # 576 tokens, ragged both ways
     (2, 128, (8, 8), (16, 19), 1),       # two waves at 128 channels
-    (1, 128, (23, 29), (25, 33), 1),     # 667 tokens: eight waves, odd width
+    (1, 128, (23, 29), (25, 33), 1),     # 667 tokens, odd width
     (1, 128, (32, 32), (40, 48), 1),     # 1024 tokens
 ]
 

@@ -1,0 +1,50 @@
+"""The GPU tests' cases reach the kernel forms that they are there for, by the
+library's own rules (256 compute units where there is no GPU)."""
+
+import ctypes
+import os
+
+import pytest
+
+P = pytest.importorskip("paper_2608_15211_amd")
+pytest.importorskip("torch")
+
+import test_gpu_dq_waves as dq_waves  # noqa: E402
+
+pytestmark = pytest.mark.skipif(not os.path.exists(P.LIB_PATH), reason="libterra_swin.so not built")
+
+FWD, DQ, DKDV = 0, 1, 2
+
+
+def attn_waves(cfg, dtype, which):
+    code = {"f32": P.TERRA_F32, "bf16": P.TERRA_BF16, "f16": P.TERRA_F16}[dtype]
+    n = P.lib().terra_internal_attn_waves(ctypes.byref(P._geom(cfg)), code, which)
+    assert n >= 0
+    return n
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("heads,win,grid,mask", dq_waves.CASES)
+def test_eight_wave_cases(heads, win, grid, mask, dtype):
+    cfg = dq_waves.config(heads, win, grid, mask, dtype)
+    assert [attn_waves(cfg, dtype, w) for w in (FWD, DQ, DKDV)] == [8, 8, 8]
+
+
+# Both sides of the eight-wave dQ kernel's line: measured whole backwards, us,
+# general kernel then eight waves (bf16, 128 channels).
+LINE = [
+    (8, (32, 32), (64, 64), 4),          # 157.1, 170.0
+    (12, (32, 32), (64, 64), 8),         # 223.8, 177.0
+    (3, (21, 31), (64, 96), 4),          # 159.7, 196.9: 9 of 16 windows are full
+    (4, (21, 31), (64, 96), 8),          # 219.8, 199.3
+    (2, (21, 31), (64, 200), 4),         # 169.2, 199.9
+    (6, (24, 32), (60, 80), 8),          # 146.0, 129.2
+    (3, (32, 32), (80, 80), 4),          # 146.2, 158.4
+    (4, (32, 32), (80, 80), 8),          # 168.7, 161.8
+    (12, (28, 28), (56, 56), 4),         # 25 of 32 waves busy
+]
+
+
+@pytest.mark.parametrize("heads,win,grid,waves", LINE)
+def test_eight_wave_line(heads, win, grid, waves):
+    assert attn_waves(dq_waves.config(heads, win, grid, 1, "bf16"), "bf16", DQ) == waves
