@@ -24,6 +24,8 @@ hipError_t launch_block_bwd(const Geo& g, const void* dx2, const void* x, const 
                             const BlockSaved& s, void* dx, const BlockGrads& gr, float* dtable, void* ws,
                             hipStream_t st);
 size_t block_bwd_workspace(const Geo& g);
+int block_product_plan(int M, int N, int K, int max_split);
+int block_wgrad_plan(int T, int Nl, int Kl);
 hipError_t launch_attn_fwd(const Geo& g, int dt, bool nhwc, const void* q, const void* k,
                            const void* v, const float* table, void* o, void* olo, float* lse,
                            hipStream_t st);
@@ -304,6 +306,10 @@ size_t terra_winattn_bwd_workspace_bytes(const terra_geom* g, int dtype) {
 // Which form of a kernel a call takes on this device (256 compute units where
 // there is none): no part of the interface, for tests that have to reach a
 // given form.  Host only.
+int terra_internal_product_plan(int M, int N, int K, int max_split) {
+  return terra::block_product_plan(M, N, K, max_split);
+}
+int terra_internal_wgrad_plan(int T, int Nl, int Kl) { return terra::block_wgrad_plan(T, Nl, Kl); }
 int terra_internal_attn_waves(const terra_geom* g, int dtype, int which) {
   const int s = check_attn(g, dtype);
   return s ? -s : terra::attn_waves(launch_geo(g), dtype, which);

@@ -923,6 +923,9 @@ __global__ __launch_bounds__(256) void block_bwd_prep_kernel(BwdPrep w, const bf
 // ---------------------------------------------------------------------------
 // Host side.
 // ---------------------------------------------------------------------------
+// Contraction indices of each of ns slices: whole stages.
+static int slice_len(int K, int ns) { return ((K + ns - 1) / ns + kBK - 1) / kBK * kBK; }
+
 template <bool AKROW, bool BKROW, int EPI, bool SEG, int NW>
 static hipError_t gemm_form(const Mat& A, const Mat& B, const EpiArgs& ep, int M, int N, int K, int nsplit,
                             hipStream_t st) {
@@ -930,7 +933,7 @@ static hipError_t gemm_form(const Mat& A, const Mat& B, const EpiArgs& ep, int M
   // stages of A and B: 3 + 2 of 32 KB (160 KB), or 4 + 4 of 16 KB (128 KB)
   constexpr size_t lds = (NW == 8 ? 5 : 8) * (size_t)BM * kBK * sizeof(bf16);
   const int tiles = ((M + BM - 1) / BM) * ((N + BM - 1) / BM);
-  const int kslice = ((K + nsplit - 1) / nsplit + kBK - 1) / kBK * kBK;
+  const int kslice = slice_len(K, nsplit);
   hipLaunchKernelGGL((gemm_kernel<AKROW, BKROW, EPI, SEG, NW>), dim3(tiles * nsplit), dim3(NW * 64), lds, st, A, B,
                      ep, M, N, K, kslice);
   return hipGetLastError();
@@ -944,6 +947,12 @@ static hipError_t gemm_form(const Mat& A, const Mat& B, const EpiArgs& ep, int M
 struct Plan {
   int nw, ns;
 };
+// The plan without slices past the contraction's end (2056 tokens in eight
+// slices of 320 end in the seventh).
+static Plan without_empty(Plan p, int K) {
+  const int len = slice_len(K, p.ns);
+  return {p.nw, (K + len - 1) / len};
+}
 static double plan_cost(int M, int N, int K, Plan p) {
   const int bm = p.nw == 8 ? kBM : kBS;
   const int tiles = ((M + bm - 1) / bm) * ((N + bm - 1) / bm);
@@ -959,7 +968,7 @@ static Plan plan_product(int M, int N, int K, int max_split) {
     const double d = plan_cost(M, N, K, {4, ns});
     if (d < c) { c = d; best = {4, ns}; }
   }
-  return best;
+  return without_empty(best, K);
 }
 
 template <bool AKROW, bool BKROW, int EPI, bool SEG = false>
@@ -1154,7 +1163,18 @@ static Plan wgrad_plan(int T, int Nl, int Kl) {
     const double d = plan_cost(Nl, Kl, T, {4, ns});
     if (d < c) { c = d; best = {4, ns}; }
   }
-  return best;
+  return without_empty(best, T);
+}
+
+// For tests: waves and slices, 100 nw + ns, of a product and of a weight
+// gradient.
+int block_product_plan(int M, int N, int K, int max_split) {
+  const Plan p = plan_product(M, N, K, max_split);
+  return 100 * p.nw + p.ns;
+}
+int block_wgrad_plan(int T, int Nl, int Kl) {
+  const Plan p = wgrad_plan(T, Nl, Kl);
+  return 100 * p.nw + p.ns;
 }
 
 // Backward workspace layout (bytes, 256-aligned pieces).

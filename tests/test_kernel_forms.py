@@ -48,3 +48,24 @@ LINE = [
 @pytest.mark.parametrize("heads,win,grid,waves", LINE)
 def test_eight_wave_line(heads, win, grid, waves):
     assert attn_waves(dq_waves.config(heads, win, grid, 1, "bf16"), "bf16", DQ) == waves
+
+
+def block_plans(T, C):
+    """(waves, slices) of each of the block's products."""
+    L = P.lib()
+    product = {"qkv": (3 * C, C, 1), "proj": (C, C, 1), "fc1": (4 * C, C, 1), "fc2": (C, 4 * C, 8),
+               "dln1": (C, 3 * C, 8)}
+    wgrad = {"w_qkv": (3 * C, C), "w_proj": (C, C), "w_fc1": (4 * C, C), "w_fc2": (C, 4 * C)}
+    out = {n: L.terra_internal_product_plan(T, *a) for n, a in product.items()}
+    out.update({n: L.terra_internal_wgrad_plan(T, *a) for n, a in wgrad.items()})
+    return {n: divmod(v, 100) for n, v in out.items()}
+
+
+@pytest.mark.parametrize("C", [128, 384, 768, 1408, 1920])
+def test_no_empty_contraction_slice(C):
+    """Slices hold whole 64-deep stages; the last one must hold some too."""
+    for T in list(range(1, 400, 13)) + list(range(400, 40000, 211)) + [2056, 138240]:
+        for n, (_, slices) in block_plans(T, C).items():
+            depth = T if n.startswith("w_") else {"fc2": 4 * C, "dln1": 3 * C}.get(n, C)
+            stages = -(-depth // 64)
+            assert (slices - 1) * -(-stages // slices) < stages, (T, n, slices)
