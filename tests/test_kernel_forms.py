@@ -9,6 +9,7 @@ import pytest
 P = pytest.importorskip("paper_2608_15211_amd")
 pytest.importorskip("torch")
 
+import test_gpu_block_waves as block_waves  # noqa: E402
 import test_gpu_dq_waves as dq_waves  # noqa: E402
 
 pytestmark = pytest.mark.skipif(not os.path.exists(P.LIB_PATH), reason="libterra_swin.so not built")
@@ -59,6 +60,21 @@ def block_plans(T, C):
     out = {n: L.terra_internal_product_plan(T, *a) for n, a in product.items()}
     out.update({n: L.terra_internal_wgrad_plan(T, *a) for n, a in wgrad.items()})
     return {n: divmod(v, 100) for n, v in out.items()}
+
+
+@pytest.mark.parametrize("cfg,eight", block_waves.CASES, ids=[c.name for c, _ in block_waves.CASES])
+def test_eight_wave_products(cfg, eight):
+    k = cfg.geom_kwargs()
+    plans = block_plans(k["B"] * k["H"] * k["W"], k["C"])
+    assert {n for n, (nw, _) in plans.items() if nw == 8} == set(eight)
+
+
+def test_rest_of_rows_is_ragged():
+    k = block_waves.CASES[-1][0].geom_kwargs()
+    T, C = k["B"] * k["H"] * k["W"], k["C"]
+    rows, cols = -(-T // 256), -(-C // 256)
+    whole = rows * cols // 256 * 256 // cols
+    assert 0 < whole < rows and T % 128 != 0 and C % 256 == 128
 
 
 @pytest.mark.parametrize("C", [128, 384, 768, 1408, 1920])
