@@ -68,20 +68,23 @@ struct EpiArgs {
   const float* rstd;   // per-column sum of the folded weights (lns) and constant (lnc)
   const float* lns;
   const float* lnc;
-  // EPI_GELU_GRAD: column sums of the bf16 output over each wave's 128 rows,
-  // partial row 2 (tile row) + (wave row), ld = N (nullable)
+  // EPI_GELU_GRAD: column sums of the bf16 output over the rows of each wave
+  // (half a tile's: 128, in the four-wave form 64), partial row 2 (tile row) +
+  // (wave row), ld = N (nullable)
   float* colpart;
 };
 
 // Phi(x), the standard normal distribution function: with a = |x|,
 // Phi(-a) = 2^P(a), P a degree-8 polynomial fitted to log2 Phi(-a) on
-// [0, 5.6] (weighted minimax, error of Phi at most 4.5e-8 in float32
-// arithmetic; P falls without bound beyond, where Phi(-a) < 1.1e-8).  One
-// exponential and no division: the MLP epilogues are bound by vector
-// instructions.  Against Abramowitz and Stegun's 7.1.26 (a reciprocal and an
-// exponential, error 7.5e-8) the fc1 epilogue goes from 21.6 to 17.6
-// instructions an element and the 128 x 1080 fc1 product from 1026 to 959 us,
-// dh from 890 to 851.
+// [0, 5.6] (weighted minimax; P falls without bound beyond, where Phi(-a) <
+// 1.1e-8).  Largest error as the hardware computes it, over 5e6 points from
+// -40 to 40: Phi 5.7e-8 below zero and 8.2e-8 above (one minus it), GELU
+// 4.0e-7, its derivative 1.3e-7.  One exponential and no division: the MLP
+// epilogues are bound by vector instructions.  Against Abramowitz and
+// Stegun's 7.1.26 (a reciprocal and an exponential: 2.9e-7, 4.7e-7 and 3.2e-7
+// on the same points, and no interval where it is closer) the fc1 epilogue
+// goes from 21.6 to 17.6 instructions an element and the 128 x 1080 fc1
+// product from 1026 to 959 us, dh from 890 to 851.
 __device__ inline float phi_f(float x) {
   const float a = fabsf(x);
   float p = -2.772049e-06f;
@@ -1367,7 +1370,7 @@ hipError_t launch_block_bwd(const Geo& g, const void* dx2, const void* x, const 
   TERRA_TRY(wgrad<false>(mat(dx2, C, T), mat(s.a, 4 * C, T), T, C, 4 * C, gr.w_fc2, ws, w, st));
   TERRA_TRY(colsum(mat(dx2, C, T), C, cpart, gr.b_fc2, w, st));
   // db1 = colsum(dh) from the same epilogue: per-wave partial rows, then a
-  // fixed-order sum of the 2 ceil(T / 256) partials
+  // fixed-order sum of the two of each row tile
   ep.out[0] = dh; ep.split = 4 * C; ep.aux = (const bf16*)s.h; ep.colpart = cpart;
   TERRA_TRY((gemm<true, true, EPI_GELU_GRAD>(mat(dx2, C, T), mat(wt_fc2, C, 4 * C), ep, T, 4 * C, C, st)));
   {
