@@ -58,15 +58,16 @@ template <typename T, int HD> constexpr int tile_of() { return (sizeof(T) == 4 &
 constexpr int kPad = 8;         // LDS row padding, elements
 constexpr int kLabBad = 0xFF;   // label of padding slots (never matches)
 
-// Work item of a forward workgroup.  The hardware hands consecutive
-// workgroups to the 8 XCDs in turn; giving each XCD one contiguous range of
-// items puts the query chunks of one window and head, which stage the same
-// K/V tiles, behind the same L2 (forward -2 to -4 %; measured no better or
-// slower for the dK/dV and dQ kernels, which keep the plain order).  The grid
-// is rounded up to a multiple of 8 and the padding workgroups exit at once.
+// Work item of a workgroup, one contiguous range of items per XCD: the hardware
+// hands consecutive workgroups to the 8 XCDs in turn, and this puts the query
+// chunks of one window and head, which stage the same K/V tiles, behind the
+// same L2 (float32 forward -2 to -4 %; the eight-wave dQ kernel; measured no
+// better or slower for the general dQ and the float32 dK/dV kernel, which keep
+// the plain order).  The grid is rounded up to a multiple of 8 and the padding
+// workgroups exit at once.
 __device__ inline int xcd_item(int bid, int nblocks) { return (bid & 7) * (nblocks >> 3) + (bid >> 3); }
 static inline int grid8(int n) { return (n + 7) & ~7; }
-// The same for the 16-bit kernels with one unit of `unit` consecutive items
+// The same for the 16-bit forward and dK/dV with one unit of `unit` consecutive items
 // (the chunks of a window and head, and the heads that share a 128-byte
 // line) per XCD in turn: contiguous ranges gave some XCDs the full windows
 // and others the short ones of a ragged last row (25 rows of 24-row windows:

@@ -326,9 +326,9 @@ __device__ __forceinline__ void buffer_load_lds16x4(const i32x4& rsrc, const voi
       : "memory", "m0", "scc");
 }
 
-// Buffer descriptor of a whole operand: base, size in bytes (below 2^31, so
-// that the offset 2^31 used for rows outside the operand is past the end and
-// reads zeros).
+// Buffer descriptor: base and size in bytes; offsets from the size on read
+// zeros.  (The block's operands are below 2^31 bytes, so that 2^31 is such an
+// offset; one image of an attention tensor is below 2^32.)
 __device__ inline i32x4 buffer_rsrc(const void* base, uint32_t bytes) {
   const uint64_t b = (uint64_t)base;
   i32x4 r;
