@@ -1130,7 +1130,7 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkdv_kernel(
 // direct-to-LDS buffers, one barrier a tile, O (and O_lo) out in whole row
 // pieces, a copy of the walk for masked and unmasked windows.  Bound by vector
 // instructions (576 tokens).  Measured (us, before -> now): 144 tokens of 32
-// channels 42 -> 34, 576 of 64 with O_lo 1332 -> 1224, 64 of 128 309 -> 273,
+// channels 42 -> 34, 576 of 64 with O_lo 1332 -> 1224, 64 of 128 309 -> 218,
 // 1024 of 128 with O_lo 1260 -> 1100.
 // ---------------------------------------------------------------------------
 template <typename T, int HD, bool NHWC, bool QUAD, bool SPLIT, int NW, bool DIRECT = true>
@@ -1565,8 +1565,8 @@ __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
 // What bounds it: latency, at two waves per SIMD (registers).  So
 // * everything per query that does not depend on the tile (row address, bias
 //   offset, label, log-sum-exp, D) is worked out once per workgroup into
-//   LDS, and direct-to-LDS loads fill two tile buffers: one barrier a tile,
-//   no wait for a load just issued;
+//   LDS, and direct-to-LDS loads fill two tile buffers (one where the window
+//   is a single tile): one barrier a tile, no wait for a load just issued;
 // * up to head dim 64 the compiler is held to four phases that each issue
 //   the LDS reads of the next;
 // * masked and unmasked windows have their own copy of the walk (merged in
@@ -1575,7 +1575,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
 //   their common tiles, and dK, dV leave in whole row pieces.
 // Measured (us, before -> now): 64-token windows of 32 channels on 128 x 256
 // x 6 heads 28 -> 19, 144 tokens 65 -> 47, 576 tokens of 64 channels 1820 ->
-// 1603, 1024 tokens of 128 channels 1650 -> 1381, 64 tokens 458 -> 434.
+// 1603, 1024 tokens of 128 channels 1650 -> 1381, 64 tokens 458 -> 373.
 // ---------------------------------------------------------------------------
 template <typename T, int HD, bool NHWC, bool QUAD, int NW, bool DIRECT = true>
 __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
