@@ -67,14 +67,19 @@ constexpr int kLabBad = 0xFF;   // label of padding slots (never matches)
 // workgroups exit at once.
 __device__ inline int xcd_item(int bid, int nblocks) { return (bid & 7) * (nblocks >> 3) + (bid >> 3); }
 static inline int grid8(int n) { return (n + 7) & ~7; }
-// The same for the 16-bit forward and dK/dV with one unit of `unit` consecutive items
-// (the chunks of a window and head, and the heads that share a 128-byte
-// line) per XCD in turn: contiguous ranges gave some XCDs the full windows
-// and others the short ones of a ragged last row (25 rows of 24-row windows:
-// dK/dV 233 -> 271 us).
+// The same for the 16-bit forward and dK/dV with one unit of `unit`
+// consecutive items (the chunks of a window and head, and the heads that share
+// a 128-byte line) per XCD in turn: contiguous ranges gave some XCDs the full
+// windows and others the short ones of a ragged last row (25 rows of 24-row
+// windows: dK/dV 233 -> 271 us).  TURN (dK/dV): each turn of eight units starts
+// one XCD further, or a row of windows that is a whole number of turns puts
+// its ragged last window on the same XCDs in every row (21 x 31 windows on 64 x
+// 96 tokens, 12 heads of 32: 54 us, with it 42).  The forward measured 0.93 to
+// 1.07 with it and keeps the plain turn.
+template <bool TURN>
 __device__ inline int xcd_unit_item(int bid, int unit) {
   const int idx = bid >> 3, u = idx / unit;
-  return (u * 8 + (bid & 7)) * unit + (idx - u * unit);
+  return (u * 8 + ((TURN ? bid + u : bid) & 7)) * unit + (idx - u * unit);
 }
 static inline int unit_grid(int n, int unit) { return ((n + unit - 1) / unit + 7) / 8 * 8 * unit; }
 // Up to two workgroups a CU, whole units would leave some XCDs short: single
@@ -1148,7 +1153,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd16_kernel(
   int* klabs = knb + nP;                              // [nP] label
   float* tab = reinterpret_cast<float*>(klabs + nP);  // [nbins+4], reversed
 
-  int bid = xcd_unit_item(blockIdx.x, unit);
+  int bid = xcd_unit_item<false>(blockIdx.x, unit);
   if (bid >= g.B * g.nwin * g.heads * nqc) return;
   const int qc = bid % nqc; bid /= nqc;
   const int h = bid % g.heads; bid /= g.heads;
@@ -1595,7 +1600,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
   float* qd = ql + nP;                                // [nP] -D
   float* tab = qd + nP;                               // [nbins+4], forward order
 
-  int bid = xcd_unit_item(blockIdx.x, unit);
+  int bid = xcd_unit_item<true>(blockIdx.x, unit);
   if (bid >= g.B * g.nwin * g.heads * nkc) return;
   const int kc = bid % nkc; bid /= nkc;
   const int h = bid % g.heads; bid /= g.heads;
