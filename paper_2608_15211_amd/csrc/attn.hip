@@ -1580,7 +1580,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dq16_kernel(
 //   their common tiles, and dK, dV leave in whole row pieces.
 // Measured (us, before -> now): 64-token windows of 32 channels on 128 x 256
 // x 6 heads 28 -> 19, 144 tokens 65 -> 47, 576 tokens of 64 channels 1820 ->
-// 1603, 1024 tokens of 128 channels 1650 -> 1381, 64 tokens 458 -> 373.
+// 1603, 1024 tokens of 128 channels 1650 -> 1381, 64 tokens 458 -> 368.
 // ---------------------------------------------------------------------------
 template <typename T, int HD, bool NHWC, bool QUAD, int NW, bool DIRECT = true>
 __global__ __launch_bounds__(NW * 64, 2) void bwd_dkdv16_kernel(
